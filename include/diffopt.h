@@ -422,15 +422,17 @@ int diffopt_rmsprop_bwd_tree(const diffopt_segtable* table,
  *   noise       [num_samples][n], row-major (row i is z_i)
  *   out         [num_samples][n], row i = theta + sigma z_i; with antithetic != 0
  *               [2 num_samples][n], rows num_samples + i = theta - sigma z_i
- * num_samples <= 65,535 x 8.  n % 4 == 0 with 16-byte aligned pointers takes
- * 128-bit accesses; anything else an element path with the same result.    */
+ * num_samples <= 65,535 x 8.  Any n and any 4-byte alignment take 128-bit
+ * accesses; the result does not depend on the alignment.                   */
 int diffopt_es_perturb(const float* params, const float* noise,
                        int64_t num_samples, int64_t n, double sigma,
                        int32_t antithetic, float* out, void* stream);
 
 /* es_estimate (Sec. 2.2, the Monte-Carlo estimate of the smoothed gradient):
- * grad_j = scale * sum_i weights_i noise_ij, accumulated in
- * sample order in fp32.  weights is a DEVICE array [num_samples] formed by the
+ * grad_j = scale * sum_i weights_i noise_ij, accumulated in fp32 in an order
+ * that depends on n and num_samples alone: sample order, or (few parameters)
+ * sample order within up to 64 groups of consecutive samples whose sums are
+ * then added in order.  weights is a DEVICE array [num_samples] formed by the
  * caller from its evaluations f_i:
  *   plain:       w_i = f(theta + s z_i),                    scale = 1/(N s)
  *   baseline:    w_i = f(theta + s z_i) - f(theta),         scale = 1/(N s)
@@ -463,12 +465,11 @@ int diffopt_es_estimate(const float* noise, const float* weights,
  * The same seed gives the same z in both calls, and in any launch shape.
  *
  * es_perturb_gaussian: out as for diffopt_es_perturb ([N][n], or [2N][n]
- *   with antithetic != 0); num_samples <= 65,535 x 8.  n % 4 == 0 with
- *   16-byte aligned pointers takes 128-bit accesses, anything else an element
- *   path with the same result.
- * es_estimate_gaussian: grad_j = scale * sum_i w_i z_ij, accumulated in
- *   sample order in fp32, with the weights and scale formed in the kernel
- *   from the caller's evaluations `fvals` (a DEVICE array):
+ *   with antithetic != 0); num_samples <= 65,535 x 8.  Rows are written in
+ *   128-bit stores whatever n and the alignment, with the same result.
+ * es_estimate_gaussian: grad_j = scale * sum_i w_i z_ij, accumulated in fp32
+ *   as diffopt_es_estimate does (groups of consecutive samples from 16
+ *   samples on), with the weights and scale formed in the kernel from the caller's evaluations `fvals` (a DEVICE array):
  *     method 0, plain:      w_i = f_i,            scale = 1/(N s), fvals [N]
  *     method 1, baseline:   w_i = f_i - *f0,      scale = 1/(N s), fvals [N],
  *                           f0 a DEVICE pointer to f(theta)

@@ -15,6 +15,11 @@ namespace diffopt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Four consecutive floats at any 4-byte aligned address: loads and stores of
+// it are the same single 128-bit instructions as those of f32x4 (gfx950
+// accepts dword-aligned 128-bit global accesses).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // Coefficients derived on the host in fp64 and rounded once to fp32.
 struct AdamCoef {
   float b1, omb1, b2, omb2;  // b1, 1-b1, b2, 1-b2

@@ -47,86 +47,97 @@ struct PerturbPlan {
   int32_t P;                        // classes: rows i and i + P share a phase
 };
 
-// Grid: x over 16-byte vectors of theta (shifted per class), y over groups of
-// kRows same-phase samples.  The dispatcher walks x fastest, so the chip
+// Grid: x over 4-element vectors of theta (shifted per class), y over groups
+// of kRows same-phase samples.  The dispatcher walks x fastest, so the chip
 // works through one group of rows at a time (few DRAM pages open at once);
 // theta is re-read per group, mostly from the Infinity Cache.  A lane issues
-// all of its group's row loads first.
-__global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const float* noise, int64_t N,
-                                                       int64_t nv, float sigma, int antithetic, float* out,
-                                                       PerturbPlan plan) {
+// all of its group's row loads first.  Rows are n elements apart, so with
+// n % 4 != 0 (or pointers off 16 bytes) their vectors are only 4-byte aligned
+// and the plan has one unshifted class; vector nv then holds the n % 4 last
+// elements of each row, moved one by one.
+__global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const float* noise, int64_t N, int64_t n,
+                                                       float sigma, int antithetic, float* out, PerturbPlan plan) {
   int r = 0;  // phase class of this group
   while (r + 1 < plan.P && (int64_t)blockIdx.y >= plan.gstart[r + 1]) ++r;
   const int64_t v = (int64_t)blockIdx.x * kEB + threadIdx.x - plan.shift[r];
-  if (v < 0 || v >= nv) return;
+  const int64_t nv = n >> 2;
+  if (v < 0 || 4 * v >= n) return;
   const int64_t P = plan.P;
   const int64_t i0 = r + P * ((int64_t)kRows * ((int64_t)blockIdx.y - plan.gstart[r]));  // first row; rows step by P
-  const f32x4 t = ld(reinterpret_cast<const f32x4*>(theta) + v);
-  const f32x4* z = reinterpret_cast<const f32x4*>(noise) + v;
-  f32x4* o = reinterpret_cast<f32x4*>(out) + v;
+  const float* z = noise + 4 * v;
+  float* o = out + 4 * v;
+  if (v == nv) {
+    for (int64_t i = i0; i < N && i < i0 + P * kRows; i += P)
+      for (int e = 0; e < (int)(n & 3); ++e) {
+        const float x = z[i * n + e], t = theta[4 * v + e];
+        o[i * n + e] = fmaf(sigma, x, t);
+        if (antithetic) o[(N + i) * n + e] = fmaf(-sigma, x, t);
+      }
+    return;
+  }
+  const f32x4 t = ld(reinterpret_cast<const f32x4u*>(theta) + v);
+  const auto in = [&](int64_t i) { return reinterpret_cast<const f32x4u*>(z + i * n); };
+  const auto to = [&](int64_t i) { return reinterpret_cast<f32x4u*>(o + i * n); };
   if (i0 + P * (kRows - 1) < N) {
     f32x4 rw[kRows];
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) rw[u] = ld(z + (i0 + P * u) * nv);
+    for (int u = 0; u < kRows; ++u) rw[u] = ld(in(i0 + P * u));
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
       const int64_t i = i0 + P * u;
-      f32x4 a, b;
+      f32x4u a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = fmaf(sigma, rw[u][e], t[e]);
         b[e] = fmaf(-sigma, rw[u][e], t[e]);
       }
-      st(o + i * nv, a);
-      if (antithetic) st(o + (N + i) * nv, b);
+      st(to(i), a);
+      if (antithetic) st(to(N + i), b);
     }
   } else {
     for (int64_t i = i0; i < N; i += P) {
-      const f32x4 rw = ld(z + i * nv);
-      f32x4 a, b;
+      const f32x4 rw = ld(in(i));
+      f32x4u a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = fmaf(sigma, rw[e], t[e]);
         b[e] = fmaf(-sigma, rw[e], t[e]);
       }
-      st(o + i * nv, a);
-      if (antithetic) st(o + (N + i) * nv, b);
+      st(to(i), a);
+      if (antithetic) st(to(N + i), b);
     }
   }
 }
 
-__global__ __launch_bounds__(kEB) void es_perturb_scalar(const float* theta, const float* noise, int64_t N,
-                                                          int64_t n, float sigma, int antithetic, float* out) {
-  const int64_t j = (int64_t)blockIdx.x * kEB + threadIdx.x;
-  if (j >= n) return;
-  const float t = theta[j];
-  const int64_t i0 = (int64_t)blockIdx.y * kRows;
-  const int64_t i1 = i0 + kRows < N ? i0 + kRows : N;
-  for (int64_t i = i0; i < i1; ++i) {
-    const float z = noise[i * n + j];
-    out[i * n + j] = fmaf(sigma, z, t);
-    if (antithetic) out[(N + i) * n + j] = fmaf(-sigma, z, t);
-  }
-}
-
-// Each lane owns kEstU 16-byte slices of grad, kEB vectors apart, and
+// Each lane owns kEstU 4-element slices of grad, kEB vectors apart, and
 // accumulates the N rows in sample order, kUnroll rows in flight.  A
 // workgroup thus covers kEB * kEstU contiguous vectors of every row; rows
-// start at varying 16-byte phases of the 128-byte lines, so the lines at the
-// ends of a workgroup's range are also fetched by its neighbours, and a wider
-// range makes that a smaller share.
+// start at varying phases of the 128-byte lines, so the lines at the ends of a
+// workgroup's range are also fetched by its neighbours, and a wider range
+// makes that a smaller share.  Vectors need only 4-byte alignment; the lane of
+// vector nv takes the n % 4 last elements one by one.
 __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const float* __restrict__ w, int64_t N,
-                                                        int64_t nv, float scale, float* grad) {
+                                                        int64_t n, float scale, float* grad) {
   const int64_t v0 = (int64_t)blockIdx.x * (kEB * kEstU) + threadIdx.x;
-  const f32x4* z = reinterpret_cast<const f32x4*>(noise);
+  const int64_t nv = n >> 2;
   f32x4 acc[kEstU];
   bool on[kEstU];
 #pragma unroll
   for (int q = 0; q < kEstU; ++q) {
     acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     on[q] = v0 + (int64_t)q * kEB < nv;
+    if (v0 + (int64_t)q * kEB == nv) {
+      for (int64_t e = 4 * nv; e < n; ++e) {
+        float t = 0.0f;
+        for (int64_t i = 0; i < N; ++i) t = fmaf(w[i], noise[i * n + e], t);
+        grad[e] = scale * t;
+      }
+    }
   }
   if (!on[0]) return;
+  const auto row = [&](int64_t i, int q) {
+    return reinterpret_cast<const f32x4u*>(noise + i * n) + v0 + (int64_t)q * kEB;
+  };
   int64_t i = 0;
   for (; i + kUnroll <= N; i += kUnroll) {
     f32x4 r[kUnroll][kEstU];
@@ -134,7 +145,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
     for (int u = 0; u < kUnroll; ++u)
 #pragma unroll
       for (int q = 0; q < kEstU; ++q)
-        if (on[q]) r[u][q] = ld(z + (i + u) * nv + v0 + (int64_t)q * kEB);
+        if (on[q]) r[u][q] = ld(row(i + u, q));
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const float wi = w[i + u];
@@ -150,7 +161,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
 #pragma unroll
     for (int q = 0; q < kEstU; ++q)
       if (on[q]) {
-        const f32x4 r = ld(z + i * nv + v0 + (int64_t)q * kEB);
+        const f32x4 r = ld(row(i, q));
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(wi, r[e], acc[q][e]);
       }
@@ -158,20 +169,109 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
 #pragma unroll
   for (int q = 0; q < kEstU; ++q)
     if (on[q]) {
-      f32x4 out;
+      f32x4u out;
 #pragma unroll
       for (int e = 0; e < 4; ++e) out[e] = scale * acc[q][e];
-      st(reinterpret_cast<f32x4*>(grad) + v0 + (int64_t)q * kEB, out);
+      st(reinterpret_cast<f32x4u*>(grad) + v0 + (int64_t)q * kEB, out);
     }
 }
 
-__global__ __launch_bounds__(kEB) void es_estimate_scalar(const float* noise, const float* __restrict__ w, int64_t N,
-                                                           int64_t n, float scale, float* grad) {
-  const int64_t j = (int64_t)blockIdx.x * kEB + threadIdx.x;
-  if (j >= n) return;
-  float acc = 0.0f;
-  for (int64_t i = 0; i < N; ++i) acc = fmaf(w[i], noise[i * n + j], acc);
-  grad[j] = scale * acc;
+// ---- estimates of few parameters: the samples split over a workgroup ---------
+//
+// With few parameters the one-lane-per-slice estimates leave most of the chip
+// idle while each lane walks all N samples: they are bound by one serial
+// chain.  Here a workgroup of kSB threads owns kSB / G slots (a slot: the E
+// parameters one lane accumulates) and cuts the samples into G contiguous
+// groups; each lane sums its group in sample order, and the G partial sums of
+// a parameter are added through LDS in group order: first eight (or four)
+// neighbouring groups, then those sums.  The order depends only on n, N and
+// the entry point, so results are reproducible, and a sum of short ordered
+// sums rounds no worse than one long chain.
+constexpr int kSB = 1024;
+
+// Samples [lo, hi) of group g of G.
+__device__ __forceinline__ void group_range(int64_t N, int G, int g, int64_t& lo, int64_t& hi) {
+  lo = N * g / G;
+  hi = N * (g + 1) / G;
+}
+
+// Adds the G partial sums of each of the workgroup's SLOTS * E parameters:
+// acc[e] is this lane's partial sum for parameter slot * E + e of the
+// workgroup, slot = threadIdx.x % SLOTS, group = threadIdx.x / SLOTS.  Returns
+// the total of parameter threadIdx.x for threads below SLOTS * E.  Every
+// thread of the workgroup calls it.
+template <int SLOTS, int E>
+__device__ __forceinline__ float group_sum(const float (&acc)[E]) {
+  constexpr int O = SLOTS * E;            // parameters of the workgroup
+  constexpr int G = kSB / SLOTS;          // groups
+  constexpr int PARTS = kSB / O;          // threads per parameter in the first pass
+  constexpr int RUN = G / PARTS;          // groups per such thread (= E)
+  static_assert(PARTS * O == kSB && RUN * PARTS == G, "whole passes");
+  __shared__ float part[G * O];
+  __shared__ float part2[kSB];
+  const int t = threadIdx.x, slot = t % SLOTS, g = t / SLOTS;
+#pragma unroll
+  for (int e = 0; e < E; ++e) part[g * O + slot * E + e] = acc[e];
+  __syncthreads();
+  const int o = t % O, p = t / O;
+  float x = part[p * RUN * O + o];
+#pragma unroll
+  for (int q = 1; q < RUN; ++q) x += part[(p * RUN + q) * O + o];
+  if (PARTS == 1) return x;
+  part2[t] = x;
+  __syncthreads();
+  float y = 0.0f;
+  if (t < O) {
+    y = part2[t];
+#pragma unroll
+    for (int q = 1; q < PARTS; ++q) y += part2[q * O + t];
+  }
+  return y;
+}
+
+// Explicit noise: a slot is a 4-element vector of the row (4-byte aligned;
+// the last one may be short), SLOTS vectors per workgroup.
+template <int SLOTS>
+__global__ __launch_bounds__(kSB) void es_estimate_split(const float* noise, const float* __restrict__ w, int64_t N,
+                                                          int64_t n, float scale, float* grad) {
+  constexpr int kInFlight = 8;  // rows loaded before the first is added
+  const int slot = threadIdx.x % SLOTS, g = threadIdx.x / SLOTS;
+  const int64_t j = 4 * ((int64_t)blockIdx.x * SLOTS + slot);  // first parameter of the slot
+  int64_t lo, hi;
+  group_range(N, kSB / SLOTS, g, lo, hi);
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (j + 4 <= n) {
+    const float* z = noise + j;
+    int64_t i = lo;
+    for (; i + kInFlight <= hi; i += kInFlight) {
+      f32x4 r[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) r[u] = ld(reinterpret_cast<const f32x4u*>(z + (i + u) * n));
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const float wi = w[i + u];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, r[u][e], acc[e]);
+      }
+    }
+    for (; i < hi; ++i) {
+      const float wi = w[i];
+      const f32x4 r = ld(reinterpret_cast<const f32x4u*>(z + i * n));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, r[e], acc[e]);
+    }
+  } else if (j < n) {
+    const int left = (int)(n - j);
+    for (int64_t i = lo; i < hi; ++i) {
+      const float wi = w[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < left) acc[e] = fmaf(wi, noise[i * n + j + e], acc[e]);
+    }
+  }
+  const float sum = group_sum<SLOTS, 4>(acc);
+  const int64_t out = 4 * (int64_t)blockIdx.x * SLOTS + threadIdx.x;
+  if (threadIdx.x < 4 * SLOTS && out < n) grad[out] = scale * sum;
 }
 
 // ---- Gaussian noise generated in registers -----------------------------------
@@ -290,68 +390,7 @@ __device__ __forceinline__ float es_weight(const float* __restrict__ f, const fl
   return f[i] - f[N + i];
 }
 
-#ifndef DIFFOPT_ES_GROWS
-#define DIFFOPT_ES_GROWS 8
-#endif
-constexpr int kGRows = DIFFOPT_ES_GROWS;  // samples per lane in the Gaussian perturb
-
-// Grid: x over Philox blocks (one per lane), y over groups of kGRows samples.
-// A lane reads its eight theta values once and writes its eight parameters
-// of every sample of the group (and of the antithetic rows).  VEC: n % 4 == 0
-// and 16-byte aligned theta and out, so each run of four moves as one
-// 128-bit access.
-template <bool VEC>
-__global__ __launch_bounds__(kEB) void es_perturb_gauss(const float* theta, int64_t N, int64_t n, uint64_t seed,
-                                                         float sigma, int antithetic, float* out) {
-  const int64_t b = (int64_t)blockIdx.x * kEB + threadIdx.x;
-  const int64_t j[2] = {run_start(b, 0), run_start(b, 1)};
-  if (j[0] >= n) return;
-  int cnt[2];
-  float t[8];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int64_t left = n - j[h];
-    cnt[h] = left <= 0 ? 0 : (left < 4 ? (int)left : 4);
-    if (VEC) {
-      const f32x4 a = cnt[h] ? *reinterpret_cast<const f32x4*>(theta + j[h]) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[4 * h + e] = a[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[4 * h + e] = e < cnt[h] ? theta[j[h] + e] : 0.0f;
-    }
-  }
-  const int64_t i0 = (int64_t)blockIdx.y * kGRows;
-  const int64_t i1 = i0 + kGRows < N ? i0 + kGRows : N;
-  for (int64_t i = i0; i < i1; ++i) {
-    float z[8], a[8], m[8];
-    noise8(b, i, seed, z);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      a[e] = fmaf(sigma, z[e], t[e]);
-      m[e] = fmaf(-sigma, z[e], t[e]);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (!cnt[h]) continue;
-      float* row = out + i * n + j[h];
-      float* rowm = out + (N + i) * n + j[h];
-      if (VEC) {
-        st(reinterpret_cast<f32x4*>(row), f32x4{a[4 * h], a[4 * h + 1], a[4 * h + 2], a[4 * h + 3]});
-        if (antithetic) st(reinterpret_cast<f32x4*>(rowm), f32x4{m[4 * h], m[4 * h + 1], m[4 * h + 2], m[4 * h + 3]});
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e < cnt[h]) {
-            row[e] = a[4 * h + e];
-            if (antithetic) rowm[e] = m[4 * h + e];
-          }
-      }
-    }
-  }
-}
-
-// 128-bit path with line-aligned stores.  A workgroup's waves own as many
+// Perturb with line-aligned stores.  A workgroup's waves own as many
 // consecutive segments (8 waves: 4096 parameters, 16 KiB of each output row);
 // a row starts at a 16-byte phase d within its 128-byte lines
 // (d = (address / 16) mod 8, n mod 32 = 8 at the ResNet-18 size).  Stored
@@ -372,37 +411,54 @@ constexpr int kLW = DIFFOPT_ES_LINE_WAVES;  // waves (segments) per workgroup
 // Samples per workgroup.  The grid is one-dimensional with the sample groups
 // of one parameter chunk consecutive, so the dispatcher runs them side by side
 // and they share the chunk's theta through the cache.  Measured (n =
-// 11,689,512, N = 64, six paired rounds): chunk-major order with 8, 4 or 2
-// samples per workgroup 1.138, 1.129, 1.137 ms, against 1.176 ms for the
-// sample groups outermost (8 per workgroup; 16, 32, 64: 1.185, 1.203, 1.257).
+// 11,689,512, N = 64 antithetic): 1, 2, 4, 8 samples per workgroup 1.100,
+// 1.143, 1.143, 1.138 ms alone, equal when the estimate follows (the chip then
+// runs at its power limit, and one sample per workgroup redoes the
+// sample-independent part of the generator); the sample groups outermost 1.176.
+// One row a sample (not antithetic): 0.839, 0.762, 0.718 ms for 1, 2, 4.  With
+// few workgroups each takes one sample (n = 112,261, N = 64 antithetic: 13.9
+// us against 16.9 for four).
 #ifndef DIFFOPT_ES_LINE_ROWS
 #define DIFFOPT_ES_LINE_ROWS 4
 #endif
 constexpr int kLRows = DIFFOPT_ES_LINE_ROWS;
 constexpr int kLB = 64 * kLW;
-constexpr int kRowChunks = kLW * 128;  // 16-byte chunks of one row per workgroup
+constexpr int kRowElems = kLW * 512;  // elements of one row per workgroup
 
+// VEC: n % 4 == 0 and 16-byte aligned theta and out, so every row's phase d is
+// a whole number of 16-byte chunks and LDS is read in aligned chunks.
+// Otherwise rows start at any element of a line: the 16-byte chunks stored are
+// still aligned in memory, each gathered from LDS at the row's element phase,
+// and the chunks that reach past the workgroup's range (its two ends) are
+// stored element by element.
+template <bool VEC>
 __global__ __launch_bounds__(kLB) void es_perturb_gauss_lines(const float* theta, int64_t N, int64_t n,
                                                                uint64_t seed, float sigma, int antithetic,
-                                                               uint32_t groups, float* out) {
-  __shared__ f32x4 rows[2][kRowChunks];  // the plus and minus rows of one sample
+                                                               uint32_t groups, int rows_per_group, float* out) {
+  __shared__ __attribute__((aligned(16))) float rows[2][kRowElems];  // the plus and minus rows of one sample
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t chunk = blockIdx.x / groups, group = blockIdx.x - chunk * groups;
   const int64_t b = (int64_t)chunk * kLB + threadIdx.x;
-  const int64_t first = (int64_t)chunk * (kRowChunks * 4);  // the workgroup's first parameter
-  const int64_t left = (n - first) >> 2;                          // n % 4 == 0 here
-  const int nchunks = left < kRowChunks ? (int)left : kRowChunks;
+  const int64_t first = (int64_t)chunk * kRowElems;  // the workgroup's first parameter
+  const int64_t left = n - first;
+  const int elems = left < kRowElems ? (int)left : kRowElems;
   bool on[2];
   float t[8];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    on[h] = run_start(b, h) < n;
-    const f32x4 a = on[h] ? *reinterpret_cast<const f32x4*>(theta + run_start(b, h)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int64_t j = run_start(b, h);
+    on[h] = j < n;
+    if (VEC || j + 4 <= n) {
+      const f32x4 a = on[h] ? *reinterpret_cast<const f32x4u*>(theta + j) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[4 * h + e] = a[e];
+      for (int e = 0; e < 4; ++e) t[4 * h + e] = a[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[4 * h + e] = j + e < n ? theta[j + e] : 0.0f;
+    }
   }
-  const int64_t i0 = (int64_t)group * kLRows;
-  const int64_t i1 = i0 + kLRows < N ? i0 + kLRows : N;
+  const int64_t i0 = (int64_t)group * rows_per_group;
+  const int64_t i1 = i0 + rows_per_group < N ? i0 + rows_per_group : N;
   const int nrows = antithetic ? 2 : 1;
   for (int64_t i = i0; i < i1; ++i) {
     if (on[0]) {  // a lane past the end computes nothing but still meets both barriers
@@ -416,17 +472,29 @@ __global__ __launch_bounds__(kLB) void es_perturb_gauss_lines(const float* theta
           pa[e] = fmaf(sigma, z[4 * h + e], t[4 * h + e]);
           pm[e] = fmaf(-sigma, z[4 * h + e], t[4 * h + e]);
         }
-        rows[0][128 * wave + 64 * h + lane] = pa;  // chunk of parameter run_start(b, h)
-        if (antithetic) rows[1][128 * wave + 64 * h + lane] = pm;
+        const int at = 512 * wave + 256 * h + 4 * lane;  // element run_start(b, h) of the row
+        *reinterpret_cast<f32x4*>(&rows[0][at]) = pa;
+        if (antithetic) *reinterpret_cast<f32x4*>(&rows[1][at]) = pm;
       }
     }
     __syncthreads();
     for (int r = 0; r < nrows; ++r) {
       float* row = out + (r ? N + i : i) * n + first;
-      const int d = (int)((reinterpret_cast<uintptr_t>(row) >> 4) & 7u);
+      const int d = (int)((reinterpret_cast<uintptr_t>(row) >> 2) & 31u);  // row's phase in its line, in elements
       for (int q = wave; q <= 2 * kLW; q += kLW) {
-        const int c = 64 * q + lane - d;
-        if (c >= 0 && c < nchunks) st(reinterpret_cast<f32x4*>(row) + c, rows[r][c]);
+        const int x = 4 * (64 * q + lane) - d;  // first element of this lane's chunk
+        if (x >= 0 && x + 4 <= elems) {
+          if (VEC) {
+            st(reinterpret_cast<f32x4*>(row + x), *reinterpret_cast<const f32x4*>(&rows[r][x]));
+          } else {
+            const f32x4 y = {rows[r][x], rows[r][x + 1], rows[r][x + 2], rows[r][x + 3]};
+            st(reinterpret_cast<f32x4*>(row + x), y);
+          }
+        } else if (!VEC) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (x + e >= 0 && x + e < elems) row[x + e] = rows[r][x + e];
+        }
       }
     }
     __syncthreads();
@@ -469,6 +537,36 @@ __global__ __launch_bounds__(kEB) void es_estimate_gauss(const float* __restrict
   }
 }
 
+// Few parameters: a slot is a Philox block, SLOTS blocks per workgroup, the
+// samples split over the workgroup (see group_sum).  With 64 slots a wave
+// holds one group, so its sample index stays in scalar registers.
+template <int SLOTS>
+__global__ __launch_bounds__(kSB) void es_estimate_gauss_split(const float* __restrict__ f,
+                                                                const float* __restrict__ f0, int64_t N, int method,
+                                                                int64_t n, uint64_t seed, float scale, float* grad) {
+  const int slot = threadIdx.x % SLOTS;
+  const int g = SLOTS == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / SLOTS) : threadIdx.x / SLOTS;
+  const int64_t b = (int64_t)blockIdx.x * SLOTS + slot;
+  int64_t lo, hi;
+  group_range(N, kSB / SLOTS, g, lo, hi);
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+  if (run_start(b, 0) < n) {
+    for (int64_t i = lo; i < hi; ++i) {
+      const float wi = es_weight(f, f0, N, method, i);
+      float z[8];
+      noise8(b, i, seed, z);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = fmaf(wi, z[e], acc[e]);
+    }
+  }
+  const float sum = group_sum<SLOTS, 8>(acc);
+  const int o = threadIdx.x;
+  const int64_t out = run_start((int64_t)blockIdx.x * SLOTS + o / 8, (o & 7) >> 2) + (o & 3);
+  if (o < 8 * SLOTS && out < n) grad[out] = scale * sum;
+}
+
 // weights_i = scale * (method difference of the evaluations), for the
 // explicit-noise estimate.
 __global__ __launch_bounds__(kEB) void es_weights_kernel(const float* __restrict__ f, const float* __restrict__ f0,
@@ -476,6 +574,34 @@ __global__ __launch_bounds__(kEB) void es_weights_kernel(const float* __restrict
   const int64_t i = (int64_t)blockIdx.x * kEB + threadIdx.x;
   if (i < N) w[i] = scale * es_weight(f, f0, N, method, i);
 }
+
+// Slots per workgroup of a split estimate over `work` slots and N samples, or 0
+// for the kernel that walks all samples in one lane: split while its lanes
+// cannot fill the chip, and only where every group gets a sample.
+// Measured on MI355X, microseconds plain / 64 slots / 16 slots:
+//   explicit noise (slots of 4)  n = 1,761, N = 256: 90 / 8.0 / 4.6;
+//     n = 112,261, N = 64: 19.4 / 5.8 / 9.4; n = 400,001, N = 16: 6.3 / 7.5 / 22,
+//     N = 64: 28.8 / 19.4 / 28, N = 256: 109 / 73 / 88; n = 1,000,003, N = 64:
+//     38.8 / 44.1 / 67
+//   generated noise (slots of 8)  n = 1,761, N = 64: 39 / 8.2 / 4.4;
+//     n = 112,261, N = 64: 40 / 9.1 / 10.0; n = 400,001, N = 16: 12.4 / 10.3 / 25;
+//     n = 2,000,003, N = 16: 29 / 34 / 111, N = 64: 110 / 101 / 120, N = 128:
+//     206 / 188; n = 11,689,512, N = 32: 261 / 284, N = 64: 510 / 505
+// Generated noise costs arithmetic only, so with four samples a group the
+// split's finer workgroups win until they number tens of thousands.
+int noise_split_slots(int64_t work, int64_t N) {
+  if (N < 16 || work >= (N < 32 ? int64_t(1) << 16 : int64_t(1) << 17)) return 0;
+  return work >= (int64_t(1) << 13) || N < 64 ? 64 : 16;
+}
+
+int gauss_split_slots(int64_t work, int64_t N) {
+  if (N < 16 || work >= (N < 64 ? int64_t(1) << 16 : int64_t(1) << 20)) return 0;
+  return work >= (int64_t(1) << 13) || N < 64 ? 64 : 16;
+}
+
+constexpr int kMaxPerturbRows = 65535 * 8;
+// Workgroups of kLRows samples below which each takes one sample instead.
+constexpr int64_t kFewLineGroups = 2048;
 
 bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 bool al4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
@@ -494,13 +620,11 @@ extern "C" int diffopt_es_perturb(const float* params, const float* noise, int64
   if (n == 0 || num_samples == 0) return DIFFOPT_OK;
   if (!params || !noise || !out) return fail(DIFFOPT_EINVAL, "%s: null required pointer", who);
   if (!al4(params) || !al4(noise) || !al4(out)) return fail(DIFFOPT_EINVAL, "%s: pointers must be 4-byte aligned", who);
-  const int64_t groups = (num_samples + kRows - 1) / kRows;
   hipStream_t st = as_stream(stream);
-  const bool vec = (n % 4 == 0) && al16(params) && al16(noise) && al16(out);
-  if (vec) {
-    const int64_t nv = n / 4;
-    PerturbPlan plan{};
-    const int64_t q = nv % 8;
+  PerturbPlan plan{};
+  plan.P = 1;
+  if (n % 4 == 0 && al16(params) && al16(noise) && al16(out)) {  // whole 16-byte vectors: align the lanes to the lines
+    const int64_t q = (n / 4) % 8;
     int64_t g = 8;  // gcd(q, 8)
     if (q != 0) {
       g = q;
@@ -513,26 +637,20 @@ extern "C" int diffopt_es_perturb(const float* params, const float* noise, int64
     const int64_t P = 8 / g;  // rows i and i + P share a phase
     plan.P = (int32_t)(P < num_samples ? P : num_samples);
     const int64_t base = (int64_t)((reinterpret_cast<uintptr_t>(noise) >> 4) & 7u);
-    int64_t gy = 0;
-    for (int r = 0; r < plan.P; ++r) {
-      plan.gstart[r] = gy;
-      plan.shift[r] = (int32_t)((base + (int64_t)r * q) & 7);  // row r's phase, in vectors
-      const int64_t rows = (num_samples - r + plan.P - 1) / plan.P;
-      gy += (rows + kRows - 1) / kRows;
-    }
-    plan.gstart[plan.P] = gy;
-    if (gy > 65535) return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max about %d)", who, 65535 * kRows);
-    const int64_t bx = (nv + 7 + kEB - 1) / kEB;  // lanes shifted by up to 7 vectors
-    if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
-    hipLaunchKernelGGL(es_perturb_vec, dim3((unsigned)bx, (unsigned)gy), dim3(kEB), 0, st, params, noise,
-                       num_samples, nv, (float)sigma, antithetic ? 1 : 0, out, plan);
-  } else {
-    if (groups > 65535) return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max %d)", who, 65535 * kRows);
-    const int64_t bx = (n + kEB - 1) / kEB;
-    if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
-    hipLaunchKernelGGL(es_perturb_scalar, dim3((unsigned)bx, (unsigned)groups), dim3(kEB), 0, st, params, noise,
-                       num_samples, n, (float)sigma, antithetic ? 1 : 0, out);
+    for (int r = 0; r < plan.P; ++r) plan.shift[r] = (int32_t)((base + (int64_t)r * q) & 7);  // row r's phase, in vectors
   }
+  int64_t gy = 0;
+  for (int r = 0; r < plan.P; ++r) {
+    plan.gstart[r] = gy;
+    const int64_t rows = (num_samples - r + plan.P - 1) / plan.P;
+    gy += (rows + kRows - 1) / kRows;
+  }
+  plan.gstart[plan.P] = gy;
+  if (gy > 65535) return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max about %d)", who, 65535 * kRows);
+  const int64_t bx = ((n + 3) / 4 + 7 + kEB - 1) / kEB;  // lanes shifted by up to 7 vectors
+  if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
+  hipLaunchKernelGGL(es_perturb_vec, dim3((unsigned)bx, (unsigned)gy), dim3(kEB), 0, st, params, noise, num_samples,
+                     n, (float)sigma, antithetic ? 1 : 0, out, plan);
   return launch_status(who);
 }
 
@@ -547,19 +665,20 @@ extern "C" int diffopt_es_estimate(const float* noise, const float* weights, int
     return fail(DIFFOPT_EINVAL, "%s: null required pointer", who);
   if (!al4(noise) || !al4(weights) || !al4(grad)) return fail(DIFFOPT_EINVAL, "%s: pointers must be 4-byte aligned", who);
   hipStream_t st = as_stream(stream);
-  const bool vec = (n % 4 == 0) && al16(grad) && (num_samples == 0 || al16(noise));
-  if (vec) {
-    const int64_t nv = n / 4;
-    const int64_t bx = (nv + kEB * kEstU - 1) / (kEB * kEstU);
-    if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
-    hipLaunchKernelGGL(es_estimate_vec, dim3((unsigned)bx), dim3(kEB), 0, st, noise, weights, num_samples, nv,
-                       (float)scale, grad);
-  } else {
-    const int64_t bx = (n + kEB - 1) / kEB;
-    if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
-    hipLaunchKernelGGL(es_estimate_scalar, dim3((unsigned)bx), dim3(kEB), 0, st, noise, weights, num_samples, n,
-                       (float)scale, grad);
-  }
+  const int64_t nvec = (n + 3) / 4;
+  const int slots = noise_split_slots(nvec, num_samples);
+  const int64_t per = slots ? slots : kEB * kEstU;  // vectors per workgroup
+  const int64_t bx = (nvec + per - 1) / per;
+  if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
+  const dim3 grid((unsigned)bx);
+  if (slots == 64)
+    hipLaunchKernelGGL(es_estimate_split<64>, grid, dim3(kSB), 0, st, noise, weights, num_samples, n, (float)scale,
+                       grad);
+  else if (slots == 16)
+    hipLaunchKernelGGL(es_estimate_split<16>, grid, dim3(kSB), 0, st, noise, weights, num_samples, n, (float)scale,
+                       grad);
+  else
+    hipLaunchKernelGGL(es_estimate_vec, grid, dim3(kEB), 0, st, noise, weights, num_samples, n, (float)scale, grad);
   return launch_status(who);
 }
 
@@ -584,21 +703,22 @@ extern "C" int diffopt_es_perturb_gaussian(const float* params, int64_t n, int64
   if (n == 0 || num_samples == 0) return DIFFOPT_OK;
   if (!params || !out) return fail(DIFFOPT_EINVAL, "%s: null required pointer", who);
   if (!al4(params) || !al4(out)) return fail(DIFFOPT_EINVAL, "%s: pointers must be 4-byte aligned", who);
-  const int64_t gy = (num_samples + kGRows - 1) / kGRows;
-  if (gy > 65535) return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max %d)", who, 65535 * kGRows);
+  if (num_samples > kMaxPerturbRows)
+    return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max %d)", who, kMaxPerturbRows);
   const int64_t blocks = 64 * ((n + 511) / 512);  // Philox blocks: 64 per 512 parameters
-  const int64_t bx = (blocks + kEB - 1) / kEB;
-  if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
+  if ((blocks + kEB - 1) / kEB > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
+  const int64_t chunks = (blocks + kLB - 1) / kLB;
+  const int rows = chunks * ((num_samples + kLRows - 1) / kLRows) < kFewLineGroups ? 1 : kLRows;
+  const int64_t groups = (num_samples + rows - 1) / rows;
+  if (chunks * groups > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n x num_samples too large", who);
   hipStream_t st = as_stream(stream);
-  const dim3 grid((unsigned)bx, (unsigned)gy);
-  if (n % 4 == 0 && al16(params) && al16(out)) {
-    const int64_t chunks = (blocks + kLB - 1) / kLB, lgroups = (num_samples + kLRows - 1) / kLRows;
-    if (chunks * lgroups > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n x num_samples too large", who);
-    hipLaunchKernelGGL(es_perturb_gauss_lines, dim3((unsigned)(chunks * lgroups)), dim3(kLB), 0, st, params,
-                       num_samples, n, seed, (float)sigma, antithetic ? 1 : 0, (uint32_t)lgroups, out);
-  } else
-    hipLaunchKernelGGL(es_perturb_gauss<false>, grid, dim3(kEB), 0, st, params, num_samples, n, seed, (float)sigma,
-                       antithetic ? 1 : 0, out);
+  const dim3 grid((unsigned)(chunks * groups));
+  if (n % 4 == 0 && al16(params) && al16(out))
+    hipLaunchKernelGGL(es_perturb_gauss_lines<true>, grid, dim3(kLB), 0, st, params, num_samples, n, seed,
+                       (float)sigma, antithetic ? 1 : 0, (uint32_t)groups, rows, out);
+  else
+    hipLaunchKernelGGL(es_perturb_gauss_lines<false>, grid, dim3(kLB), 0, st, params, num_samples, n, seed,
+                       (float)sigma, antithetic ? 1 : 0, (uint32_t)groups, rows, out);
   return launch_status(who);
 }
 
@@ -620,6 +740,17 @@ extern "C" int diffopt_es_estimate_gaussian(const float* fvals, const float* f0,
   if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
   const float scale = num_samples > 0 ? es_scale(method, num_samples, sigma) : 0.0f;
   hipStream_t st = as_stream(stream);
+  const int slots = gauss_split_slots(blocks, num_samples);
+  if (slots) {
+    const dim3 grid((unsigned)((blocks + slots - 1) / slots));
+    if (slots == 64)
+      hipLaunchKernelGGL(es_estimate_gauss_split<64>, grid, dim3(kSB), 0, st, fvals, f0, num_samples, (int)method, n,
+                         seed, scale, grad);
+    else
+      hipLaunchKernelGGL(es_estimate_gauss_split<16>, grid, dim3(kSB), 0, st, fvals, f0, num_samples, (int)method, n,
+                         seed, scale, grad);
+    return launch_status(who);
+  }
   if (n % 4 == 0 && al16(grad))
     hipLaunchKernelGGL(es_estimate_gauss<true>, dim3((unsigned)bx), dim3(kEB), 0, st, fvals, f0, num_samples,
                        (int)method, n, seed, scale, grad);

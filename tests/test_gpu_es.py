@@ -196,6 +196,62 @@ def test_gaussian_paths_misaligned_and_empty():
         P.es_estimate_gaussian(f, "baseline", N, seed, 0.1, g2)  # f0 missing
 
 
+@pytest.mark.parametrize("n", [1, 3, 63, 65, 257, 32764, 32769, 65533])
+@pytest.mark.parametrize("N", [15, 16, 31, 32, 63, 64, 67, 129])
+def test_es_estimate_split_over_samples(n, N):
+    # few parameters: the samples are cut into 16 or 64 groups (from 16 and 64
+    # samples on; 16 slots of four parameters below 32768 parameters), with
+    # short last slots and groups of unequal length
+    import paper_2211_06934_amd as P
+    Z = normal(N * n, 1.0, "ges", "misc", N).reshape(N, n)
+    w = normal(N, 2.0, "ges", "cot_p", N)
+    g = torch.full((n,), 7.0, device="cuda")
+    P.es_estimate(_dev(Z), _dev(w), 0.25, g)
+    torch.cuda.synchronize()
+    assert_mag_close(g.cpu().numpy(), oracle.es_estimate(Z, w, 0.25), oracle.es_estimate_mag(Z, w, 0.25), BWD_RTOL)
+
+
+@pytest.mark.parametrize("n", [1, 5, 511, 515, 8193, 65536 - 512, 65541])
+@pytest.mark.parametrize("N,method", [(15, "plain"), (16, "antithetic"), (63, "baseline"), (64, "plain"), (70, "antithetic")])
+def test_gaussian_estimate_split_over_samples(n, N, method):
+    import paper_2211_06934_amd as P
+    sigma, seed = 0.05, 77 + n
+    f = normal((2 if method == "antithetic" else 1) * N, 1.0, "ges", "cot_m", N) + 3.0
+    f0 = np.float32(2.5)
+    g = torch.full((n,), 7.0, device="cuda")
+    P.es_estimate_gaussian(_dev(f), method, N, seed, sigma, g, f0=_dev(np.array([f0])))
+    torch.cuda.synchronize()
+    z = oracle.es_gaussian_noise(N, n, seed)
+    w, scale = oracle.es_weights(f, method, sigma, f0=float(f0))
+    mag = oracle.es_estimate_mag(oracle.es_gaussian_noise_radius(N, n, seed),
+                                 oracle.es_weight_terms(f, method, f0=float(f0)), scale)
+    assert_mag_close(g.cpu().numpy(), oracle.es_estimate(z, w, scale), mag, BWD_RTOL, "estimate " + method)
+
+
+@pytest.mark.parametrize("n", [4093, 4094, 4095, 4096, 4097, 4123, 8191, 8193])
+@pytest.mark.parametrize("offset", [0, 1, 4, 31])
+def test_perturb_rows_at_every_phase(n, offset):
+    # rows of any length and alignment hold the same values as a prefix of
+    # longer, line-aligned rows, and nothing outside them is written
+    import paper_2211_06934_amd as P
+    N, m, seed, sigma = 9, 8704, 5, 0.1
+    theta, Z = _dev(normal(m, 0.05, "ges", "p0", 11)), _dev(normal(N * m, 1.0, "ges", "misc", 12)).view(N, m)
+    tn = torch.empty(n + offset, device="cuda")[offset:].copy_(theta[:n])
+    zn = Z[:, :n].contiguous()
+    for antithetic in (False, True):
+        R = (2 if antithetic else 1) * N
+        ref = [torch.empty(R, m, device="cuda") for _ in range(2)]
+        P.es_perturb_gaussian(theta, N, seed, sigma, antithetic, ref[0])
+        P.es_perturb(theta, Z, sigma, antithetic, ref[1])
+        bufs = [torch.full((offset + R * n + 40,), 7.0, device="cuda") for _ in range(2)]
+        P.es_perturb_gaussian(tn, N, seed, sigma, antithetic, bufs[0][offset:offset + R * n])
+        P.es_perturb(tn, zn, sigma, antithetic, bufs[1][offset:offset + R * n])
+        torch.cuda.synchronize()
+        for buf, full in zip(bufs, ref):
+            assert torch.equal(buf[offset:offset + R * n].view(R, n), full[:, :n])
+            assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + R * n:] == 7.0)
+
+
 @pytest.mark.parametrize("method", ["plain", "baseline", "antithetic"])
 def test_es_weights_match_oracle(method):
     import paper_2211_06934_amd as P
