@@ -294,10 +294,10 @@ constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull;
 constexpr uint64_t kPhiloxW1 = 0xBB67AE8584CAA73Bull;
 
 // Full 128-bit product of a 64-bit constant and a 64-bit value from four
-// 32 x 32 -> 64-bit partial products, each with its carry-in folded into the
-// same multiply-add (none of the sums can overflow 64 bits).  Forming the low
-// and high halves separately (a 64-bit multiply and __umul64hi) repeats
-// three of the four partial products.
+// 32 x 32 -> 64-bit multiply-adds, each carry folded into a multiply-add's
+// addend (none of the sums can overflow 64 bits).  Forming the low and high
+// halves separately (a 64-bit multiply and __umul64hi) repeats three of the
+// four partial products.
 template <uint64_t M>
 __device__ __forceinline__ void mul128(uint64_t c, uint64_t& lo, uint64_t& hi) {
   constexpr uint64_t ml = M & 0xffffffffull, mh = M >> 32;
@@ -307,6 +307,39 @@ __device__ __forceinline__ void mul128(uint64_t c, uint64_t& lo, uint64_t& hi) {
   const uint64_t t2 = ch * ml + (t1 & 0xffffffffull);
   hi = ch * mh + (t1 >> 32) + (t2 >> 32);
   lo = (t2 << 32) | (t0 & 0xffffffffull);
+}
+
+// Both products of a round, M0 c0 and M1 c2.  The third multiply-add takes the
+// whole second one as its addend and its carry-out, as a lane mask in scalar
+// registers, becomes the high word of the fourth one's addend: three moves and
+// selects a product instead of five and a half moves and adds (205 instead of
+// 240 VALU instructions per block and sample; the pass at n = 11,689,512, N =
+// 64, perturb then estimate, 1.70 -> 1.62 ms: its generator keeps the chip at
+// its power limit).  The two third
+// multiply-adds and the selects share one asm statement because an SGPR
+// written by a vector instruction may be read by another only two wait states
+// later, which the compiler does not see to across asm statements: each mask
+// is read two instructions after it is written (s_nop 0 is one wait state).
+__device__ __forceinline__ void mul128_round(uint64_t c0, uint64_t c2, uint64_t& lo0, uint64_t& hi0, uint64_t& lo1,
+                                             uint64_t& hi1) {
+  constexpr uint32_t l0 = (uint32_t)kPhiloxM0, h0 = (uint32_t)(kPhiloxM0 >> 32);
+  constexpr uint32_t l1 = (uint32_t)kPhiloxM1, h1 = (uint32_t)(kPhiloxM1 >> 32);
+  const uint32_t c0l = (uint32_t)c0, c0h = (uint32_t)(c0 >> 32), c2l = (uint32_t)c2, c2h = (uint32_t)(c2 >> 32);
+  const uint64_t a0 = (uint64_t)c0l * l0, a1 = (uint64_t)c2l * l1;
+  const uint64_t b0 = (uint64_t)c0l * h0 + (a0 >> 32), b1 = (uint64_t)c2l * h1 + (a1 >> 32);
+  uint64_t t0, t1, m0, m1;  // third sums and their carry masks
+  uint32_t top0, top1;
+  asm("v_mad_u64_u32 %0, %2, %6, %7, %8\n\t"
+      "v_mad_u64_u32 %1, %3, %9, %10, %11\n\t"
+      "s_nop 0\n\t"
+      "v_cndmask_b32 %4, 0, 1, %2\n\t"
+      "v_cndmask_b32 %5, 0, 1, %3"
+      : "=&v"(t0), "=&v"(t1), "=&s"(m0), "=&s"(m1), "=&v"(top0), "=&v"(top1)
+      : "v"(c0h), "s"(l0), "v"(b0), "v"(c2h), "s"(l1), "v"(b1));
+  hi0 = (uint64_t)c0h * h0 + (((uint64_t)top0 << 32) | (t0 >> 32));
+  hi1 = (uint64_t)c2h * h1 + (((uint64_t)top1 << 32) | (t1 >> 32));
+  lo0 = (t0 << 32) | (a0 & 0xffffffffull);
+  lo1 = (t1 << 32) | (a1 & 0xffffffffull);
 }
 
 // a ^ b ^ c on 64-bit words through the three-input bitwise instruction
@@ -331,8 +364,15 @@ __device__ __forceinline__ void philox_block(uint64_t block, uint64_t sample, ui
       k1 += kPhiloxW1;
     }
     uint64_t lo0, hi0, lo1, hi1;
-    mul128<kPhiloxM0>(c0, lo0, hi0);
-    mul128<kPhiloxM1>(c2, lo1, hi1);
+    // The first three rounds' products depend in part on the block alone or
+    // on the sample and seed alone: ordinary code, which the compiler moves out
+    // of the sample loop or to scalar registers.
+    if (r < 3) {
+      mul128<kPhiloxM0>(c0, lo0, hi0);
+      mul128<kPhiloxM1>(c2, lo1, hi1);
+    } else {
+      mul128_round(c0, c2, lo0, hi0, lo1, hi1);
+    }
     // The first two rounds are left to the compiler, which keeps their
     // sample- and seed-only terms in scalar registers.
     const uint64_t n0 = r < 2 ? hi1 ^ c1 ^ k0 : xor3(hi1, c1, k0);
