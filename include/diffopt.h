@@ -29,8 +29,9 @@
  *     nonzero return on the calling thread is diffopt_last_error().  No call
  *     aborts the process or throws across the ABI.
  *   - n == 0 is a valid no-op.
- *   - 16-byte aligned element pointers take the 128-bit vector path; any
- *     other (4-byte aligned) pointer takes a scalar path with the same result.
+ *   - Element pointers need 4-byte alignment; any of them takes 128-bit
+ *     accesses, fastest when the call's arrays share one phase of the
+ *     128-byte lines.  The results do not depend on the alignment.
  */
 #ifndef DIFFOPT_H
 #define DIFFOPT_H
@@ -209,9 +210,7 @@ int diffopt_adam_bwd(const float* dupdate, const float* dmu, const float* dnu,
  * whole trajectory, 24 + 4K with the final state only).  When a 16-step
  * launch boundary falls on an unstored state, the running moments pass to the
  * next launch through mu_traj[K], nu_traj[K].  Every stored state and pK
- * equal K calls of diffopt_adam_fwd bit for bit.  Pointers that are not
- * 16-byte aligned take a one-element-per-lane kernel with the same result.
- * No host synchronisation.                                                  */
+ * equal K calls of diffopt_adam_fwd bit for bit.  No host synchronisation.  */
 int diffopt_adam_unrolled_fwd(int64_t K, int64_t n, const float* p0,
                               const float* const* grads,
                               float* const* mu_traj, float* const* nu_traj,
@@ -246,8 +245,7 @@ int diffopt_adam_unrolled_fwd(int64_t K, int64_t n, const float* p0,
  * once, recomputes the run's states in registers, then runs its VJP steps
  * (20 + 8K bytes per element for K <= DIFFOPT_REMAT_SPAN with nothing
  * stored).  The result equals K calls of diffopt_adam_bwd (the first with
- * zero dM, dV) on the full trajectory bit for bit.  Pointers that are not
- * 16-byte aligned take one-element-per-lane kernels with the same result. */
+ * zero dM, dV) on the full trajectory bit for bit.                          */
 int diffopt_adam_unrolled_bwd(int64_t K, int64_t n, const float* dpK,
                               const float* const* grads,
                               const float* const* mu_traj,

@@ -13,19 +13,15 @@
 
 #include "adam_math.hpp"
 
-// Launch shape, chosen by measurement on MI355X (fp32, n ~ 1.2e8):
-// 1024-thread workgroups, one 16-byte vector per thread per array.  Smaller
-// workgroups with more vectors per thread, and persistent grid-stride grids of
-// 8-32 waves per CU, measured 1-20% slower.
-#ifndef DIFFOPT_FWD_U
-#define DIFFOPT_FWD_U 1  // 16-byte vectors per thread per array, forward
-#endif
-#ifndef DIFFOPT_BWD_U
-#define DIFFOPT_BWD_U 1  // 16-byte vectors per thread per array, backward
-#endif
-#ifndef DIFFOPT_ADAM_BLOCK
-#define DIFFOPT_ADAM_BLOCK 1024  // threads per workgroup of the Adam kernels
-#endif
+// Launch shape of the single-step kernels, chosen by measurement on MI355X:
+// one 4-element vector per thread per array; 1024-thread workgroups for the
+// calls that stream from memory (n = 1.2e8, forward then VJP: 1.27 ms against
+// 1.31 at 512 threads and 1.33 at 256), 512 threads for those small enough to
+// be served by the Infinity Cache (n = 1.2e7: 108.6 us against 110.4 at 1024
+// and 109.2 at 256).  More vectors per thread, and persistent grid-stride
+// grids of 8-32 waves per CU, measured 1-20% slower.
+constexpr int kStreamB = 1024;
+constexpr int kKeepB = 512;
 // Fused K-step kernels, measured in the many-small step (K = 3).  Forward
 // storing only the final state: 1024 threads 0.695 ms, 512 0.710, 256 0.731
 // (with the whole trajectory stored the three were within 1%).  VJP reading
@@ -102,7 +98,6 @@ int make_coef(const char* who, int64_t count, double lr, double b1, double b2, d
 
 namespace {
 
-inline bool aligned16(const void* p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline bool aligned4(const void* p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 
 // Order in which the single-step kernels' workgroups take the tiles.  The
@@ -128,6 +123,9 @@ __device__ __forceinline__ int64_t flat_tile(int64_t b, int64_t ntiles) {
 #endif
 }
 
+__device__ __forceinline__ const f32x4u* cv4(const float* q) { return reinterpret_cast<const f32x4u*>(q); }
+__device__ __forceinline__ f32x4u* v4(float* q) { return reinterpret_cast<f32x4u*>(q); }
+
 // One workgroup per tile; the kernels' grid-stride loop covers the (never
 // reached in practice) case of more tiles than a grid dimension holds.
 int64_t grid_for(int64_t tiles) {
@@ -136,67 +134,40 @@ int64_t grid_for(int64_t tiles) {
 }
 
 // ---- kernels -----------------------------------------------------------------
-// Vector kernels: tile t covers 16-byte vectors [t*B*U, (t+1)*B*U) for B
-// threads per workgroup; lane j of the workgroup takes vectors j, j+B, ... so
-// each load instruction of a wave is one contiguous 1 KiB.  Workgroups walk
-// tiles with a grid stride (one tile each when the grid covers them all).
-// Full tiles skip the per-vector bounds checks.  The last workgroup also
-// finishes the n % 4 tail element by element.
+// Vector kernels: tile t covers vectors [t*B, (t+1)*B) for B threads per
+// workgroup, so each load instruction of a wave is one contiguous 1 KiB.
+// Workgroups walk tiles with a grid stride (one tile each when the grid covers
+// them all).  Full tiles skip the bounds check.  The last workgroup also moves
+// the head and the n % 4 tail element by element (see line_head).
 
-constexpr int kAB = DIFFOPT_ADAM_BLOCK;
-
-template <int U, bool WU, bool GUARD>
-__device__ __forceinline__ void fwd_tile(int64_t t, int64_t nv, const float* p, const float* g, const float* m,
-                                         const float* v, float* po, float* mo, float* vo, float* uo,
-                                         const AdamCoef& c) {
-  const int64_t base = t * (kAB * U) + threadIdx.x;
-  f32x4 P[U], G[U], M[U], V[U];
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    const int64_t i = base + (int64_t)k * kAB;
-    if (!GUARD || i < nv) {
-      P[k] = ld(reinterpret_cast<const f32x4*>(p) + i);
-      G[k] = ld(reinterpret_cast<const f32x4*>(g) + i);
-      M[k] = ld(reinterpret_cast<const f32x4*>(m) + i);
-      V[k] = ld(reinterpret_cast<const f32x4*>(v) + i);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    const int64_t i = base + (int64_t)k * kAB;
-    if (!GUARD || i < nv) {
-      f32x4 rp, rm, rv, ru;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const FwdOut o = fwd_elem(P[k][e], G[k][e], M[k][e], V[k][e], c);
-        rp[e] = o.p;
-        rm[e] = o.m;
-        rv[e] = o.v;
-        ru[e] = o.u;
-      }
-      st(reinterpret_cast<f32x4*>(po) + i, rp);
-      st(reinterpret_cast<f32x4*>(mo) + i, rm);
-      st(reinterpret_cast<f32x4*>(vo) + i, rv);
-      if (WU) st(reinterpret_cast<f32x4*>(uo) + i, ru);
-    }
-  }
-}
-
-template <int U, bool WU>
-__global__ __launch_bounds__(kAB) void adam_fwd_vec(const float* p, const float* g, const float* m,
-                                                    const float* v, float* po, float* mo, float* vo, float* uo,
-                                                    int64_t n, AdamCoef c) {
+template <bool WU, int B, bool KEEP>
+__global__ __launch_bounds__(B) void adam_fwd_vec(const float* p, const float* g, const float* m, const float* v,
+                                                  float* po, float* mo, float* vo, float* uo, int64_t n,
+                                                  int64_t head, AdamCoef c) {
   const int64_t nv = n >> 2;
-  const int64_t nfull = nv / (kAB * U);
-  const int64_t ntiles = (nv + kAB * U - 1) / (kAB * U);
+  const int64_t ntiles = (nv + B - 1) / B;
   for (int64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
-    const int64_t t = flat_tile(b, ntiles);
-    if (t < nfull) fwd_tile<U, WU, false>(t, nv, p, g, m, v, po, mo, vo, uo, c);
-    else fwd_tile<U, WU, true>(t, nv, p, g, m, v, po, mo, vo, uo, c);
+    const int64_t i = flat_tile(b, ntiles) * B + threadIdx.x;
+    if (i >= nv) continue;
+    const f32x4 P = ld<KEEP>(cv4(p) + i), G = ld<KEEP>(cv4(g) + i), M = ld<KEEP>(cv4(m) + i),
+                V = ld<KEEP>(cv4(v) + i);
+    f32x4u rp, rm, rv, ru;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const FwdOut o = fwd_elem(P[e], G[e], M[e], V[e], c);
+      rp[e] = o.p;
+      rm[e] = o.m;
+      rv[e] = o.v;
+      ru[e] = o.u;
+    }
+    st(v4(po) + i, rp);
+    st(v4(mo) + i, rm);
+    st(v4(vo) + i, rv);
+    if (WU) st(v4(uo) + i, ru);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < n) {
+    int64_t e;
+    if (edge_element(n, head, e)) {
       const FwdOut o = fwd_elem(p[e], g[e], m[e], v[e], c);
       po[e] = o.p;
       mo[e] = o.m;
@@ -206,99 +177,38 @@ __global__ __launch_bounds__(kAB) void adam_fwd_vec(const float* p, const float*
   }
 }
 
-// Scalar kernel for pointers that are not 16-byte aligned.
-template <bool WU>
-__global__ __launch_bounds__(kAB) void adam_fwd_scalar(const float* p, const float* g, const float* m,
-                                                       const float* v, float* po, float* mo, float* vo, float* uo,
-                                                       int64_t n, AdamCoef c) {
-  const int64_t base = (int64_t)blockIdx.x * (kAB * 4) + threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t e = base + (int64_t)k * kAB;
-    if (e < n) {
-      const FwdOut o = fwd_elem(p[e], g[e], m[e], v[e], c);
-      po[e] = o.p;
-      mo[e] = o.m;
-      vo[e] = o.v;
-      if (WU) uo[e] = o.u;
-    }
-  }
-}
-
-template <int U, bool HAS_MV, bool WDP, bool GUARD>
-__device__ __forceinline__ void bwd_tile(int64_t t, int64_t nv, const float* dP, const float* dM,
-                                         const float* dV, const float* g, const float* m, const float* v,
-                                         float* dpo, float* dgo, float* dmo, float* dvo, const AdamCoef& c) {
-  const int64_t base = t * (kAB * U) + threadIdx.x;
-  f32x4 P[U], Mb[U], Vb[U], G[U], M[U], V[U];
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    const int64_t i = base + (int64_t)k * kAB;
-    if (!GUARD || i < nv) {
-      P[k] = ld(reinterpret_cast<const f32x4*>(dP) + i);
-      if (HAS_MV) {
-        Mb[k] = ld(reinterpret_cast<const f32x4*>(dM) + i);
-        Vb[k] = ld(reinterpret_cast<const f32x4*>(dV) + i);
-      }
-      G[k] = ld(reinterpret_cast<const f32x4*>(g) + i);
-      M[k] = ld(reinterpret_cast<const f32x4*>(m) + i);
-      V[k] = ld(reinterpret_cast<const f32x4*>(v) + i);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < U; ++k) {
-    const int64_t i = base + (int64_t)k * kAB;
-    if (!GUARD || i < nv) {
-      f32x4 rg, rm, rv;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const BwdOut o = bwd_elem<HAS_MV>(P[k][e], HAS_MV ? Mb[k][e] : 0.0f, HAS_MV ? Vb[k][e] : 0.0f, G[k][e],
-                                          M[k][e], V[k][e], c);
-        rg[e] = o.g;
-        rm[e] = o.m;
-        rv[e] = o.v;
-      }
-      st(reinterpret_cast<f32x4*>(dgo) + i, rg);
-      st(reinterpret_cast<f32x4*>(dmo) + i, rm);
-      st(reinterpret_cast<f32x4*>(dvo) + i, rv);
-      if (WDP) st(reinterpret_cast<f32x4*>(dpo) + i, P[k]);
-    }
-  }
-}
-
-template <int U, bool HAS_MV, bool WDP>
-__global__ __launch_bounds__(kAB) void adam_bwd_vec(const float* dP, const float* dM, const float* dV,
-                                                    const float* g, const float* m, const float* v, float* dpo,
-                                                    float* dgo, float* dmo, float* dvo, int64_t n, AdamCoef c) {
+template <bool HAS_MV, bool WDP, int B, bool KEEP>
+__global__ __launch_bounds__(B) void adam_bwd_vec(const float* dP, const float* dM, const float* dV, const float* g,
+                                                  const float* m, const float* v, float* dpo, float* dgo, float* dmo,
+                                                  float* dvo, int64_t n, int64_t head, AdamCoef c) {
   const int64_t nv = n >> 2;
-  const int64_t nfull = nv / (kAB * U);
-  const int64_t ntiles = (nv + kAB * U - 1) / (kAB * U);
+  const int64_t ntiles = (nv + B - 1) / B;
   for (int64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
-    const int64_t t = flat_tile(b, ntiles);
-    if (t < nfull) bwd_tile<U, HAS_MV, WDP, false>(t, nv, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, c);
-    else bwd_tile<U, HAS_MV, WDP, true>(t, nv, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, c);
+    const int64_t i = flat_tile(b, ntiles) * B + threadIdx.x;
+    if (i >= nv) continue;
+    const f32x4 P = ld<KEEP>(cv4(dP) + i);
+    f32x4 Mb = {0.0f, 0.0f, 0.0f, 0.0f}, Vb = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (HAS_MV) {
+      Mb = ld<KEEP>(cv4(dM) + i);
+      Vb = ld<KEEP>(cv4(dV) + i);
+    }
+    const f32x4 G = ld<KEEP>(cv4(g) + i), M = ld<KEEP>(cv4(m) + i), V = ld<KEEP>(cv4(v) + i);
+    f32x4u rg, rm, rv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const BwdOut o = bwd_elem<HAS_MV>(P[e], Mb[e], Vb[e], G[e], M[e], V[e], c);
+      rg[e] = o.g;
+      rm[e] = o.m;
+      rv[e] = o.v;
+    }
+    st(v4(dgo) + i, rg);
+    st(v4(dmo) + i, rm);
+    st(v4(dvo) + i, rv);
+    if (WDP) st(v4(dpo) + i, (f32x4u)P);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < n) {
-      const BwdOut o = bwd_elem<HAS_MV>(dP[e], HAS_MV ? dM[e] : 0.0f, HAS_MV ? dV[e] : 0.0f, g[e], m[e], v[e], c);
-      dgo[e] = o.g;
-      dmo[e] = o.m;
-      dvo[e] = o.v;
-      if (WDP) dpo[e] = dP[e];
-    }
-  }
-}
-
-template <bool HAS_MV, bool WDP>
-__global__ __launch_bounds__(kAB) void adam_bwd_scalar(const float* dP, const float* dM, const float* dV,
-                                                       const float* g, const float* m, const float* v, float* dpo,
-                                                       float* dgo, float* dmo, float* dvo, int64_t n, AdamCoef c) {
-  const int64_t base = (int64_t)blockIdx.x * (kAB * 4) + threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t e = base + (int64_t)k * kAB;
-    if (e < n) {
+    int64_t e;
+    if (edge_element(n, head, e)) {
       const BwdOut o = bwd_elem<HAS_MV>(dP[e], HAS_MV ? dM[e] : 0.0f, HAS_MV ? dV[e] : 0.0f, g[e], m[e], v[e], c);
       dgo[e] = o.g;
       dmo[e] = o.m;
@@ -337,6 +247,7 @@ struct UFwdArgs {
   float* v[kUK];
   AdamCoef c[kUK];
   int64_t n;
+  int64_t head;  // elements before the pointers (see line_head)
   int32_t K;  // steps in this launch, 1..kUK
 };
 
@@ -352,12 +263,10 @@ struct UBwdArgs {
   float* dg[kUK];
   AdamCoef c[kUK];
   int64_t n;
+  int64_t head;
   int32_t K;
   int32_t init_mv;  // 0: dM = dV = 0 before the first step (the last unrolled step)
 };
-
-__device__ __forceinline__ const f32x4* cv4(const float* q) { return reinterpret_cast<const f32x4*>(q); }
-__device__ __forceinline__ f32x4* v4(float* q) { return reinterpret_cast<f32x4*>(q); }
 
 __device__ __forceinline__ void ufwd_vector(int64_t i, const UFwdArgs& a) {
   f32x4 P = ld(cv4(a.p) + i), M = ld(cv4(a.m0) + i), V = ld(cv4(a.v0) + i);
@@ -373,12 +282,12 @@ __device__ __forceinline__ void ufwd_vector(int64_t i, const UFwdArgs& a) {
       V[e] = o.v;
     }
     if (a.m[s]) {  // uniform: the same for every lane
-      st(v4(a.m[s]) + i, M);
-      st(v4(a.v[s]) + i, V);
+      st(v4(a.m[s]) + i, (f32x4u)M);
+      st(v4(a.v[s]) + i, (f32x4u)V);
     }
     G = Gn;
   }
-  st(v4(a.pK) + i, P);
+  st(v4(a.pK) + i, (f32x4u)P);
 }
 
 __device__ __forceinline__ void ufwd_element(int64_t e, const UFwdArgs& a) {
@@ -408,21 +317,15 @@ __global__ __launch_bounds__(B) void adam_unrolled_fwd_vec(UFwdArgs a) {
     if (i < nv) ufwd_vector(i, a);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < a.n) ufwd_element(e, a);
+    int64_t e;
+    if (edge_element(a.n, a.head, e)) ufwd_element(e, a);
   }
-}
-
-// Any alignment: one element per thread (pointers only 4-byte aligned).
-__global__ __launch_bounds__(kUFB) void adam_unrolled_fwd_elem(UFwdArgs a) {
-  for (int64_t e = (int64_t)blockIdx.x * kUFB + threadIdx.x; e < a.n; e += (int64_t)gridDim.x * kUFB)
-    ufwd_element(e, a);
 }
 
 template <bool HAS_MV>
 __device__ __forceinline__ void ubwd_step(const f32x4& dP, f32x4& dM, f32x4& dV, const f32x4& g, const f32x4& m,
-                                          const f32x4& v, const AdamCoef& c, f32x4* dgo) {
-  f32x4 rg;
+                                          const f32x4& v, const AdamCoef& c, f32x4u* dgo) {
+  f32x4u rg;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const BwdOut o = bwd_elem<HAS_MV>(dP[e], dM[e], dV[e], g[e], m[e], v[e], c);
@@ -466,8 +369,8 @@ __device__ __forceinline__ void ubwd_vector(int64_t i, const UBwdArgs& a) {
     M = Mn;
     V = Vn;
   }
-  st(v4(a.dm) + i, dM);
-  st(v4(a.dv) + i, dV);
+  st(v4(a.dm) + i, (f32x4u)dM);
+  st(v4(a.dv) + i, (f32x4u)dV);
 }
 
 __device__ __forceinline__ void ubwd_element(int64_t e, const UBwdArgs& a) {
@@ -503,14 +406,9 @@ __global__ __launch_bounds__(B) void adam_unrolled_bwd_vec(UBwdArgs a) {
     if (i < nv) ubwd_vector(i, a);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < a.n) ubwd_element(e, a);
+    int64_t e;
+    if (edge_element(a.n, a.head, e)) ubwd_element(e, a);
   }
-}
-
-__global__ __launch_bounds__(kUBB) void adam_unrolled_bwd_elem(UBwdArgs a) {
-  for (int64_t e = (int64_t)blockIdx.x * kUBB + threadIdx.x; e < a.n; e += (int64_t)gridDim.x * kUBB)
-    ubwd_element(e, a);
 }
 
 // ---- small buffers ---------------------------------------------------------------
@@ -646,6 +544,7 @@ struct URBwdArgs {
   float* dg[kRS];
   AdamCoef c[kRS];
   int64_t n;
+  int64_t head;
   int32_t init_mv;  // 0: the run holds the last unrolled step (zero dM, dV before it)
 };
 
@@ -688,8 +587,8 @@ __device__ __forceinline__ void urbwd_vector(int64_t i, const URBwdArgs& a) {
 #pragma unroll
   for (int s = C - 2; s >= 0; --s) ubwd_step<true>(dP, dM, dV, G[s], M[s], V[s], a.c[s], v4(a.dg[s]) + i);
 #endif
-  st(v4(a.dm) + i, dM);
-  st(v4(a.dv) + i, dV);
+  st(v4(a.dm) + i, (f32x4u)dM);
+  st(v4(a.dv) + i, (f32x4u)dV);
 }
 
 template <int C>
@@ -765,48 +664,39 @@ __global__ __launch_bounds__(B) void adam_unrolled_bwd_remat_vec(URBwdArgs a) {
     if (i < nv) urbwd_vector<C>(i, a);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < a.n) urbwd_element<C>(e, a);
+    int64_t e;
+    if (edge_element(a.n, a.head, e)) urbwd_element<C>(e, a);
   }
-}
-
-template <int C, int B>
-__global__ __launch_bounds__(B) void adam_unrolled_bwd_remat_elem(URBwdArgs a) {
-  for (int64_t e = (int64_t)blockIdx.x * B + threadIdx.x; e < a.n; e += (int64_t)gridDim.x * B)
-    urbwd_element<C>(e, a);
 }
 
 // Long runs hold more registers per lane, so fewer waves fit on a SIMD; they
 // take smaller workgroups so that whole workgroups still fill the CU.
 template <int C>
-void launch_urbwd(bool vec, const URBwdArgs& a, hipStream_t st) {
+void launch_urbwd(const URBwdArgs& a, hipStream_t st) {
   constexpr int B = C >= DIFFOPT_URBWD_LONG_RUN ? DIFFOPT_URBWD_BLOCK_LONG : kURB;
   constexpr int BS = B < kSmallB ? B : kSmallB;
-  if (a.n <= kSmallElems)
+  if (a.n + a.head <= kSmallElems)
     hipLaunchKernelGGL((adam_unrolled_bwd_remat_small<C>), dim3((unsigned)((a.n + kSEB - 1) / kSEB)), dim3(kSEB), 0,
                        st, a);
-  else if (vec && (a.n >> 2) < kSmallVecs)
+  else if ((a.n >> 2) < kSmallVecs)
     hipLaunchKernelGGL((adam_unrolled_bwd_remat_vec<C, BS>), dim3((unsigned)grid_for(((a.n >> 2) + BS - 1) / BS)),
                        dim3(BS), 0, st, a);
-  else if (vec)
+  else
     hipLaunchKernelGGL((adam_unrolled_bwd_remat_vec<C, B>), dim3((unsigned)grid_for(((a.n >> 2) + B - 1) / B)),
                        dim3(B), 0, st, a);
-  else
-    hipLaunchKernelGGL((adam_unrolled_bwd_remat_elem<C, B>), dim3((unsigned)grid_for((a.n + B - 1) / B)), dim3(B),
-                       0, st, a);
 }
 
 // Run length C is a template argument so the trajectory stays in registers.
-int launch_urbwd_c(const char* who, int C, bool vec, const URBwdArgs& a, hipStream_t st) {
+int launch_urbwd_c(const char* who, int C, const URBwdArgs& a, hipStream_t st) {
   switch (C) {
-    case 1: launch_urbwd<1>(vec, a, st); break;
-    case 2: launch_urbwd<2>(vec, a, st); break;
-    case 3: launch_urbwd<3>(vec, a, st); break;
-    case 4: launch_urbwd<4>(vec, a, st); break;
-    case 5: launch_urbwd<5>(vec, a, st); break;
-    case 6: launch_urbwd<6>(vec, a, st); break;
-    case 7: launch_urbwd<7>(vec, a, st); break;
-    case 8: launch_urbwd<8>(vec, a, st); break;
+    case 1: launch_urbwd<1>(a, st); break;
+    case 2: launch_urbwd<2>(a, st); break;
+    case 3: launch_urbwd<3>(a, st); break;
+    case 4: launch_urbwd<4>(a, st); break;
+    case 5: launch_urbwd<5>(a, st); break;
+    case 6: launch_urbwd<6>(a, st); break;
+    case 7: launch_urbwd<7>(a, st); break;
+    case 8: launch_urbwd<8>(a, st); break;
     default: return fail(DIFFOPT_EINVAL, "%s: recompute run of %d steps (at most %d)", who, C, kRS);
   }
   return DIFFOPT_OK;
@@ -818,43 +708,33 @@ static_assert(kRS == 8, "launch_urbwd_c instantiates run lengths 1..8");
 int launch_fwd(const float* p, const float* g, const float* m, const float* v, int64_t n, const AdamCoef& c,
                float* po, float* mo, float* vo, float* uo, hipStream_t st) {
   if (n == 0) return DIFFOPT_OK;
-  const bool vec = aligned16(p) && aligned16(g) && aligned16(m) && aligned16(v) && aligned16(po) &&
-                   aligned16(mo) && aligned16(vo) && aligned16(uo);
-  if (vec) {
-    constexpr int U = DIFFOPT_FWD_U;
-    const int64_t blocks = grid_for(((n >> 2) + kAB * U - 1) / (kAB * U));
-    if (uo)
-      hipLaunchKernelGGL((adam_fwd_vec<U, true>), dim3((unsigned)blocks), dim3(kAB), 0, st, p, g, m, v, po, mo, vo,
-                         uo, n, c);
-    else
-      hipLaunchKernelGGL((adam_fwd_vec<U, false>), dim3((unsigned)blocks), dim3(kAB), 0, st, p, g, m, v, po, mo,
-                         vo, uo, n, c);
-  } else {
-    const int64_t blocks = (n + kAB * 4 - 1) / (kAB * 4);
-    if (uo)
-      hipLaunchKernelGGL((adam_fwd_scalar<true>), dim3((unsigned)blocks), dim3(kAB), 0, st, p, g, m, v, po, mo, vo,
-                         uo, n, c);
-    else
-      hipLaunchKernelGGL((adam_fwd_scalar<false>), dim3((unsigned)blocks), dim3(kAB), 0, st, p, g, m, v, po, mo,
-                         vo, uo, n, c);
-  }
+  const int64_t h = line_head(po, n);
+  p += h, g += h, m += h, v += h, po += h, mo += h, vo += h, n -= h;
+  if (uo) uo += h;
+  const auto go = [&](auto kernel, int block) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid_for(((n >> 2) + block - 1) / block)), dim3(block), 0, st, p, g, m,
+                       v, po, mo, vo, uo, n, h, c);
+  };
+  if (keep_in_cache((uo ? 32 : 28) * n))
+    uo ? go(adam_fwd_vec<true, kKeepB, true>, kKeepB) : go(adam_fwd_vec<false, kKeepB, true>, kKeepB);
+  else
+    uo ? go(adam_fwd_vec<true, kStreamB, false>, kStreamB) : go(adam_fwd_vec<false, kStreamB, false>, kStreamB);
   return launch_status("diffopt_adam_fwd");
 }
 
 template <bool HAS_MV, bool WDP>
-void launch_bwd_t(bool vec, const float* dP, const float* dM, const float* dV, const float* g, const float* m,
-                  const float* v, float* dpo, float* dgo, float* dmo, float* dvo, int64_t n, const AdamCoef& c,
-                  hipStream_t st) {
-  if (vec) {
-    constexpr int U = DIFFOPT_BWD_U;
-    const int64_t blocks = grid_for(((n >> 2) + kAB * U - 1) / (kAB * U));
-    hipLaunchKernelGGL((adam_bwd_vec<U, HAS_MV, WDP>), dim3((unsigned)blocks), dim3(kAB), 0, st, dP, dM, dV, g, m,
-                       v, dpo, dgo, dmo, dvo, n, c);
-  } else {
-    const int64_t blocks = (n + kAB * 4 - 1) / (kAB * 4);
-    hipLaunchKernelGGL((adam_bwd_scalar<HAS_MV, WDP>), dim3((unsigned)blocks), dim3(kAB), 0, st, dP, dM, dV, g, m,
-                       v, dpo, dgo, dmo, dvo, n, c);
-  }
+void launch_bwd_t(const float* dP, const float* dM, const float* dV, const float* g, const float* m, const float* v,
+                  float* dpo, float* dgo, float* dmo, float* dvo, int64_t n, const AdamCoef& c, hipStream_t st) {
+  const int64_t h = line_head(dgo, n);
+  dP += h, g += h, m += h, v += h, dgo += h, dmo += h, dvo += h, n -= h;
+  if (HAS_MV) dM += h, dV += h;
+  if (WDP) dpo += h;
+  const auto go = [&](auto kernel, int block) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid_for(((n >> 2) + block - 1) / block)), dim3(block), 0, st, dP, dM,
+                       dV, g, m, v, dpo, dgo, dmo, dvo, n, h, c);
+  };
+  if (keep_in_cache((28 + (HAS_MV ? 8 : 0) + (WDP ? 4 : 0)) * n)) go(adam_bwd_vec<HAS_MV, WDP, kKeepB, true>, kKeepB);
+  else go(adam_bwd_vec<HAS_MV, WDP, kStreamB, false>, kStreamB);
 }
 
 int launch_bwd(const float* dP, const float* dM, const float* dV, const float* g, const float* m, const float* v,
@@ -862,15 +742,12 @@ int launch_bwd(const float* dP, const float* dM, const float* dV, const float* g
   if (n == 0) return DIFFOPT_OK;
   const bool has_mv = dM != nullptr;  // the entry point makes dM, dV both null or both set
   const bool wdp = dpo != nullptr && dpo != dP;
-  const bool vec = aligned16(dP) && aligned16(dM) && aligned16(dV) && aligned16(g) && aligned16(m) &&
-                   aligned16(v) && aligned16(wdp ? dpo : nullptr) && aligned16(dgo) && aligned16(dmo) &&
-                   aligned16(dvo);
   if (has_mv) {
-    if (wdp) launch_bwd_t<true, true>(vec, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
-    else launch_bwd_t<true, false>(vec, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
+    if (wdp) launch_bwd_t<true, true>(dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
+    else launch_bwd_t<true, false>(dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
   } else {
-    if (wdp) launch_bwd_t<false, true>(vec, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
-    else launch_bwd_t<false, false>(vec, dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
+    if (wdp) launch_bwd_t<false, true>(dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
+    else launch_bwd_t<false, false>(dP, dM, dV, g, m, v, dpo, dgo, dmo, dvo, n, c, st);
   }
   return launch_status("diffopt_adam_bwd");
 }
@@ -938,46 +815,43 @@ extern "C" int diffopt_adam_unrolled_fwd(int64_t K, int64_t n, const float* p0, 
   int rc = check_trajectory(who, K, mu_traj, nu_traj, true, false);
   if (rc) return rc;
   hipStream_t st = as_stream(stream);
-  bool vec = aligned16(p0) && aligned16(pK);
-  for (int64_t k = 0; k <= K; ++k) {
-    vec = vec && aligned16(mu_traj[k]) && aligned16(nu_traj[k]);
-    if (k < K) vec = vec && aligned16(grads[k]);
-  }
+  // The vector kernels start at a line boundary of pK (the small ones take
+  // every element the same way).
+  const int64_t h = n <= kSmallElems ? 0 : line_head(pK, n);
   for (int64_t k0 = 0; k0 < K; k0 += kUK) {  // one fused launch per kUK steps
     UFwdArgs a;
     a.K = (int32_t)(K - k0 < kUK ? K - k0 : kUK);
-    a.n = n;
+    a.n = n - h;
+    a.head = h;
     // Between launches the running params pass through pK.  The running
     // moments pass through the state stored at the boundary, or, when that
     // entry is NULL, through the final-state buffers mu_traj[K], nu_traj[K]
     // (each lane reads its elements there before writing them).
-    a.p = (k0 == 0) ? p0 : pK;
-    a.m0 = mu_traj[k0] ? mu_traj[k0] : mu_traj[K];
-    a.v0 = nu_traj[k0] ? nu_traj[k0] : nu_traj[K];
-    a.pK = pK;
+    a.p = ((k0 == 0) ? p0 : pK) + h;
+    a.m0 = (mu_traj[k0] ? mu_traj[k0] : mu_traj[K]) + h;
+    a.v0 = (nu_traj[k0] ? nu_traj[k0] : nu_traj[K]) + h;
+    a.pK = pK + h;
     for (int s = 0; s < kUK; ++s) {
       const bool on = s < a.K;
-      a.g[s] = on ? grads[k0 + s] : nullptr;
-      a.m[s] = on ? mu_traj[k0 + s + 1] : nullptr;
-      a.v[s] = on ? nu_traj[k0 + s + 1] : nullptr;
+      const bool kept = on && mu_traj[k0 + s + 1];
+      a.g[s] = on ? grads[k0 + s] + h : nullptr;
+      a.m[s] = kept ? mu_traj[k0 + s + 1] + h : nullptr;
+      a.v[s] = kept ? nu_traj[k0 + s + 1] + h : nullptr;
       if (on) make_coef(who, count0 + k0 + s, lr, b1, b2, eps, eps_root, &a.c[s]);
       else a.c[s] = AdamCoef{};
     }
     if (!a.m[a.K - 1]) {  // boundary state not stored: carry it in the final-state buffers
-      a.m[a.K - 1] = mu_traj[K];
-      a.v[a.K - 1] = nu_traj[K];
+      a.m[a.K - 1] = mu_traj[K] + h;
+      a.v[a.K - 1] = nu_traj[K] + h;
     }
     if (n <= kSmallElems)
       dispatch_k<UFwdArgs, FwdSmall>(a.K, a, st);
-    else if (vec && (n >> 2) < kSmallVecs)
-      hipLaunchKernelGGL((adam_unrolled_fwd_vec<kSmallB>), dim3((unsigned)grid_for(((n >> 2) + kSmallB - 1) / kSmallB)),
-                         dim3(kSmallB), 0, st, a);
-    else if (vec)
-      hipLaunchKernelGGL((adam_unrolled_fwd_vec<kUFB>), dim3((unsigned)grid_for(((n >> 2) + kUFB - 1) / kUFB)),
+    else if ((a.n >> 2) < kSmallVecs)
+      hipLaunchKernelGGL((adam_unrolled_fwd_vec<kSmallB>),
+                         dim3((unsigned)grid_for(((a.n >> 2) + kSmallB - 1) / kSmallB)), dim3(kSmallB), 0, st, a);
+    else
+      hipLaunchKernelGGL((adam_unrolled_fwd_vec<kUFB>), dim3((unsigned)grid_for(((a.n >> 2) + kUFB - 1) / kUFB)),
                          dim3(kUFB), 0, st, a);
-    else  // some pointer is not 16-byte aligned: one element per lane, same arithmetic
-      hipLaunchKernelGGL(adam_unrolled_fwd_elem, dim3((unsigned)grid_for((n + kUFB - 1) / kUFB)), dim3(kUFB), 0, st,
-                         a);
     rc = launch_status(who);
     if (rc) return rc;
   }
@@ -1007,9 +881,7 @@ extern "C" int diffopt_adam_unrolled_bwd(int64_t K, int64_t n, const float* dpK,
   int rc = check_trajectory(who, K, mu_traj, nu_traj, false, true);
   if (rc) return rc;
   hipStream_t st = as_stream(stream);
-  bool vec = aligned16(dpK) && aligned16(dmu0) && aligned16(dnu0);
-  for (int64_t k = 0; k < K; ++k)
-    vec = vec && aligned16(grads[k]) && aligned16(mu_traj[k]) && aligned16(nu_traj[k]) && aligned16(dgrads[k]);
+  const int64_t h = n <= kSmallElems ? 0 : line_head(dmu0, n);  // as in the forward
   // Last steps first.  Steps whose input state was stored run up to kUK per
   // launch, reading it back; a run of steps j+1..khi whose states were not
   // stored (only mu_j, nu_j) runs in one launch that recomputes them.
@@ -1020,53 +892,52 @@ extern "C" int diffopt_adam_unrolled_bwd(int64_t K, int64_t n, const float* dpK,
       int32_t run = 0;
       while (run < kUK && khi - run >= 1 && mu_traj[khi - run - 1]) ++run;
       a.K = run;
-      a.n = n;
-      a.dP = dpK;
-      a.dm = dmu0;
-      a.dv = dnu0;
+      a.n = n - h;
+      a.head = h;
+      a.dP = dpK + h;
+      a.dm = dmu0 + h;
+      a.dv = dnu0 + h;
       a.init_mv = init_mv;
       for (int s = 0; s < kUK; ++s) {
         const bool on = s < a.K;
         const int64_t k = khi - s;  // unrolled step (1-based) run as the launch's step s
-        a.g[s] = on ? grads[k - 1] : nullptr;
-        a.m[s] = on ? mu_traj[k - 1] : nullptr;
-        a.v[s] = on ? nu_traj[k - 1] : nullptr;
-        a.dg[s] = on ? dgrads[k - 1] : nullptr;
+        a.g[s] = on ? grads[k - 1] + h : nullptr;
+        a.m[s] = on ? mu_traj[k - 1] + h : nullptr;
+        a.v[s] = on ? nu_traj[k - 1] + h : nullptr;
+        a.dg[s] = on ? dgrads[k - 1] + h : nullptr;
         if (on) make_coef(who, count0 + k - 1, lr, b1, b2, eps, eps_root, &a.c[s]);
         else a.c[s] = AdamCoef{};
       }
       if (n <= kSmallElems)
         dispatch_k<UBwdArgs, BwdSmall>(a.K, a, st);
-      else if (vec && (n >> 2) < kSmallVecs)
+      else if ((a.n >> 2) < kSmallVecs)
         hipLaunchKernelGGL((adam_unrolled_bwd_vec<kSmallB>),
-                           dim3((unsigned)grid_for(((n >> 2) + kSmallB - 1) / kSmallB)), dim3(kSmallB), 0, st, a);
-      else if (vec)
-        hipLaunchKernelGGL((adam_unrolled_bwd_vec<kUBB>), dim3((unsigned)grid_for(((n >> 2) + kUBB - 1) / kUBB)),
-                           dim3(kUBB), 0, st, a);
+                           dim3((unsigned)grid_for(((a.n >> 2) + kSmallB - 1) / kSmallB)), dim3(kSmallB), 0, st, a);
       else
-        hipLaunchKernelGGL(adam_unrolled_bwd_elem, dim3((unsigned)grid_for((n + kUBB - 1) / kUBB)), dim3(kUBB), 0,
-                           st, a);
+        hipLaunchKernelGGL((adam_unrolled_bwd_vec<kUBB>), dim3((unsigned)grid_for(((a.n >> 2) + kUBB - 1) / kUBB)),
+                           dim3(kUBB), 0, st, a);
       khi -= run;
     } else {
       int64_t j = khi - 1;
       while (!mu_traj[j]) --j;  // mu_traj[0] is stored; check_trajectory bounds khi - j by kRS
       URBwdArgs a;
       const int C = (int)(khi - j);
-      a.n = n;
-      a.dP = dpK;
-      a.dm = dmu0;
-      a.dv = dnu0;
-      a.m0 = mu_traj[j];
-      a.v0 = nu_traj[j];
+      a.n = n - h;
+      a.head = h;
+      a.dP = dpK + h;
+      a.dm = dmu0 + h;
+      a.dv = dnu0 + h;
+      a.m0 = mu_traj[j] + h;
+      a.v0 = nu_traj[j] + h;
       a.init_mv = init_mv;
       for (int s = 0; s < kRS; ++s) {
         const bool on = s < C;
-        a.g[s] = on ? grads[j + s] : nullptr;
-        a.dg[s] = on ? dgrads[j + s] : nullptr;
+        a.g[s] = on ? grads[j + s] + h : nullptr;
+        a.dg[s] = on ? dgrads[j + s] + h : nullptr;
         if (on) make_coef(who, count0 + j + s, lr, b1, b2, eps, eps_root, &a.c[s]);
         else a.c[s] = AdamCoef{};
       }
-      rc = launch_urbwd_c(who, C, vec, a, st);
+      rc = launch_urbwd_c(who, C, a, st);
       if (rc) return rc;
       khi = j;
     }

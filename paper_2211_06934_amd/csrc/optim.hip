@@ -5,8 +5,8 @@
 // arithmetic is in optim_ops.hpp.
 // Like Adam they are HBM-bound elementwise streams; they share one generic
 // kernel skeleton with the measured Adam launch shape (1024-thread workgroups,
-// one 16-byte vector per lane per array, bounds checks only on the last tile,
-// a scalar kernel for pointers that are not 16-byte aligned).
+// one 4-element vector per lane per array, bounds checks only on the last tile,
+// vectors counted from a line boundary of the first output).
 #include <cmath>
 #include <initializer_list>
 
@@ -15,7 +15,10 @@
 namespace diffopt {
 namespace {
 
-constexpr int kOB = 1024;  // threads per workgroup
+// Threads per workgroup of the calls that stream from memory and of those small
+// enough for the Infinity Cache (measured with Adam's, see adam.hip).
+constexpr int kStreamB = 1024;
+constexpr int kKeepB = 512;
 
 template <int NIN, int NOUT>
 struct Streams {
@@ -23,39 +26,32 @@ struct Streams {
   float* out[NOUT];
 };
 
-template <class Op, bool GUARD>
-__device__ __forceinline__ void ew_tile(const Streams<Op::NIN, Op::NOUT>& s, int64_t t, int64_t nv, const Op& op) {
-  const int64_t i = t * kOB + threadIdx.x;
-  if (GUARD && i >= nv) return;
-  f32x4 x[Op::NIN];
-#pragma unroll
-  for (int a = 0; a < Op::NIN; ++a) x[a] = ld(reinterpret_cast<const f32x4*>(s.in[a]) + i);
-  f32x4 y[Op::NOUT];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float xi[Op::NIN], yo[Op::NOUT];
-#pragma unroll
-    for (int a = 0; a < Op::NIN; ++a) xi[a] = x[a][e];
-    op.apply(xi, yo);
-#pragma unroll
-    for (int b = 0; b < Op::NOUT; ++b) y[b][e] = yo[b];
-  }
-#pragma unroll
-  for (int b = 0; b < Op::NOUT; ++b) st(reinterpret_cast<f32x4*>(s.out[b]) + i, y[b]);
-}
-
-template <class Op>
-__global__ __launch_bounds__(kOB) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int64_t n, Op op) {
+template <class Op, int B, bool KEEP>
+__global__ __launch_bounds__(B) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int64_t n, int64_t head, Op op) {
   const int64_t nv = n >> 2;
-  const int64_t nfull = nv / kOB;
-  const int64_t ntiles = (nv + kOB - 1) / kOB;
+  const int64_t ntiles = (nv + B - 1) / B;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    if (t < nfull) ew_tile<Op, false>(s, t, nv, op);
-    else ew_tile<Op, true>(s, t, nv, op);
+    const int64_t i = t * B + threadIdx.x;
+    if (i >= nv) continue;
+    f32x4 x[Op::NIN];
+#pragma unroll
+    for (int a = 0; a < Op::NIN; ++a) x[a] = ld<KEEP>(reinterpret_cast<const f32x4u*>(s.in[a]) + i);
+    f32x4u y[Op::NOUT];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float xi[Op::NIN], yo[Op::NOUT];
+#pragma unroll
+      for (int a = 0; a < Op::NIN; ++a) xi[a] = x[a][e];
+      op.apply(xi, yo);
+#pragma unroll
+      for (int b = 0; b < Op::NOUT; ++b) y[b][e] = yo[b];
+    }
+#pragma unroll
+    for (int b = 0; b < Op::NOUT; ++b) st(reinterpret_cast<f32x4u*>(s.out[b]) + i, y[b]);
   }
   if (blockIdx.x == gridDim.x - 1) {
-    const int64_t e = (nv << 2) + threadIdx.x;
-    if (e < n) {
+    int64_t e;
+    if (edge_element(n, head, e)) {
       float xi[Op::NIN], yo[Op::NOUT];
 #pragma unroll
       for (int a = 0; a < Op::NIN; ++a) xi[a] = s.in[a][e];
@@ -67,33 +63,21 @@ __global__ __launch_bounds__(kOB) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int6
 }
 
 template <class Op>
-__global__ __launch_bounds__(kOB) void ew_scalar(Streams<Op::NIN, Op::NOUT> s, int64_t n, Op op) {
-  const int64_t e = (int64_t)blockIdx.x * kOB + threadIdx.x;
-  if (e >= n) return;
-  float xi[Op::NIN], yo[Op::NOUT];
-#pragma unroll
-  for (int a = 0; a < Op::NIN; ++a) xi[a] = s.in[a][e];
-  op.apply(xi, yo);
-#pragma unroll
-  for (int b = 0; b < Op::NOUT; ++b) s.out[b][e] = yo[b];
-}
-
-template <class Op>
-int launch(const char* who, const Streams<Op::NIN, Op::NOUT>& s, int64_t n, const Op& op, hipStream_t st) {
+int launch(const char* who, Streams<Op::NIN, Op::NOUT> s, int64_t n, const Op& op, hipStream_t st) {
   if (n == 0) return DIFFOPT_OK;
-  bool vec = true;
-  for (int a = 0; a < Op::NIN; ++a) vec = vec && (reinterpret_cast<uintptr_t>(s.in[a]) & 15u) == 0;
-  for (int b = 0; b < Op::NOUT; ++b) vec = vec && (reinterpret_cast<uintptr_t>(s.out[b]) & 15u) == 0;
-  if (vec) {
-    int64_t tiles = ((n >> 2) + kOB - 1) / kOB;
-    if (tiles < 1) tiles = 1;
-    if (tiles > 0x7fffffff) tiles = 0x7fffffff;
-    hipLaunchKernelGGL(ew_vec<Op>, dim3((unsigned)tiles), dim3(kOB), 0, st, s, n, op);
-  } else {
-    const int64_t blocks = (n + kOB - 1) / kOB;
-    if (blocks > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large for the unaligned path", who);
-    hipLaunchKernelGGL(ew_scalar<Op>, dim3((unsigned)blocks), dim3(kOB), 0, st, s, n, op);
-  }
+  const int64_t h = line_head(s.out[0], n);
+  for (int a = 0; a < Op::NIN; ++a) s.in[a] += h;
+  for (int b = 0; b < Op::NOUT; ++b) s.out[b] += h;
+  n -= h;
+  const bool keep = keep_in_cache(4 * (int64_t)(Op::NIN + Op::NOUT) * n);
+  const int block = keep ? kKeepB : kStreamB;
+  int64_t tiles = ((n >> 2) + block - 1) / block;
+  if (tiles < 1) tiles = 1;
+  if (tiles > 0x7fffffff) tiles = 0x7fffffff;
+  if (keep)
+    hipLaunchKernelGGL((ew_vec<Op, kKeepB, true>), dim3((unsigned)tiles), dim3(block), 0, st, s, n, h, op);
+  else
+    hipLaunchKernelGGL((ew_vec<Op, kStreamB, false>), dim3((unsigned)tiles), dim3(block), 0, st, s, n, h, op);
   return launch_status(who);
 }
 
