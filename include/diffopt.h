@@ -268,8 +268,9 @@ int diffopt_adam_unrolled_bwd(int64_t K, int64_t n, const float* dpK,
  *   every other pointer argument is a DEVICE array [nseg] of uint64 leaf
  *               addresses of one operand tree, in table order (entries of
  *               empty leaves are ignored); leaves are fp32, 4-byte aligned;
- *               leaves 16-byte aligned in every operand take 128-bit
- *               accesses, others an element path with the same result
+ *               any alignment takes 128-bit accesses with the same result,
+ *               fastest when a leaf has one phase of the 128-byte lines in
+ *               every operand
  * Aliasing as in the flat calls: an output leaf may be its own input leaf
  * (params_out[j] == params[j], dmu_in[j] == dmu[j], ...), never another leaf.
  * dmu and dnu are both NULL (zero cotangents) or both given.

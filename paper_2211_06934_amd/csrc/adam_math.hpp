@@ -68,16 +68,13 @@ int check_trajectory(const char* who, int64_t K, const P* mu_traj, const P* nu_t
   return DIFFOPT_OK;
 }
 
-// How a recomputing VJP gets each step's input moments: 0 keeps the run's
-// trajectory in registers, 1 recomputes each step's moments from the stored
-// state (C(C-1)/2 moment steps instead of C-1).  Measured on MI355X (K = 3,
-// n = 1.2e8): the flat kernel is faster with 1 (5.86 against 5.60 TB/s), the
-// leaf-direct one with 0 (5.37 against 5.08 TB/s).
+// How the flat recomputing VJP gets each step's input moments: 1 recomputes
+// each step's moments from the stored state (C(C-1)/2 moment steps instead of
+// C-1), 0 keeps the run's trajectory in registers, as the leaf-direct one
+// does.  Measured on MI355X (K = 3, n = 1.2e8): the flat kernel is faster with
+// 1 (5.86 against 5.60 TB/s), the leaf-direct one was not (5.08 against 5.37).
 #ifndef DIFFOPT_REMAT_QUAD_FLAT
 #define DIFFOPT_REMAT_QUAD_FLAT 1
-#endif
-#ifndef DIFFOPT_REMAT_QUAD_TREE
-#define DIFFOPT_REMAT_QUAD_TREE 0
 #endif
 
 // Loads of the inputs are streaming (non-temporal) unless the call is small
@@ -95,6 +92,15 @@ int check_trajectory(const char* who, int64_t K, const P* mu_traj, const P* nu_t
 constexpr int64_t kKeepBytes = int64_t(160) << 20;
 
 inline bool keep_in_cache(int64_t bytes_per_call) { return bytes_per_call <= kKeepBytes; }
+
+// The K-step drivers read the gradients in the forward and again in the VJP,
+// so keeping them pays a little further: leaf-direct forward + VJP, 3.6e6
+// elements (576 leaves), K = 4 (a VJP of 187 MB) 67.7 -> 60.7 us, K = 5 (215 MB)
+// 79.5 -> 75.4, K = 8 (302 MB) the same; 1.2e7 elements, K = 2 (421 MB) the
+// same, K = 4 191 -> 199.
+constexpr int64_t kKeepRunBytes = int64_t(224) << 20;
+
+inline bool keep_run_in_cache(int64_t bytes_per_launch) { return bytes_per_launch <= kKeepRunBytes; }
 
 template <bool KEEP = false, typename T>
 __device__ __forceinline__ T ld(const T* p) {

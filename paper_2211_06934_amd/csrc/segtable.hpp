@@ -122,6 +122,7 @@ __device__ __forceinline__ bool tiny_slot(const TinyTable& tt, int64_t j, int& o
 struct diffopt_segtable {
   int64_t nseg = 0;
   int64_t total = 0;
+  int64_t elems = 0;                // elements of all leaves
   int64_t nact = 0;
   int64_t ngroups = 0;
   int64_t ntiles = 0;

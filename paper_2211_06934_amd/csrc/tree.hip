@@ -425,6 +425,7 @@ extern "C" int diffopt_segtable_create(int64_t nseg, const int64_t* numel, const
   if (hipGetDevice(&t->device) != hipSuccess) t->device = -1;
   int64_t elems = 0;
   for (int64_t j = 0; j < nact; ++j) elems += host[(size_t)j].numel;
+  t->elems = elems;
   t->contiguous = 1;
   for (int64_t j = 0, at = 0; j < nact; at += host[(size_t)j].numel, ++j)
     if (host[(size_t)j].off != at) t->contiguous = 0;

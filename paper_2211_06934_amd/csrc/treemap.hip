@@ -4,17 +4,24 @@
 // Table 2 "Tree Map"; Sec. 2.3 for the step).  It saves the 8 bytes per element
 // that each flatten or unflatten of an operand tree would move.
 //
-// Work decomposition: the segment table of tree.hip.  Group k of nonempty
-// leaf j covers the leaf's elements [4k, 4k + 4); the table gives each leaf
-// ceil(numel / 4) + 1 groups rounded up to a multiple of 8, so the last ones
-// are empty here.  Leaves start on 8-group boundaries, so for 128-byte aligned
-// leaves no cache line is shared by two tiles (which run on different XCDs).  A
+// Work decomposition: the segment table of tree.hip.  As there, the groups of a
+// leaf are counted from the 128-byte line that holds the first byte of the
+// leaf in one operand, the first output: group k covers the leaf's elements
+// [4k - d, 4k - d + 4), d the leaf's element phase in that line, so waves store
+// whole lines whatever the leaf's alignment; the table gives each leaf
+// ceil(numel / 4) + 8 groups rounded up to a multiple of 8, which covers any
+// phase, and the rest are empty.  Leaves start on 8-group boundaries, so no
+// line of that operand is shared by two tiles (which run on different XCDs).  A
 // workgroup stages its window of the table in LDS together with the leaf
 // addresses of every operand tree, each lane binary-searches the window for
 // its groups, issues every operand load of all of its groups, then computes
-// and stores.  A group whose four elements exist and whose leaf is 16-byte
-// aligned in every operand takes 128-bit loads and stores; any other group is
-// processed element by element with the same arithmetic.
+// and stores: 128-bit accesses (dword-aligned where an operand's phase differs)
+// but for the elements at the ends of a leaf (see Whole).
+// Trees that are views of one flat buffer (576 leaves, 3.6e6 elements, odd
+// offsets) took an element path of serial 4-byte loads before: RMSProp with
+// momentum, forward and VJP, 74.4 us against 38.2 now.
+#include <type_traits>
+
 #include "adam_math.hpp"
 #include "optim_ops.hpp"
 #include "segtable.hpp"
@@ -35,8 +42,7 @@ namespace {
 
 constexpr int kFB = DIFFOPT_TM_FWD_BLOCK;
 constexpr int kBB = DIFFOPT_TM_BWD_BLOCK;
-static_assert(kTileGroups % kFB == 0 && kTileGroups % kBB == 0,
-              "a workgroup must cover one table tile exactly");
+static_assert(kTileGroups == kFB && kTileGroups % kBB == 0, "a workgroup must cover one table tile exactly");
 
 // Device arrays of leaf addresses, one per operand tree (table order).
 template <int NA>
@@ -44,13 +50,13 @@ struct LeafArrays {
   const uint64_t* a[NA];
 };
 
-// Stage the window of tile b: group offsets, element counts, one leaf address
-// per operand and an all-operands-aligned flag.  Operands with a null array
-// are skipped.  Returns the window length W.
+// Stage the window of tile b: group offsets, element counts and one leaf
+// address per operand.  Operands with a null array are skipped.  Returns the
+// window length W.
 template <int NA, int NT>
 __device__ __forceinline__ int stage_window(const SegEntry* __restrict__ seg, const int64_t* __restrict__ tile_first,
                                             const LeafArrays<NA>& arr, int dense_orig, int64_t b, int64_t* s_goff,
-                                            int64_t* s_numel, uint64_t (*s_ptr)[kWindowMax], int* s_al) {
+                                            int64_t* s_numel, uint64_t (*s_ptr)[kWindowMax]) {
   const int64_t j0 = tile_first[b];
   const int W = (int)(tile_first[b + 1] - j0 + 1);
   for (int t = threadIdx.x; t <= W; t += NT) {
@@ -59,23 +65,17 @@ __device__ __forceinline__ int stage_window(const SegEntry* __restrict__ seg, co
     if (t < W) {
       const int64_t leaf = dense_orig ? j0 + t : e.orig;
       // Every operand's address is loaded unconditionally (a null operand
-      // reads the table instead and keeps 0), so all NA loads go out before
-      // one wait; a load under the null test was followed by its own wait.
+      // reads the table instead and keeps 0): a load under the null test was
+      // followed by its own wait.
       uint64_t v[NA];
 #pragma unroll
       for (int q = 0; q < NA; ++q) {
         const uint64_t* src = arr.a[q] ? arr.a[q] + leaf : reinterpret_cast<const uint64_t*>(seg);
         v[q] = *src;
       }
-      uint64_t any = 0;
 #pragma unroll
-      for (int q = 0; q < NA; ++q) {
-        const uint64_t ptr = arr.a[q] ? v[q] : 0;
-        s_ptr[q][t] = ptr;
-        any |= ptr;
-      }
+      for (int q = 0; q < NA; ++q) s_ptr[q][t] = arr.a[q] ? v[q] : 0;
       s_numel[t] = e.numel;
-      s_al[t] = (any & 15u) == 0;
     }
   }
   return W;
@@ -96,91 +96,197 @@ __device__ __forceinline__ gptr<T> at(uint64_t base, int64_t i) {
   return gaddr<T>(base) + i;
 }
 
+// Elements between the start of a leaf's 128-byte line and the leaf.
+__device__ __forceinline__ int64_t line_phase(uint64_t leaf) { return (int64_t)((leaf >> 2) & 31u); }
+
+// How a group's elements [e0, e0 + 4) within [0, nel) are moved.  A group whose
+// four elements exist takes 128-bit accesses.  For the groups at the ends of a
+// leaf there are two ways:
+// - calls served by the Infinity Cache (KEEP) move a window of four
+//   consecutive elements of the leaf there too: at the ends it lies inside the
+//   leaf, so it holds elements of the neighbouring group as well (whose lane
+//   may be overwriting them, where an output leaf is its input leaf); they are
+//   computed and not stored.  A wave then makes one pass whatever its lanes
+//   hold (2,000 leaves of up to 2,000 elements, Adam forward and VJP: 14.9 us
+//   against 15.4 with a pass element by element; 20,000 leaves of up to 50, 19.7
+//   against 21.9).  Leaves of fewer than four elements move theirs together
+//   too, one by one (Few).
+// - calls that stream from memory go element by element: there a wave whose
+//   lanes are not 16 bytes apart costs more than the extra pass (20,000 leaves
+//   of up to 65,536: forward 586 us with windows, 555 without).
+struct Whole {
+  int64_t e0;
+  __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
+    return ld((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, e0));
+  }
+  template <int N>
+  __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
+#pragma unroll
+    for (int q = 0; q < N; ++q) st((gptr<f32x4u>)at<float>(leaf[q], e0), (f32x4u)x[q]);
+  }
+};
+
+// One element, in every slot.
+struct One {
+  int64_t i;
+  __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
+    const float x = *at<const float>(leaf, i);
+    return f32x4{x, x, x, x};
+  }
+  template <int N>
+  __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
+#pragma unroll
+    for (int q = 0; q < N; ++q) *at<float>(leaf[q], i) = x[q][0];
+  }
+};
+
+struct Window {
+  int64_t w;  // first element of the window
+  int own;    // bit e: element w + e belongs to this group
+  __device__ __forceinline__ Window(int64_t e0, int64_t nel) {
+    w = e0 < 0 ? 0 : (e0 + 4 <= nel ? e0 : nel - 4);
+    const int d = (int)(e0 - w);  // -3..3
+    own = d < 0 ? 15 >> -d : (15 << d) & 15;
+  }
+  __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
+    return ld<true>((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, w));
+  }
+  template <int N>
+  __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
+    if (own == 15) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) st((gptr<f32x4u>)at<float>(leaf[q], w), (f32x4u)x[q]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (own >> e & 1)
+#pragma unroll
+          for (int q = 0; q < N; ++q) *at<float>(leaf[q], w + e) = x[q][e];
+    }
+  }
+};
+
+// The elements of a leaf of one to three; a slot without an element takes the
+// group's last one, and computes and stores its value once more.
+struct Few {
+  int64_t first;
+  int last;  // counted from the first
+  __device__ __forceinline__ Few(int64_t e0, int64_t nel) {
+    first = e0 < 0 ? 0 : e0;
+    last = (int)((e0 + 4 < nel ? e0 + 4 : nel) - first) - 1;
+  }
+  __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) x[e] = *at<const float>(leaf, first + (e < last ? e : last));
+    x[3] = x[2];
+    return x;
+  }
+  template <int N>
+  __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) *at<float>(leaf[q], first + (e < last ? e : last)) = x[q][e];
+  }
+};
+
+template <class V>
+__device__ __forceinline__ V vector_at(int64_t e0, int64_t nel) {
+  if constexpr (std::is_same_v<V, Window>) return Window(e0, nel);
+  else return Whole{e0};
+}
+
+// The elements of a group that is not moved as a vector.
+template <bool KEEP, class Body>
+__device__ __forceinline__ void other_elements(int64_t e0, int64_t nel, const Body& body) {
+  if constexpr (KEEP) {
+    body(Few(e0, nel));
+  } else {
+    const int64_t end = e0 + 4 < nel ? e0 + 4 : nel;
+    for (int64_t i = e0 < 0 ? 0 : e0; i < end; ++i) body(One{i});
+  }
+}
+
+// Run a kernel's per-group code on the group's elements, if it has any.
+template <bool KEEP, class Body>
+__device__ __forceinline__ void on_group(int64_t e0, int64_t nel, const Body& body) {
+  if (e0 + 4 <= 0 || e0 >= nel) return;
+  if constexpr (KEEP) {
+    if (nel >= 4) body(Window(e0, nel));
+    else other_elements<true>(e0, nel, body);
+  } else {
+    if (e0 >= 0 && e0 + 4 <= nel) body(Whole{e0});
+    else other_elements<false>(e0, nel, body);
+  }
+}
+
+// One step on four elements.
+__device__ __forceinline__ void fwd_group(f32x4& p, const f32x4& g, f32x4& m, f32x4& v, const AdamCoef& c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const FwdOut o = fwd_elem(p[e], g[e], m[e], v[e], c);
+    p[e] = o.p;
+    m[e] = o.m;
+    v[e] = o.v;
+  }
+}
+
+template <bool HAS_MV>
+__device__ __forceinline__ f32x4 bwd_group(const f32x4& dP, f32x4& dM, f32x4& dV, const f32x4& g, const f32x4& m,
+                                           const f32x4& v, const AdamCoef& c) {
+  f32x4 rg;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const BwdOut o = bwd_elem<HAS_MV>(dP[e], HAS_MV ? dM[e] : 0.0f, HAS_MV ? dV[e] : 0.0f, g[e], m[e], v[e], c);
+    rg[e] = o.g;
+    dM[e] = o.m;
+    dV[e] = o.v;
+  }
+  return rg;
+}
+
 // Operands: 0 p, 1 g, 2 m, 3 v (inputs); 4 p', 5 m', 6 v' (outputs).
+template <bool KEEP>
 __global__ __launch_bounds__(kFB) void adam_fwd_tree_kernel(const SegEntry* __restrict__ seg,
                                                             const int64_t* __restrict__ tile_first, int64_t ngroups,
                                                             LeafArrays<7> arr, int dense_orig, AdamCoef c) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
   __shared__ uint64_t s_ptr[7][kWindowMax];
-  __shared__ int s_al[kWindowMax];
   const int64_t b = blockIdx.x;
-  const int W = stage_window<7, kFB>(seg, tile_first, arr, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window<7, kFB>(seg, tile_first, arr, dense_orig, b, s_goff, s_numel, s_ptr);
   __syncthreads();
-
-  constexpr int kFU = (int)(kTileGroups / kFB);  // groups per lane
-  f32x4 P[kFU], G[kFU], M[kFU], V[kFU];
-  int leaf[kFU], kind[kFU];
-  int64_t e0[kFU];
-#pragma unroll
-  for (int u = 0; u < kFU; ++u) {
-    const int64_t gidx = b * kTileGroups + (int64_t)u * kFB + threadIdx.x;
-    kind[u] = 0;
-    leaf[u] = 0;
-    e0[u] = 0;
-    if (gidx < ngroups) {
-      const int t = find_leaf(s_goff, W, gidx);
-      leaf[u] = t;
-      e0[u] = 4 * (gidx - s_goff[t]);
-      const int64_t nel = s_numel[t];
-      if (e0[u] < nel) {
-        kind[u] = (e0[u] + 4 <= nel && s_al[t]) ? 1 : 2;
-        if (kind[u] == 1) {
-          const int64_t i = e0[u] >> 2;
-          P[u] = ld(at<const f32x4>(s_ptr[0][t], i));
-          G[u] = ld(at<const f32x4>(s_ptr[1][t], i));
-          M[u] = ld(at<const f32x4>(s_ptr[2][t], i));
-          V[u] = ld(at<const f32x4>(s_ptr[3][t], i));
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kFU; ++u) {
-    const int t = leaf[u];
-    if (kind[u] == 1) {
-      f32x4 rp, rm, rv;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const FwdOut o = fwd_elem(P[u][e], G[u][e], M[u][e], V[u][e], c);
-        rp[e] = o.p;
-        rm[e] = o.m;
-        rv[e] = o.v;
-      }
-      const int64_t i = e0[u] >> 2;
-      st(at<f32x4>(s_ptr[4][t], i), rp);
-      st(at<f32x4>(s_ptr[5][t], i), rm);
-      st(at<f32x4>(s_ptr[6][t], i), rv);
-    } else if (kind[u] == 2) {
-      const int64_t end = e0[u] + 4 < s_numel[t] ? e0[u] + 4 : s_numel[t];
-      for (int64_t i = e0[u]; i < end; ++i) {
-        const FwdOut o = fwd_elem(*at<const float>(s_ptr[0][t], i), *at<const float>(s_ptr[1][t], i),
-                                  *at<const float>(s_ptr[2][t], i), *at<const float>(s_ptr[3][t], i), c);
-        *at<float>(s_ptr[4][t], i) = o.p;
-        *at<float>(s_ptr[5][t], i) = o.m;
-        *at<float>(s_ptr[6][t], i) = o.v;
-      }
-    }
-  }
+  const int64_t gidx = b * kTileGroups + threadIdx.x;
+  if (gidx >= ngroups) return;
+  const int t = find_leaf(s_goff, W, gidx);
+  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(s_ptr[4][t]), s_numel[t], [&](const auto& a) {
+    f32x4 p = a.load(s_ptr[0][t]);
+    const f32x4 g = a.load(s_ptr[1][t]);
+    f32x4 m = a.load(s_ptr[2][t]), v = a.load(s_ptr[3][t]);
+    const uint64_t out[3] = {s_ptr[4][t], s_ptr[5][t], s_ptr[6][t]};
+    fwd_group(p, g, m, v, c);
+    a.store(out, {p, m, v});
+  });
 }
 
 // Operands: 0 dP, 1 dM, 2 dV (null unless HAS_MV), 3 g, 4 m, 5 v (inputs);
 // 6 dg, 7 dm, 8 dv (outputs).
-template <bool HAS_MV>
+template <bool HAS_MV, bool KEEP>
 __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __restrict__ seg,
                                                             const int64_t* __restrict__ tile_first, int64_t ngroups,
                                                             LeafArrays<9> arr, int dense_orig, AdamCoef c) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
   __shared__ uint64_t s_ptr[9][kWindowMax];
-  __shared__ int s_al[kWindowMax];
   const int64_t b = blockIdx.x;
-  const int W = stage_window<9, kBB>(seg, tile_first, arr, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window<9, kBB>(seg, tile_first, arr, dense_orig, b, s_goff, s_numel, s_ptr);
   __syncthreads();
 
   constexpr int kBU = (int)(kTileGroups / kBB);  // groups per lane
   f32x4 P[kBU], Mb[kBU], Vb[kBU], G[kBU], M[kBU], V[kBU];
-  int leaf[kBU], kind[kBU];
+  using Vector = std::conditional_t<KEEP, Window, Whole>;
+  int leaf[kBU], kind[kBU];  // kind 0: no element, 1: a vector, loaded here, 2: other elements, below
   int64_t e0[kBU];
 #pragma unroll
   for (int u = 0; u < kBU; ++u) {
@@ -191,21 +297,22 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
     if (gidx < ngroups) {
       const int t = find_leaf(s_goff, W, gidx);
       leaf[u] = t;
-      e0[u] = 4 * (gidx - s_goff[t]);
+      e0[u] = 4 * (gidx - s_goff[t]) - line_phase(s_ptr[6][t]);
       const int64_t nel = s_numel[t];
-      if (e0[u] < nel) {
-        kind[u] = (e0[u] + 4 <= nel && s_al[t]) ? 1 : 2;
-        if (kind[u] == 1) {
-          const int64_t i = e0[u] >> 2;
-          P[u] = ld(at<const f32x4>(s_ptr[0][t], i));
-          if (HAS_MV) {
-            Mb[u] = ld(at<const f32x4>(s_ptr[1][t], i));
-            Vb[u] = ld(at<const f32x4>(s_ptr[2][t], i));
-          }
-          G[u] = ld(at<const f32x4>(s_ptr[3][t], i));
-          M[u] = ld(at<const f32x4>(s_ptr[4][t], i));
-          V[u] = ld(at<const f32x4>(s_ptr[5][t], i));
+      const bool any = e0[u] + 4 > 0 && e0[u] < nel;
+      if (any && (KEEP ? nel >= 4 : e0[u] >= 0 && e0[u] + 4 <= nel)) {
+        kind[u] = 1;
+        const Vector a = vector_at<Vector>(e0[u], nel);
+        P[u] = a.load(s_ptr[0][t]);
+        if (HAS_MV) {
+          Mb[u] = a.load(s_ptr[1][t]);
+          Vb[u] = a.load(s_ptr[2][t]);
         }
+        G[u] = a.load(s_ptr[3][t]);
+        M[u] = a.load(s_ptr[4][t]);
+        V[u] = a.load(s_ptr[5][t]);
+      } else if (any) {
+        kind[u] = 2;
       }
     }
   }
@@ -213,30 +320,28 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
   for (int u = 0; u < kBU; ++u) {
     const int t = leaf[u];
     if (kind[u] == 1) {
-      f32x4 rg, rm, rv;
+      const Vector a = vector_at<Vector>(e0[u], s_numel[t]);
+      const uint64_t out[3] = {s_ptr[6][t], s_ptr[7][t], s_ptr[8][t]};
+      const f32x4 rg = bwd_group<HAS_MV>(P[u], Mb[u], Vb[u], G[u], M[u], V[u], c);
+      a.store(out, {rg, Mb[u], Vb[u]});
+    }
+  }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const BwdOut o = bwd_elem<HAS_MV>(P[u][e], HAS_MV ? Mb[u][e] : 0.0f, HAS_MV ? Vb[u][e] : 0.0f, G[u][e],
-                                          M[u][e], V[u][e], c);
-        rg[e] = o.g;
-        rm[e] = o.m;
-        rv[e] = o.v;
-      }
-      const int64_t i = e0[u] >> 2;
-      st(at<f32x4>(s_ptr[6][t], i), rg);
-      st(at<f32x4>(s_ptr[7][t], i), rm);
-      st(at<f32x4>(s_ptr[8][t], i), rv);
-    } else if (kind[u] == 2) {
-      const int64_t end = e0[u] + 4 < s_numel[t] ? e0[u] + 4 : s_numel[t];
-      for (int64_t i = e0[u]; i < end; ++i) {
-        const BwdOut o = bwd_elem<HAS_MV>(
-            *at<const float>(s_ptr[0][t], i), HAS_MV ? *at<const float>(s_ptr[1][t], i) : 0.0f,
-            HAS_MV ? *at<const float>(s_ptr[2][t], i) : 0.0f, *at<const float>(s_ptr[3][t], i),
-            *at<const float>(s_ptr[4][t], i), *at<const float>(s_ptr[5][t], i), c);
-        *at<float>(s_ptr[6][t], i) = o.g;
-        *at<float>(s_ptr[7][t], i) = o.m;
-        *at<float>(s_ptr[8][t], i) = o.v;
-      }
+  for (int u = 0; u < kBU; ++u) {
+    const int t = leaf[u];
+    if (kind[u] == 2) {
+      other_elements<KEEP>(e0[u], s_numel[t], [&](const auto& a) {
+        const f32x4 p = a.load(s_ptr[0][t]);
+        f32x4 dm = {0.0f, 0.0f, 0.0f, 0.0f}, dv = dm;
+        if (HAS_MV) {
+          dm = a.load(s_ptr[1][t]);
+          dv = a.load(s_ptr[2][t]);
+        }
+        const f32x4 g = a.load(s_ptr[3][t]), m = a.load(s_ptr[4][t]), v = a.load(s_ptr[5][t]);
+        const uint64_t out[3] = {s_ptr[6][t], s_ptr[7][t], s_ptr[8][t]};
+        const f32x4 rg = bwd_group<HAS_MV>(p, dm, dv, g, m, v, c);
+        a.store(out, {rg, dm, dv});
+      });
     }
   }
 }
@@ -269,14 +374,13 @@ struct TBwdArgs {
 };
 
 // Stage the window of tile b for `na` operand trees: (operand, leaf) pairs
-// are spread over the workgroup, then each leaf's all-operands-aligned flag
-// is formed from LDS.  A NULL operand (a trajectory state the caller does
-// not store) stages address 0 and is never dereferenced.  Ends with the
-// workgroup synchronised.
+// are spread over the workgroup.  A NULL operand (a trajectory state the
+// caller does not store) stages address 0 and is never dereferenced.  Ends
+// with the workgroup synchronised.
 template <int NT = kUTB>
 __device__ __forceinline__ int stage_window_n(const SegEntry* __restrict__ seg, const int64_t* __restrict__ tile_first,
                                               const uint64_t* const* arrs, int na, int dense_orig, int64_t b,
-                                              int64_t* s_goff, int64_t* s_numel, uint64_t* s_ptr, int* s_al) {
+                                              int64_t* s_goff, int64_t* s_numel, uint64_t* s_ptr) {
   const int64_t j0 = tile_first[b];
   const int W = (int)(tile_first[b + 1] - j0 + 1);
   for (int t = threadIdx.x; t <= W; t += NT) {
@@ -290,155 +394,80 @@ __device__ __forceinline__ int stage_window_n(const SegEntry* __restrict__ seg, 
     s_ptr[q * kWindowMax + t] = arrs[q] ? arrs[q][leaf] : 0;  // NULL operand: an unstored state
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < W; t += NT) {
-    uint64_t any = 0;
-    for (int q = 0; q < na; ++q) any |= s_ptr[q * kWindowMax + t];
-    s_al[t] = (any & 15u) == 0;
-  }
-  __syncthreads();
   return W;
 }
 
+template <bool KEEP>
 __global__ __launch_bounds__(kUTB) void adam_unrolled_fwd_tree_kernel(const SegEntry* __restrict__ seg,
                                                                      const int64_t* __restrict__ tile_first,
                                                                      int64_t ngroups, int dense_orig, TFwdArgs a) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
-  __shared__ int s_al[kWindowMax];
   extern __shared__ uint64_t s_ptr[];  // [na][kWindowMax]
   const int na = 4 + 3 * a.K;
   const int64_t b = blockIdx.x;
-  const int W = stage_window_n(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window_n(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr);
   const int64_t gidx = b * kTileGroups + threadIdx.x;
   if (gidx >= ngroups) return;
   const int t = find_leaf(s_goff, W, gidx);
-  const int64_t e0 = 4 * (gidx - s_goff[t]);
-  const int64_t nel = s_numel[t];
-  if (e0 >= nel) return;
   const uint64_t* P = s_ptr + t;  // P[q * kWindowMax]: leaf address in operand q
 #define OP(q) P[(q) * kWindowMax]
-  if (e0 + 4 <= nel && s_al[t]) {
-    const int64_t i = e0 >> 2;
-    f32x4 p = ld(at<const f32x4>(OP(0), i)), m = ld(at<const f32x4>(OP(1), i)), v = ld(at<const f32x4>(OP(2), i));
-    f32x4 g = ld(at<const f32x4>(OP(4), i));
+  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(3)), s_numel[t], [&](const auto& x) {
+    f32x4 p = x.load(OP(0)), m = x.load(OP(1)), v = x.load(OP(2));
+    f32x4 g = x.load(OP(4));
     for (int s = 0; s < a.K; ++s) {
       f32x4 gn = g;
-      if (s + 1 < a.K) gn = ld(at<const f32x4>(OP(4 + 3 * (s + 1)), i));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const FwdOut o = fwd_elem(p[e], g[e], m[e], v[e], a.c[s]);
-        p[e] = o.p;
-        m[e] = o.m;
-        v[e] = o.v;
-      }
+      if (s + 1 < a.K) gn = x.load(OP(4 + 3 * (s + 1)));
+      fwd_group(p, g, m, v, a.c[s]);
       if (a.a[5 + 3 * s]) {  // uniform: a stored state
-        st(at<f32x4>(OP(5 + 3 * s), i), m);
-        st(at<f32x4>(OP(6 + 3 * s), i), v);
+        x.template store<2>({OP(5 + 3 * s), OP(6 + 3 * s)}, {m, v});
       }
       g = gn;
     }
-    st(at<f32x4>(OP(3), i), p);
-  } else {
-    const int64_t end = e0 + 4 < nel ? e0 + 4 : nel;
-    for (int64_t i = e0; i < end; ++i) {
-      float p = *at<const float>(OP(0), i), m = *at<const float>(OP(1), i), v = *at<const float>(OP(2), i);
-      for (int s = 0; s < a.K; ++s) {
-        const FwdOut o = fwd_elem(p, *at<const float>(OP(4 + 3 * s), i), m, v, a.c[s]);
-        p = o.p;
-        m = o.m;
-        v = o.v;
-        if (a.a[5 + 3 * s]) {
-          *at<float>(OP(5 + 3 * s), i) = m;
-          *at<float>(OP(6 + 3 * s), i) = v;
-        }
-      }
-      *at<float>(OP(3), i) = p;
-    }
-  }
+    x.template store<1>({OP(3)}, {p});
+  });
 #undef OP
 }
 
+template <bool KEEP>
 __global__ __launch_bounds__(kUTB) void adam_unrolled_bwd_tree_kernel(const SegEntry* __restrict__ seg,
                                                                      const int64_t* __restrict__ tile_first,
                                                                      int64_t ngroups, int dense_orig, TBwdArgs a) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
-  __shared__ int s_al[kWindowMax];
   extern __shared__ uint64_t s_ptr[];  // [na][kWindowMax]
   const int na = 3 + 4 * a.K;
   const int64_t b = blockIdx.x;
-  const int W = stage_window_n(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window_n(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr);
   const int64_t gidx = b * kTileGroups + threadIdx.x;
   if (gidx >= ngroups) return;
   const int t = find_leaf(s_goff, W, gidx);
-  const int64_t e0 = 4 * (gidx - s_goff[t]);
-  const int64_t nel = s_numel[t];
-  if (e0 >= nel) return;
   const uint64_t* P = s_ptr + t;
 #define OP(q) P[(q) * kWindowMax]
-  if (e0 + 4 <= nel && s_al[t]) {
-    const int64_t i = e0 >> 2;
-    const f32x4 dP = ld(at<const f32x4>(OP(0), i));
+  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
+    const f32x4 dP = x.load(OP(0));
     f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 g = ld(at<const f32x4>(OP(3), i)), m = ld(at<const f32x4>(OP(4), i)), v = ld(at<const f32x4>(OP(5), i));
+    f32x4 g = x.load(OP(3)), m = x.load(OP(4)), v = x.load(OP(5));
     if (a.init_mv) {
-      dM = ld(at<const f32x4>(OP(1), i));
-      dV = ld(at<const f32x4>(OP(2), i));
+      dM = x.load(OP(1));
+      dV = x.load(OP(2));
     }
     for (int s = 0; s < a.K; ++s) {
       f32x4 gn = g, mn = m, vn = v;
       if (s + 1 < a.K) {
-        gn = ld(at<const f32x4>(OP(3 + 4 * (s + 1)), i));
-        mn = ld(at<const f32x4>(OP(4 + 4 * (s + 1)), i));
-        vn = ld(at<const f32x4>(OP(5 + 4 * (s + 1)), i));
+        gn = x.load(OP(3 + 4 * (s + 1)));
+        mn = x.load(OP(4 + 4 * (s + 1)));
+        vn = x.load(OP(5 + 4 * (s + 1)));
       }
-      f32x4 rg;
-      if (s == 0 && !a.init_mv) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const BwdOut o = bwd_elem<false>(dP[e], 0.0f, 0.0f, g[e], m[e], v[e], a.c[s]);
-          rg[e] = o.g;
-          dM[e] = o.m;
-          dV[e] = o.v;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const BwdOut o = bwd_elem<true>(dP[e], dM[e], dV[e], g[e], m[e], v[e], a.c[s]);
-          rg[e] = o.g;
-          dM[e] = o.m;
-          dV[e] = o.v;
-        }
-      }
-      st(at<f32x4>(OP(6 + 4 * s), i), rg);
+      const f32x4 rg = s == 0 && !a.init_mv ? bwd_group<false>(dP, dM, dV, g, m, v, a.c[s])
+                                            : bwd_group<true>(dP, dM, dV, g, m, v, a.c[s]);
+      x.template store<1>({OP(6 + 4 * s)}, {rg});
       g = gn;
       m = mn;
       v = vn;
     }
-    st(at<f32x4>(OP(1), i), dM);
-    st(at<f32x4>(OP(2), i), dV);
-  } else {
-    const int64_t end = e0 + 4 < nel ? e0 + 4 : nel;
-    for (int64_t i = e0; i < end; ++i) {
-      const float dP = *at<const float>(OP(0), i);
-      float dM = 0.0f, dV = 0.0f;
-      if (a.init_mv) {
-        dM = *at<const float>(OP(1), i);
-        dV = *at<const float>(OP(2), i);
-      }
-      for (int s = 0; s < a.K; ++s) {
-        const float g = *at<const float>(OP(3 + 4 * s), i), m = *at<const float>(OP(4 + 4 * s), i),
-                    v = *at<const float>(OP(5 + 4 * s), i);
-        const BwdOut o = (s == 0 && !a.init_mv) ? bwd_elem<false>(dP, 0.0f, 0.0f, g, m, v, a.c[s])
-                                                : bwd_elem<true>(dP, dM, dV, g, m, v, a.c[s]);
-        *at<float>(OP(6 + 4 * s), i) = o.g;
-        dM = o.m;
-        dV = o.v;
-      }
-      *at<float>(OP(1), i) = dM;
-      *at<float>(OP(2), i) = dV;
-    }
-  }
+    x.template store<2>({OP(1), OP(2)}, {dM, dV});
+  });
 #undef OP
 }
 
@@ -469,42 +498,34 @@ constexpr int kTRSplit = DIFFOPT_TRBWD_SPLIT;
 constexpr int kTRB = kUTB / kTRSplit;
 static_assert(kUTB % kTRSplit == 0, "the split must divide the tile");
 
-template <int C>
+template <int C, bool KEEP>
 __global__ __launch_bounds__(kTRB) void adam_unrolled_bwd_tree_remat_kernel(const SegEntry* __restrict__ seg,
                                                                            const int64_t* __restrict__ tile_first,
                                                                            int64_t ngroups, int dense_orig,
                                                                            TRBwdArgs a) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
-  __shared__ int s_al[kWindowMax];
   extern __shared__ uint64_t s_ptr[];  // [na][kWindowMax]
   constexpr int na = 5 + 2 * C;
   const int64_t b = blockIdx.x / kTRSplit;  // table tile
-  const int W = stage_window_n<kTRB>(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window_n<kTRB>(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr);
   const int64_t gidx = b * kTileGroups + (int64_t)(blockIdx.x % kTRSplit) * kTRB + threadIdx.x;
   if (gidx >= ngroups) return;
   const int t = find_leaf(s_goff, W, gidx);
-  const int64_t e0 = 4 * (gidx - s_goff[t]);
-  const int64_t nel = s_numel[t];
-  if (e0 >= nel) return;
   const uint64_t* P = s_ptr + t;
 #define OP(q) P[(q) * kWindowMax]
-  if (e0 + 4 <= nel && s_al[t]) {
-    const int64_t i = e0 >> 2;
-    const f32x4 dP = ld(at<const f32x4>(OP(0), i));
-    const f32x4 M0 = ld(at<const f32x4>(OP(3), i)), V0 = ld(at<const f32x4>(OP(4), i));
-    f32x4 G[C];
+  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
+    const f32x4 dP = x.load(OP(0));
+    f32x4 M[C], V[C], G[C];  // M[s], V[s]: the moments step s consumed
+    M[0] = x.load(OP(3));
+    V[0] = x.load(OP(4));
 #pragma unroll
-    for (int s = 0; s < C; ++s) G[s] = ld(at<const f32x4>(OP(5 + 2 * s), i));
+    for (int s = 0; s < C; ++s) G[s] = x.load(OP(5 + 2 * s));
     f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
     if (a.init_mv) {
-      dM = ld(at<const f32x4>(OP(1), i));
-      dV = ld(at<const f32x4>(OP(2), i));
+      dM = x.load(OP(1));
+      dV = x.load(OP(2));
     }
-#if !DIFFOPT_REMAT_QUAD_TREE
-    f32x4 M[C], V[C];  // M[s], V[s]: the moments step s consumed
-    M[0] = M0;
-    V[0] = V0;
 #pragma unroll
     for (int s = 0; s + 1 < C; ++s) {
 #pragma unroll
@@ -513,76 +534,26 @@ __global__ __launch_bounds__(kTRB) void adam_unrolled_bwd_tree_remat_kernel(cons
         V[s + 1][e] = moment2(G[s][e], V[s][e], a.c[s]);
       }
     }
-#endif
 #pragma unroll
     for (int s = C - 1; s >= 0; --s) {
-#if DIFFOPT_REMAT_QUAD_TREE
-      f32x4 Ms, Vs;  // this step's input moments, recomputed from (M0, V0)
-      run_moments<C>(s, M0, V0, G, a.c, Ms, Vs);
-#else
-      const f32x4 Ms = M[s], Vs = V[s];
-#endif
-      f32x4 rg;
-      if (s == C - 1 && !a.init_mv) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const BwdOut o = bwd_elem<false>(dP[e], 0.0f, 0.0f, G[s][e], Ms[e], Vs[e], a.c[s]);
-          rg[e] = o.g;
-          dM[e] = o.m;
-          dV[e] = o.v;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const BwdOut o = bwd_elem<true>(dP[e], dM[e], dV[e], G[s][e], Ms[e], Vs[e], a.c[s]);
-          rg[e] = o.g;
-          dM[e] = o.m;
-          dV[e] = o.v;
-        }
-      }
-      st(at<f32x4>(OP(6 + 2 * s), i), rg);
+      const f32x4 rg = s == C - 1 && !a.init_mv ? bwd_group<false>(dP, dM, dV, G[s], M[s], V[s], a.c[s])
+                                                : bwd_group<true>(dP, dM, dV, G[s], M[s], V[s], a.c[s]);
+      x.template store<1>({OP(6 + 2 * s)}, {rg});
     }
-    st(at<f32x4>(OP(1), i), dM);
-    st(at<f32x4>(OP(2), i), dV);
-  } else {
-    const int64_t end = e0 + 4 < nel ? e0 + 4 : nel;
-    for (int64_t i = e0; i < end; ++i) {
-      const float dP = *at<const float>(OP(0), i);
-      float G[C], M[C], V[C];
-      M[0] = *at<const float>(OP(3), i);
-      V[0] = *at<const float>(OP(4), i);
-#pragma unroll
-      for (int s = 0; s < C; ++s) G[s] = *at<const float>(OP(5 + 2 * s), i);
-#pragma unroll
-      for (int s = 0; s + 1 < C; ++s) {
-        M[s + 1] = moment1(G[s], M[s], a.c[s]);
-        V[s + 1] = moment2(G[s], V[s], a.c[s]);
-      }
-      float dM = 0.0f, dV = 0.0f;
-      if (a.init_mv) {
-        dM = *at<const float>(OP(1), i);
-        dV = *at<const float>(OP(2), i);
-      }
-#pragma unroll
-      for (int s = C - 1; s >= 0; --s) {
-        const BwdOut o = (s == C - 1 && !a.init_mv) ? bwd_elem<false>(dP, 0.0f, 0.0f, G[s], M[s], V[s], a.c[s])
-                                                    : bwd_elem<true>(dP, dM, dV, G[s], M[s], V[s], a.c[s]);
-        *at<float>(OP(6 + 2 * s), i) = o.g;
-        dM = o.m;
-        dV = o.v;
-      }
-      *at<float>(OP(1), i) = dM;
-      *at<float>(OP(2), i) = dV;
-    }
-  }
+    x.template store<2>({OP(1), OP(2)}, {dM, dV});
+  });
 #undef OP
 }
 
 template <int C>
 void launch_trbwd(const diffopt_segtable* t, const TRBwdArgs& a, hipStream_t st) {
   const size_t lds = sizeof(uint64_t) * kWindowMax * (5 + 2 * C);
-  hipLaunchKernelGGL((adam_unrolled_bwd_tree_remat_kernel<C>), dim3((unsigned)(t->ntiles * kTRSplit)), dim3(kTRB),
-                     lds, st, t->d_seg, t->d_tile_first, t->ngroups, t->dense_orig, a);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(t->ntiles * kTRSplit)), dim3(kTRB), lds, st, t->d_seg, t->d_tile_first,
+                       t->ngroups, t->dense_orig, a);
+  };
+  if (keep_run_in_cache((20 + 8 * C + (a.init_mv ? 8 : 0)) * t->elems)) go(adam_unrolled_bwd_tree_remat_kernel<C, true>);
+  else go(adam_unrolled_bwd_tree_remat_kernel<C, false>);
 }
 
 // Run length C is a template argument so the trajectory stays in registers.
@@ -769,50 +740,38 @@ int launch_tiny_bwd_c(const char* who, int C, const diffopt_segtable* t, const T
 // Adam kernels: one table tile per workgroup, one group per lane, the leaf
 // address of every operand staged in the window.  Operands: the op's inputs,
 // then its outputs.
-template <class Op>
+template <class Op, bool KEEP>
 __global__ __launch_bounds__(kUTB) void ew_tree_kernel(const SegEntry* __restrict__ seg,
                                                       const int64_t* __restrict__ tile_first, int64_t ngroups,
                                                       int dense_orig, LeafArrays<Op::NIN + Op::NOUT> arr, Op op) {
   constexpr int NA = Op::NIN + Op::NOUT;
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
-  __shared__ int s_al[kWindowMax];
   __shared__ uint64_t s_ptr[NA * kWindowMax];
   const int64_t b = blockIdx.x;
-  const int W = stage_window_n(seg, tile_first, arr.a, NA, dense_orig, b, s_goff, s_numel, s_ptr, s_al);
+  const int W = stage_window_n(seg, tile_first, arr.a, NA, dense_orig, b, s_goff, s_numel, s_ptr);
   const int64_t gidx = b * kTileGroups + threadIdx.x;
   if (gidx >= ngroups) return;
   const int t = find_leaf(s_goff, W, gidx);
-  const int64_t e0 = 4 * (gidx - s_goff[t]);
-  const int64_t nel = s_numel[t];
-  if (e0 >= nel) return;
   const uint64_t* P = s_ptr + t;
-  float xi[Op::NIN], yo[Op::NOUT];
-  if (e0 + 4 <= nel && s_al[t]) {
-    const int64_t i = e0 >> 2;
+  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(P[Op::NIN * kWindowMax]), s_numel[t], [&](const auto& acc) {
     f32x4 x[Op::NIN], y[Op::NOUT];
 #pragma unroll
-    for (int a = 0; a < Op::NIN; ++a) x[a] = ld(at<const f32x4>(P[a * kWindowMax], i));
+    for (int a = 0; a < Op::NIN; ++a) x[a] = acc.load(P[a * kWindowMax]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
+      float xi[Op::NIN], yo[Op::NOUT];
 #pragma unroll
       for (int a = 0; a < Op::NIN; ++a) xi[a] = x[a][e];
       op.apply(xi, yo);
 #pragma unroll
       for (int q = 0; q < Op::NOUT; ++q) y[q][e] = yo[q];
     }
+    uint64_t out[Op::NOUT];
 #pragma unroll
-    for (int q = 0; q < Op::NOUT; ++q) st(at<f32x4>(P[(Op::NIN + q) * kWindowMax], i), y[q]);
-  } else {
-    const int64_t end = e0 + 4 < nel ? e0 + 4 : nel;
-    for (int64_t i = e0; i < end; ++i) {
-#pragma unroll
-      for (int a = 0; a < Op::NIN; ++a) xi[a] = *at<const float>(P[a * kWindowMax], i);
-      op.apply(xi, yo);
-#pragma unroll
-      for (int q = 0; q < Op::NOUT; ++q) *at<float>(P[(Op::NIN + q) * kWindowMax], i) = yo[q];
-    }
-  }
+    for (int q = 0; q < Op::NOUT; ++q) out[q] = P[(Op::NIN + q) * kWindowMax];
+    acc.store(out, y);
+  });
 }
 
 // Small trees (a TinyTable): one element per lane, the table in the kernel
@@ -851,8 +810,11 @@ struct TreeRun {
     for (int q = 0; q < Op::NOUT; ++q) arr.a[Op::NIN + q] = static_cast<const uint64_t*>(out[q]);
     if (t->tiny)
       hipLaunchKernelGGL((ew_tree_tiny<Op>), dim3(tiny_blocks(t)), dim3(kTinyB), 0, st, t->small, arr, op);
+    else if (keep_in_cache(4 * (int64_t)(Op::NIN + Op::NOUT) * t->elems))
+      hipLaunchKernelGGL((ew_tree_kernel<Op, true>), dim3((unsigned)t->ntiles), dim3(kUTB), 0, st, t->d_seg,
+                         t->d_tile_first, t->ngroups, t->dense_orig, arr, op);
     else
-      hipLaunchKernelGGL((ew_tree_kernel<Op>), dim3((unsigned)t->ntiles), dim3(kUTB), 0, st, t->d_seg,
+      hipLaunchKernelGGL((ew_tree_kernel<Op, false>), dim3((unsigned)t->ntiles), dim3(kUTB), 0, st, t->d_seg,
                          t->d_tile_first, t->ngroups, t->dense_orig, arr, op);
     return launch_status(who);
   }
@@ -869,31 +831,37 @@ int check_table(const char* who, const diffopt_segtable* t) {
 
 int launch_fwd_tree(const diffopt_segtable* t, const LeafArrays<7>& arr, const AdamCoef& c, hipStream_t st) {
   if (t->ntiles == 0) return DIFFOPT_OK;
-  hipLaunchKernelGGL(adam_fwd_tree_kernel, dim3((unsigned)t->ntiles), dim3(kFB), 0, st, t->d_seg, t->d_tile_first,
-                     t->ngroups, arr, t->dense_orig, c);
+  if (keep_in_cache(28 * t->elems))
+    hipLaunchKernelGGL(adam_fwd_tree_kernel<true>, dim3((unsigned)t->ntiles), dim3(kFB), 0, st, t->d_seg,
+                       t->d_tile_first, t->ngroups, arr, t->dense_orig, c);
+  else
+    hipLaunchKernelGGL(adam_fwd_tree_kernel<false>, dim3((unsigned)t->ntiles), dim3(kFB), 0, st, t->d_seg,
+                       t->d_tile_first, t->ngroups, arr, t->dense_orig, c);
   return launch_status("diffopt_adam_fwd_tree");
 }
 
 // Workgroups of the leaf-direct VJP resident per CU.  Its registers allow
 // seven; with six reads and three writes per element that many oversubscribe
 // the memory system, and five ran the 20,000-leaf tree's VJP 4% faster (four:
-// the same; six: no gain).  The launch reserves otherwise unused dynamic LDS
-// so that no more than kBwdTreeResident workgroups fit in a CU's 160 KiB.
+// the same; six: 1.5% slower).  The launch reserves otherwise unused dynamic
+// LDS so that no more than kBwdTreeResident workgroups fit in a CU's 160 KiB.
 constexpr int kBwdTreeResident = 5;
 constexpr size_t kLdsPerCU = 160 * 1024;
-constexpr size_t kBwdTreeStaticLds = (kWindowMax + 1) * 8 + kWindowMax * (8 + 9 * 8 + 4);
+constexpr size_t kBwdTreeStaticLds = (kWindowMax + 1) * 8 + kWindowMax * (8 + 9 * 8);
 constexpr size_t kBwdTreeLdsPad = kLdsPerCU / kBwdTreeResident - kBwdTreeStaticLds - 256;
 static_assert(kLdsPerCU / (kBwdTreeStaticLds + kBwdTreeLdsPad) == kBwdTreeResident,
               "the reserved LDS must leave room for exactly kBwdTreeResident workgroups");
 
 int launch_bwd_tree(const diffopt_segtable* t, const LeafArrays<9>& arr, const AdamCoef& c, hipStream_t st) {
   if (t->ntiles == 0) return DIFFOPT_OK;
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)t->ntiles), dim3(kBB), kBwdTreeLdsPad, st, t->d_seg, t->d_tile_first,
+                       t->ngroups, arr, t->dense_orig, c);
+  };
   if (arr.a[1])
-    hipLaunchKernelGGL((adam_bwd_tree_kernel<true>), dim3((unsigned)t->ntiles), dim3(kBB), kBwdTreeLdsPad, st,
-                       t->d_seg, t->d_tile_first, t->ngroups, arr, t->dense_orig, c);
+    keep_in_cache(36 * t->elems) ? go(adam_bwd_tree_kernel<true, true>) : go(adam_bwd_tree_kernel<true, false>);
   else
-    hipLaunchKernelGGL((adam_bwd_tree_kernel<false>), dim3((unsigned)t->ntiles), dim3(kBB), kBwdTreeLdsPad, st,
-                       t->d_seg, t->d_tile_first, t->ngroups, arr, t->dense_orig, c);
+    keep_in_cache(28 * t->elems) ? go(adam_bwd_tree_kernel<false, true>) : go(adam_bwd_tree_kernel<false, false>);
   return launch_status("diffopt_adam_bwd_tree");
 }
 
@@ -1017,8 +985,14 @@ extern "C" int diffopt_adam_unrolled_fwd_tree(const diffopt_segtable* table, int
       launch_tiny_fwd_k(table, a, st);
     } else {
       const size_t lds = sizeof(uint64_t) * kWindowMax * (4 + 3 * a.K);
-      hipLaunchKernelGGL(adam_unrolled_fwd_tree_kernel, dim3((unsigned)table->ntiles), dim3(kUTB), lds, st,
-                         table->d_seg, table->d_tile_first, table->ngroups, table->dense_orig, a);
+      int64_t values = 4 + a.K;  // moved per element
+      for (int s = 0; s < a.K; ++s) values += a.a[5 + 3 * s] ? 2 : 0;
+      const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)table->ntiles), dim3(kUTB), lds, st, table->d_seg,
+                           table->d_tile_first, table->ngroups, table->dense_orig, a);
+      };
+      if (keep_run_in_cache(4 * values * table->elems)) go(adam_unrolled_fwd_tree_kernel<true>);
+      else go(adam_unrolled_fwd_tree_kernel<false>);
     }
     rc = launch_status(who);
     if (rc) return rc;
@@ -1093,8 +1067,12 @@ extern "C" int diffopt_adam_unrolled_bwd_tree(const diffopt_segtable* table, int
         make_coef(who, count0 + k - 1, lr, b1, b2, eps, eps_root, &a.c[s]);
       }
       const size_t lds = sizeof(uint64_t) * kWindowMax * (3 + 4 * a.K);
-      hipLaunchKernelGGL(adam_unrolled_bwd_tree_kernel, dim3((unsigned)table->ntiles), dim3(kUTB), lds, st,
-                         table->d_seg, table->d_tile_first, table->ngroups, table->dense_orig, a);
+      const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)table->ntiles), dim3(kUTB), lds, st, table->d_seg,
+                           table->d_tile_first, table->ngroups, table->dense_orig, a);
+      };
+      if (keep_run_in_cache((12 + 16 * a.K + (init_mv ? 8 : 0)) * table->elems)) go(adam_unrolled_bwd_tree_kernel<true>);
+      else go(adam_unrolled_bwd_tree_kernel<false>);
       khi -= run;
     } else {
       int64_t j = khi - 1;

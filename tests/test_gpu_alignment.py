@@ -116,3 +116,82 @@ def test_unrolled_driver_at_any_phase(n, K, kept):
     for phases in PHASES:
         for k, (a, b) in enumerate(zip(run(_Slices(phases)), ref)):
             assert torch.equal(a, b), (n, K, phases, k)
+
+
+def _trees(P, sizes, phases, values):
+    """One tree per row of values: its leaves one after another in a guarded buffer, each tree at its own element phase."""
+    table = P.segtable_create(sizes)
+    S = _Slices(phases)
+    flats = [S.take(x) if x is not None else S.out(sum(sizes)) for x in values]
+    starts = [0]
+    for k in sizes[:-1]:
+        starts.append(starts[-1] + k)
+    ptrs = [torch.tensor([f.data_ptr() + 4 * o for o in starts], dtype=torch.int64).cuda() for f in flats]
+    return table, S, flats, ptrs
+
+
+# tiled kernels (over 32 leaves): empty, tiny and line-sized leaves around tile
+# edges, each tree's leaves at its own phases
+TREE_SIZES = [0, 1, 2, 3, 4, 5, 31, 32, 33, 64, 100, 127, 2048, 2049, 7, 1, 0, 12345] + [1, 3, 513, 6] * 6
+
+
+@pytest.mark.parametrize("phases", PHASES)
+def test_leaf_direct_steps_at_any_phase(phases):
+    import paper_2211_06934_amd as P
+    n, K = sum(TREE_SIZES), 10
+    x = _values(8 + K, n, 11)
+    x[2].abs_()
+    x[3].abs_()
+    p, g, m, v, dp, dm, dv = x[:7]
+
+    flat = {}
+    S = _Slices([0])
+    flat["adam"] = _adam(P, x[:7], S, n)
+    flat["sgd"] = _sgd(P, x[:7], S, n)
+    flat["rmsprop"] = _rmsprop(P, x[:7], S, n)
+
+    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp, dm, dv] + [None] * 9)
+    P.adam_fwd_tree(t, a[0], a[1], a[2], a[3], *HYPER, a[7], a[8], a[9])
+    P.adam_bwd_tree(t, a[4], a[5], a[6], a[1], a[2], a[3], *HYPER, a[10], a[11], a[12])
+    P.adam_bwd_tree(t, a[4], None, None, a[1], a[2], a[3], *HYPER, a[13], a[14], a[15])
+    torch.cuda.synchronize()
+    for k, i in enumerate([0, 1, 2, 4, 5, 6, 7, 8, 9]):
+        assert torch.equal(f[7 + k], flat["adam"][i]), ("adam", k)
+    S.check_guards()
+
+    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp] + [None] * 4)
+    P.sgd_fwd_tree(t, a[0], a[1], a[2], 0.1, 0.9, True, a[5], a[6])
+    P.sgd_bwd_tree(t, a[3], a[4], 0.1, 0.9, True, a[7], a[8])
+    torch.cuda.synchronize()
+    for k in range(4):
+        assert torch.equal(f[5 + k], flat["sgd"][k]), ("sgd", k)
+    S.check_guards()
+
+    h = (0.01, 0.99, 1e-8, 1e-9, 0.9)
+    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp, dm, dv] + [None] * 6)
+    P.rmsprop_fwd_tree(t, a[0], a[1], a[2], a[3], *h, a[7], a[8], a[9])
+    P.rmsprop_bwd_tree(t, a[4], a[5], a[6], a[1], a[2], *h, a[10], a[11], a[12])
+    torch.cuda.synchronize()
+    for k in range(6):
+        assert torch.equal(f[7 + k], flat["rmsprop"][k]), ("rmsprop", k)
+    S.check_guards()
+
+    for kept in ({5, 10}, set(range(1, K + 1))):
+        S = _Slices([0])
+        mu = [m] + [S.out(n) if k in kept else None for k in range(1, K + 1)]
+        nu = [v] + [S.out(n) if k in kept else None for k in range(1, K + 1)]
+        pK, dg, d0, d1 = S.out(n), [S.out(n) for _ in range(K)], S.out(n), S.out(n)
+        P.adam_unrolled_fwd(p, x[8:], mu, nu, pK, *HYPER)
+        P.adam_unrolled_bwd(dp, x[8:], mu, nu, dg, d0, d1, *HYPER)
+        order = sorted(kept)
+        t, S, f, a = _trees(P, TREE_SIZES, phases, [p, m, v, dp, *x[8:]] + [None] * (3 + K + 2 * len(kept)))
+        at = 4 + K + 3 + K
+        tmu = [a[1]] + [a[at + order.index(k)] if k in kept else None for k in range(1, K + 1)]
+        tnu = [a[2]] + [a[at + len(kept) + order.index(k)] if k in kept else None for k in range(1, K + 1)]
+        tg, out, tdg = a[4:4 + K], 4 + K, a[4 + K + 3:at]
+        P.adam_unrolled_fwd_tree(t, a[0], tg, tmu, tnu, a[out], *HYPER)
+        P.adam_unrolled_bwd_tree(t, a[3], tg, tmu, tnu, tdg, a[out + 1], a[out + 2], *HYPER)
+        torch.cuda.synchronize()
+        for k, (got, want) in enumerate(zip(f[out:], [pK, d0, d1, *dg, *(mu[k] for k in order), *(nu[k] for k in order)])):
+            assert torch.equal(got, want), ("unrolled", sorted(kept), k)
+        S.check_guards()
