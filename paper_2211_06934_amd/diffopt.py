@@ -3,7 +3,8 @@
 Argument marshalling only: every function here is the C entry point
 ``diffopt_<name>`` with the same arguments, taking torch tensors (device
 memory) or raw device addresses, and enqueuing on the current torch stream
-unless a stream is given.  All arithmetic and data movement happens in the
+unless a stream is given.  Ordinary operands are checked and passed on by the
+native module _binding, everything else by the ctypes code below it.  All arithmetic and data movement happens in the
 HIP library; importing this module fails loudly if the library is missing.
 """
 from __future__ import annotations
@@ -84,6 +85,16 @@ def _load_library():
 _lib = _load_library()
 LIBRARY_PATH = _LIB_PATH
 
+# The native half of this module (csrc/binding.cpp): _native.<entry>(n, C
+# arguments...) checks the operands, takes their addresses and calls
+# diffopt_<entry>, or returns None for operands it does not take (raw
+# subclasses, wrong sizes, ...), which the code after it here then accepts or
+# refuses.
+try:
+    from . import _binding as _native
+except ImportError as e:
+    raise ImportError("the native binding is not built (%s); run `python paper_2211_06934_amd/build.py`" % e) from e
+
 
 def last_error() -> str:
     """diffopt_last_error(): message of the last failing call on this thread."""
@@ -93,6 +104,15 @@ def last_error() -> str:
 def _check(rc: int) -> None:
     if rc != DIFFOPT_OK:
         raise DiffoptError(rc, last_error())
+
+
+def _done(rc: Optional[int]) -> bool:
+    """Whether the native call handled the arguments; raises if it failed."""
+    if rc is None:
+        return False
+    if rc != DIFFOPT_OK:
+        raise DiffoptError(rc, last_error())
+    return True
 
 
 def _addr(x, what: str, dtype=torch.float32, n: Optional[int] = None) -> Optional[int]:
@@ -267,6 +287,10 @@ def adam_fwd(params, grad, mu, nu, count, lr, b1, b2, eps, eps_root,
     """diffopt_adam_fwd; n defaults to params.numel()."""
     if n is None:
         n = params.numel()
+    if _done(_native.adam_fwd(
+            n, params, grad, mu, nu, n, count, lr, b1, b2, eps, eps_root, params_out, mu_out, nu_out,
+            update_out, _stream(stream))):
+        return
     _check(_lib.diffopt_adam_fwd(
         _addr(params, "params", n=n), _addr(grad, "grad", n=n), _addr(mu, "mu", n=n), _addr(nu, "nu", n=n),
         int(n), int(count), float(lr), float(b1), float(b2), float(eps), float(eps_root),
@@ -279,6 +303,10 @@ def adam_bwd(dupdate, dmu, dnu, grad, mu, nu, count, lr, b1, b2, eps, eps_root,
     """diffopt_adam_bwd; dmu/dnu/dparams may be None."""
     if n is None:
         n = dupdate.numel()
+    if _done(_native.adam_bwd(
+            n, dupdate, dmu, dnu, grad, mu, nu, n, count, lr, b1, b2, eps, eps_root,
+            dparams, dgrad, dmu_in, dnu_in, _stream(stream))):
+        return
     _check(_lib.diffopt_adam_bwd(
         _addr(dupdate, "dupdate", n=n), _addr(dmu, "dmu", n=n), _addr(dnu, "dnu", n=n),
         _addr(grad, "grad", n=n), _addr(mu, "mu", n=n), _addr(nu, "nu", n=n),
@@ -298,6 +326,10 @@ def adam_unrolled_fwd(p0, grads, mu_traj, nu_traj, pK, count0, lr, b1, b2, eps, 
     n = p0.numel()
     if len(mu_traj) != K + 1 or len(nu_traj) != K + 1:
         raise ValueError("mu_traj and nu_traj need K+1 entries")
+    if _done(_native.adam_unrolled_fwd(
+            n, K, n, p0, grads, mu_traj, nu_traj, pK, count0, lr, b1, b2, eps, eps_root,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_adam_unrolled_fwd(
         K, n, _addr(p0, "p0", n=n), _ptr_array(grads, "grads", n), _ptr_array(mu_traj, "mu_traj", n),
         _ptr_array(nu_traj, "nu_traj", n), _addr(pK, "pK", n=n), int(count0), float(lr), float(b1),
@@ -312,6 +344,10 @@ def adam_unrolled_bwd(dpK, grads, mu_traj, nu_traj, dgrads, dmu0, dnu0, count0, 
     n = dpK.numel()
     if len(dgrads) != K or len(mu_traj) < K or len(nu_traj) < K:
         raise ValueError("dgrads needs K entries, mu_traj/nu_traj at least K")
+    if _done(_native.adam_unrolled_bwd(
+            n, K, n, dpK, grads, mu_traj[:K], nu_traj[:K], dgrads, dmu0, dnu0, count0, lr, b1, b2, eps, eps_root,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_adam_unrolled_bwd(
         K, n, _addr(dpK, "dpK", n=n), _ptr_array(grads, "grads", n), _ptr_array(mu_traj[:K], "mu_traj", n),
         _ptr_array(nu_traj[:K], "nu_traj", n), _ptr_array(dgrads, "dgrads", n), _addr(dmu0, "dmu0", n=n),
@@ -342,6 +378,10 @@ def adam_fwd_tree(table: SegTable, params, grad, mu, nu, count, lr, b1, b2, eps,
                   params_out, mu_out, nu_out, stream=None) -> None:
     """diffopt_adam_fwd_tree."""
     k = len(table.numel)
+    if _done(_native.adam_fwd_tree(
+            k, table.handle, params, grad, mu, nu, count, lr, b1, b2, eps, eps_root,
+            params_out, mu_out, nu_out, _stream(stream))):
+        return
     _check(_lib.diffopt_adam_fwd_tree(
         table.handle, *[_leaf_array(x, w, k) for x, w in ((params, "params"), (grad, "grad"), (mu, "mu"),
                                                            (nu, "nu"))],
@@ -354,6 +394,10 @@ def adam_bwd_tree(table: SegTable, dupdate, dmu, dnu, grad, mu, nu, count, lr, b
                   dgrad, dmu_in, dnu_in, stream=None) -> None:
     """diffopt_adam_bwd_tree; dmu/dnu may be None."""
     k = len(table.numel)
+    if _done(_native.adam_bwd_tree(
+            k, table.handle, dupdate, dmu, dnu, grad, mu, nu, count, lr, b1, b2, eps, eps_root,
+            dgrad, dmu_in, dnu_in, _stream(stream))):
+        return
     _check(_lib.diffopt_adam_bwd_tree(
         table.handle, *[_leaf_array(x, w, k) for x, w in ((dupdate, "dupdate"), (dmu, "dmu"), (dnu, "dnu"),
                                                            (grad, "grad"), (mu, "mu"), (nu, "nu"))],
@@ -369,6 +413,10 @@ def adam_unrolled_fwd_tree(table: SegTable, p0, grads, mu_traj, nu_traj, pK, cou
     k = len(table.numel)
     if len(mu_traj) != K + 1 or len(nu_traj) != K + 1:
         raise ValueError("mu_traj and nu_traj need K+1 entries")
+    if _done(_native.adam_unrolled_fwd_tree(
+            k, table.handle, K, p0, grads, mu_traj, nu_traj, pK, count0, lr, b1, b2, eps, eps_root,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_adam_unrolled_fwd_tree(
         table.handle, K, _leaf_array(p0, "p0", k), _leaf_array_list(grads, "grads", k),
         _leaf_array_list(mu_traj, "mu_traj", k), _leaf_array_list(nu_traj, "nu_traj", k), _leaf_array(pK, "pK", k),
@@ -382,6 +430,10 @@ def adam_unrolled_bwd_tree(table: SegTable, dpK, grads, mu_traj, nu_traj, dgrads
     k = len(table.numel)
     if len(dgrads) != K or len(mu_traj) < K or len(nu_traj) < K:
         raise ValueError("dgrads needs K entries, mu_traj/nu_traj at least K")
+    if _done(_native.adam_unrolled_bwd_tree(
+            k, table.handle, K, dpK, grads, mu_traj[:K], nu_traj[:K], dgrads, dmu0, dnu0,
+            count0, lr, b1, b2, eps, eps_root, _stream(stream))):
+        return
     _check(_lib.diffopt_adam_unrolled_bwd_tree(
         table.handle, K, _leaf_array(dpK, "dpK", k), _leaf_array_list(grads, "grads", k),
         _leaf_array_list(mu_traj[:K], "mu_traj", k), _leaf_array_list(nu_traj[:K], "nu_traj", k),
@@ -397,6 +449,10 @@ def sgd_fwd(params, grad, trace, lr, momentum, nesterov, params_out, trace_out=N
     """diffopt_sgd_fwd; trace may be None (zero), trace_out is needed when momentum > 0."""
     if n is None:
         n = params.numel()
+    if _done(_native.sgd_fwd(
+            n, params, grad, trace, n, lr, momentum, int(bool(nesterov)), params_out, trace_out,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_sgd_fwd(_addr(params, "params", n=n), _addr(grad, "grad", n=n),
                                 _addr(trace, "trace", n=n), int(n), float(lr), float(momentum),
                                 int(bool(nesterov)), _addr(params_out, "params_out", n=n),
@@ -408,6 +464,10 @@ def sgd_bwd(dparams_out, dtrace_out, lr, momentum, nesterov, dgrad, dtrace_in=No
     """diffopt_sgd_bwd; dtrace_out may be None (zero)."""
     if n is None:
         n = dparams_out.numel()
+    if _done(_native.sgd_bwd(
+            n, dparams_out, dtrace_out, n, lr, momentum, int(bool(nesterov)), dgrad, dtrace_in,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_sgd_bwd(_addr(dparams_out, "dparams_out", n=n), _addr(dtrace_out, "dtrace_out", n=n),
                                 int(n), float(lr), float(momentum), int(bool(nesterov)),
                                 _addr(dgrad, "dgrad", n=n), _addr(dtrace_in, "dtrace_in", n=n), _stream(stream)))
@@ -418,6 +478,10 @@ def rmsprop_fwd(params, grad, nu, mom, lr, alpha, eps, eps_root, momentum, param
     """diffopt_rmsprop_fwd; mom may be None (zero), mom_out is needed when momentum > 0."""
     if n is None:
         n = params.numel()
+    if _done(_native.rmsprop_fwd(
+            n, params, grad, nu, mom, n, lr, alpha, eps, eps_root, momentum, params_out, nu_out, mom_out,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_rmsprop_fwd(_addr(params, "params", n=n), _addr(grad, "grad", n=n), _addr(nu, "nu", n=n),
                                     _addr(mom, "mom", n=n), int(n), float(lr), float(alpha), float(eps),
                                     float(eps_root), float(momentum), _addr(params_out, "params_out", n=n),
@@ -429,6 +493,10 @@ def rmsprop_bwd(dparams_out, dnu_out, dmom_out, grad, nu, lr, alpha, eps, eps_ro
     """diffopt_rmsprop_bwd; dnu_out / dmom_out may be None (zero)."""
     if n is None:
         n = dparams_out.numel()
+    if _done(_native.rmsprop_bwd(
+            n, dparams_out, dnu_out, dmom_out, grad, nu, n, lr, alpha, eps, eps_root, momentum, dgrad, dnu_in,
+            dmom_in, _stream(stream))):
+        return
     _check(_lib.diffopt_rmsprop_bwd(_addr(dparams_out, "dparams_out", n=n), _addr(dnu_out, "dnu_out", n=n),
                                     _addr(dmom_out, "dmom_out", n=n), _addr(grad, "grad", n=n),
                                     _addr(nu, "nu", n=n), int(n), float(lr), float(alpha), float(eps),
@@ -440,6 +508,10 @@ def sgd_fwd_tree(table: SegTable, params, grad, trace, lr, momentum, nesterov, p
                  stream=None) -> None:
     """diffopt_sgd_fwd_tree; every operand a device int64 array of leaf addresses (trace may be None)."""
     k = len(table.numel)
+    if _done(_native.sgd_fwd_tree(
+            k, table.handle, params, grad, trace, lr, momentum, int(bool(nesterov)), params_out, trace_out,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_sgd_fwd_tree(
         table.handle, _leaf_array(params, "params", k), _leaf_array(grad, "grad", k), _leaf_array(trace, "trace", k),
         float(lr), float(momentum), int(bool(nesterov)), _leaf_array(params_out, "params_out", k),
@@ -450,6 +522,10 @@ def sgd_bwd_tree(table: SegTable, dparams_out, dtrace_out, lr, momentum, nestero
                  stream=None) -> None:
     """diffopt_sgd_bwd_tree (dtrace_out may be None)."""
     k = len(table.numel)
+    if _done(_native.sgd_bwd_tree(
+            k, table.handle, dparams_out, dtrace_out, lr, momentum, int(bool(nesterov)), dgrad, dtrace_in,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_sgd_bwd_tree(
         table.handle, _leaf_array(dparams_out, "dparams_out", k), _leaf_array(dtrace_out, "dtrace_out", k),
         float(lr), float(momentum), int(bool(nesterov)), _leaf_array(dgrad, "dgrad", k),
@@ -460,6 +536,10 @@ def rmsprop_fwd_tree(table: SegTable, params, grad, nu, mom, lr, alpha, eps, eps
                      mom_out=None, stream=None) -> None:
     """diffopt_rmsprop_fwd_tree (mom may be None)."""
     k = len(table.numel)
+    if _done(_native.rmsprop_fwd_tree(
+            k, table.handle, params, grad, nu, mom, lr, alpha, eps, eps_root, momentum,
+            params_out, nu_out, mom_out, _stream(stream))):
+        return
     _check(_lib.diffopt_rmsprop_fwd_tree(
         table.handle, *[_leaf_array(x, w, k) for x, w in ((params, "params"), (grad, "grad"), (nu, "nu"),
                                                            (mom, "mom"))],
@@ -472,6 +552,10 @@ def rmsprop_bwd_tree(table: SegTable, dparams_out, dnu_out, dmom_out, grad, nu, 
                      dgrad, dnu_in, dmom_in=None, stream=None) -> None:
     """diffopt_rmsprop_bwd_tree (dnu_out / dmom_out may be None)."""
     k = len(table.numel)
+    if _done(_native.rmsprop_bwd_tree(
+            k, table.handle, dparams_out, dnu_out, dmom_out, grad, nu, lr, alpha, eps, eps_root, momentum,
+            dgrad, dnu_in, dmom_in, _stream(stream))):
+        return
     _check(_lib.diffopt_rmsprop_bwd_tree(
         table.handle, *[_leaf_array(x, w, k) for x, w in ((dparams_out, "dparams_out"), (dnu_out, "dnu_out"),
                                                            (dmom_out, "dmom_out"), (grad, "grad"), (nu, "nu"))],
@@ -489,6 +573,9 @@ def es_perturb(params, noise, sigma, antithetic, out, stream=None) -> None:
     N = noise.numel() // n if n else 0
     if noise.numel() != N * n or out.numel() != (2 if antithetic else 1) * N * n:
         raise ValueError("noise must be [N, n] and out [N or 2N, n]")
+    if _done(_native.es_perturb(
+            -1, params, noise, N, n, sigma, int(bool(antithetic)), out, _stream(stream))):
+        return
     _check(_lib.diffopt_es_perturb(_addr(params, "params"), _addr(noise, "noise"), int(N), int(n), float(sigma),
                                    int(bool(antithetic)), _addr(out, "out"), _stream(stream)))
 
@@ -499,6 +586,9 @@ def es_estimate(noise, weights, scale, grad, stream=None) -> None:
     N = weights.numel()
     if noise.numel() != N * n:
         raise ValueError("noise must be [N, n] with N = weights.numel(), n = grad.numel()")
+    if _done(_native.es_estimate(
+            -1, noise, weights, N, n, scale, grad, _stream(stream))):
+        return
     _check(_lib.diffopt_es_estimate(_addr(noise, "noise"), _addr(weights, "weights"), int(N), int(n), float(scale),
                                     _addr(grad, "grad"), _stream(stream)))
 
@@ -512,11 +602,19 @@ def _es_method(method) -> int:
     return ES_METHODS[method]
 
 
+def _one(x) -> bool:
+    return isinstance(x, torch.Tensor) and x.numel() == 1
+
+
 def es_perturb_gaussian(params, num_samples: int, seed: int, sigma, antithetic, out, stream=None) -> None:
     """diffopt_es_perturb_gaussian: out is [N, n] (or [2N, n] if antithetic); the noise is generated in the kernel."""
     n = params.numel()
     if out.numel() != (2 if antithetic else 1) * num_samples * n:
         raise ValueError("out must be [N or 2N, n]")
+    if _done(_native.es_perturb_gaussian(
+            -1, params, n, num_samples, int(seed) & ((1 << 64) - 1), sigma, int(bool(antithetic)), out,
+            _stream(stream))):
+        return
     _check(_lib.diffopt_es_perturb_gaussian(_addr(params, "params"), int(n), int(num_samples),
                                             int(seed) & ((1 << 64) - 1), float(sigma), int(bool(antithetic)),
                                             _addr(out, "out"), _stream(stream)))
@@ -530,6 +628,10 @@ def es_estimate_gaussian(fvals, method: str, num_samples: int, seed: int, sigma,
         raise ValueError("fvals must hold %s evaluations" % ("2N" if m == 2 else "N"))
     if m == 1 and f0 is None:
         raise ValueError("the baseline method needs f0 = f(theta)")
+    if (m != 1 or _one(f0)) and _done(_native.es_estimate_gaussian(
+            -1, fvals, f0 if m == 1 else None, num_samples, m, grad.numel(),
+            int(seed) & ((1 << 64) - 1), sigma, grad, _stream(stream))):
+        return
     _check(_lib.diffopt_es_estimate_gaussian(_addr(fvals, "fvals"), _addr(f0, "f0", n=1) if m == 1 else None,
                                              int(num_samples), m, int(grad.numel()), int(seed) & ((1 << 64) - 1),
                                              float(sigma), _addr(grad, "grad"), _stream(stream)))
@@ -542,5 +644,8 @@ def es_weights(fvals, method: str, num_samples: int, sigma, weights, f0=None, st
         raise ValueError("fvals must hold N (2N antithetic) evaluations and weights N entries")
     if m == 1 and f0 is None:
         raise ValueError("the baseline method needs f0 = f(theta)")
+    if (m != 1 or _one(f0)) and _done(_native.es_weights(
+            -1, fvals, f0 if m == 1 else None, num_samples, m, sigma, weights, _stream(stream))):
+        return
     _check(_lib.diffopt_es_weights(_addr(fvals, "fvals"), _addr(f0, "f0", n=1) if m == 1 else None,
                                    int(num_samples), m, float(sigma), _addr(weights, "weights"), _stream(stream)))

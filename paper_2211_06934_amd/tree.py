@@ -103,8 +103,13 @@ _TABLES: Dict[Tuple, _d.SegTable] = {}
 def segment_table(shapes: Sequence[Tuple[int, ...]], dtype: torch.dtype,
                   device: Optional[torch.device] = None) -> _d.SegTable:
     """Cached dense segment table for leaves of these shapes and dtype."""
+    return _table_of(tuple(tuple(int(d) for d in s) for s in shapes), dtype, device)
+
+
+def _table_of(shapes: Tuple[Tuple[int, ...], ...], dtype: torch.dtype, device) -> _d.SegTable:
+    """segment_table for shapes that are tuples of ints already."""
     dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
-    key = (tuple(tuple(int(d) for d in s) for s in shapes), dtype, dev.index)
+    key = (shapes, dtype, dev.index)
     t = _TABLES.get(key)
     if t is None:
         numel = [int(torch.Size(s).numel()) for s in shapes]
@@ -137,6 +142,12 @@ def leaf_pointer_tensors(groups: Sequence[Optional[Sequence[torch.Tensor]]], dev
     on the stream it was allocated on, so the arrays may be dropped as soon as
     the kernels are enqueued (the pinned staging block is likewise held until
     the copy has run)."""
+    dev = device if isinstance(device, torch.device) else torch.device(device)
+    if dev.type == "cuda":
+        with _stream_context(stream):
+            out = _d._native.leaf_pointers(groups, torch.cuda.current_device() if dev.index is None else dev.index)
+        if out is not None:
+            return out
     ptrs: List[int] = []
     for g in groups:
         if g is None:
@@ -148,7 +159,7 @@ def leaf_pointer_tensors(groups: Sequence[Optional[Sequence[torch.Tensor]]], dev
     with _stream_context(stream):
         host = torch.tensor(ptrs, dtype=torch.int64).pin_memory()
         dev = host.to(device, non_blocking=True)
-    out: List[Optional[torch.Tensor]] = []
+    out = []
     o = 0
     for g in groups:
         if g is None:
@@ -172,11 +183,13 @@ def flatten(tree, out: Optional[torch.Tensor] = None, stream=None) -> Tuple[torc
         raise ValueError("tree has no tensor leaves")
     dtype = leaves[0].dtype
     device = leaves[0].device
-    for x in leaves:
-        if x.dtype != dtype or x.device != device:
-            raise ValueError("all leaves must share dtype and device")
-    shapes = tuple(tuple(x.shape) for x in leaves)
-    table = segment_table(shapes, dtype, device)
+    shapes = _d._native.leaf_shapes(leaves)
+    if shapes is None:
+        for x in leaves:
+            if x.dtype != dtype or x.device != device:
+                raise ValueError("all leaves must share dtype and device")
+        shapes = tuple(tuple(x.shape) for x in leaves)
+    table = _table_of(shapes, dtype, device)
     if out is None:
         out = torch.empty(table.total, dtype=dtype, device=device)
     elif out.numel() < table.total or out.dtype != dtype:

@@ -1,0 +1,77 @@
+"""The native half of the Python binding takes and refuses what the Python
+path does, with the same results and messages: every kind of operand it hands
+back (views, subclasses, raw addresses, other number types) and every check."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+H = (3, 1e-3, 0.9, 0.999, 1e-8, 0.0)
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def _operands(n=100):
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    return [torch.empty(n, device="cuda").normal_(generator=gen).abs_() for _ in range(4)], [torch.zeros(n, device="cuda") for _ in range(3)]
+
+
+def test_operand_kinds_agree():
+    import paper_2211_06934_amd as P
+    x, ref = _operands()
+    P.adam_fwd(*x, *H, *ref)
+    kinds = {
+        "parameter": [torch.nn.Parameter(t) for t in x],
+        "subclass": [t.as_subclass(_Sub) for t in x],
+        "address": [t.data_ptr() for t in x],
+        "view": [t.view(10, 10) for t in x],
+    }
+    for name, ops in kinds.items():
+        out = [torch.zeros(100, device="cuda") for _ in range(3)]
+        P.adam_fwd(*ops, *H, *out, n=100)
+        assert all(torch.equal(a, b) for a, b in zip(out, ref)), name
+    out = [torch.zeros(100, device="cuda") for _ in range(3)]
+    P.adam_fwd(*x, np.int64(3), np.float64(1e-3), np.float32(0.9).item(), 0.999, 1e-8, 0, *out)  # other number types
+    P.adam_fwd(*x, *H, *out, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, ref))
+
+
+@pytest.mark.parametrize("bad,error", [
+    (lambda t: t.double(), ValueError), (lambda t: t[:99], ValueError), (lambda t: t.cpu(), ValueError),
+    (lambda t: torch.zeros(200, device="cuda")[::2], ValueError), (lambda t: "x", TypeError), (lambda t: None, RuntimeError)])
+def test_refused_operands(bad, error):
+    import paper_2211_06934_amd as P
+    x, out = _operands()
+    for k in range(7):
+        ops = [*x, *out]
+        ops[k] = bad(ops[k])
+        with pytest.raises(error):
+            P.adam_fwd(*ops[:4], *H, *ops[4:], n=100)
+    table = P.segtable_create([40, 60])
+    ptr = torch.tensor([x[0].data_ptr(), x[0].data_ptr() + 160], device="cuda")
+    with pytest.raises(ValueError):
+        P.adam_fwd_tree(table, ptr, ptr, ptr, ptr[:1], *H, ptr, ptr, ptr)
+    with pytest.raises(P.DiffoptError, match="b1 must be in"):
+        P.adam_fwd(*x, 0, 1e-3, 1.0, 0.999, 1e-8, 0.0, *out)
+
+
+def test_leaf_pointers_and_flatten_of_any_leaves():
+    import paper_2211_06934_amd as P
+    a, b = torch.arange(6.0, device="cuda").view(2, 3), torch.nn.Parameter(torch.ones((), device="cuda"))
+    groups = ([a, b], None, (b, a))
+    got = P.tree.leaf_pointer_tensors(groups, a.device)
+    assert got[1] is None and got[0].tolist() == [a.data_ptr(), b.data_ptr()] and got[2].tolist() == [b.data_ptr(), a.data_ptr()]
+    sub = P.tree.leaf_pointer_tensors(([a.as_subclass(_Sub), b],), "cuda")
+    assert sub[0].tolist() == [a.data_ptr(), b.data_ptr()]
+    with pytest.raises(ValueError, match="leaf 0 is not contiguous"):
+        P.tree.leaf_pointer_tensors(([a.t()],), a.device)
+    for first in (a, a.as_subclass(_Sub)):
+        flat, spec = P.tree.flatten({"w": first, "v": [b, a]})
+        assert torch.equal(flat, torch.cat([b.detach().view(1), a.view(-1), a.view(-1)]))
+        assert spec.shapes == ((), (2, 3), (2, 3))
+    with pytest.raises(ValueError, match="share dtype and device"):
+        P.tree.flatten({"a": a, "b": a.double()})
