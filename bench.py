@@ -68,7 +68,8 @@ B_BWD_ZERO_MV = 28  # dP, g, m, v -> dg, dm, dv (zero moment cotangents)
 B_BWD_FIRST = 28    # dM = dV = 0: dP, g, m, v -> dg, dm, dv
 B_COPY = 8          # pack / unpack: read once, write once
 UNROLL_CHUNK = 16   # steps per launch of the fused K-step driver
-TREE_UNROLL_CHUNK = 8  # the same for its leaf-direct form
+TREE_FWD_CHUNK = 16  # the same for its leaf-direct form, forward
+TREE_BWD_CHUNK = 8   # and VJP
 
 
 REMAT_SPAN = 8      # longest run of steps whose moments the backward recomputes
@@ -409,8 +410,8 @@ def step_treemap(P, S, ev=None):
 
 def phases_treemap(S):
     K, n = S["K"], S["n"]
-    fl, fb = fwd_plan(K, S["stored"], TREE_UNROLL_CHUNK)
-    bl, bb = bwd_plan(K, S["stored"], TREE_UNROLL_CHUNK)
+    fl, fb = fwd_plan(K, S["stored"], TREE_FWD_CHUNK)
+    bl, bb = bwd_plan(K, S["stored"], TREE_BWD_CHUNK)
     return [("adam_fwd_tree", "adam_unrolled_fwd_tree", fl, fb * n),
             ("adam_bwd_tree", "adam_unrolled_bwd_tree", bl, bb * n)]
 

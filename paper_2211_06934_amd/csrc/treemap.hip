@@ -354,16 +354,23 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
 // of every operand tree of every step in dynamic LDS (NA x kWindowMax x 8
 // bytes: 18.5 KiB for the backward at 8 steps).  One group per lane, one
 // table tile (512 groups) per workgroup.
-constexpr int kTK = 8;  // steps per fused launch
+constexpr int kTK = 8;  // steps per fused launch, VJP and small trees
+// Steps per launch of the tiled forward: a boundary between launches sends
+// the running params and moments through memory, 24 bytes per element (32 if
+// the state there is not stored): 62 leaves, 1.2e7 elements, K = 10 (state 5
+// stored) 96 -> 72 bytes per element, its forward 192 -> 143 us.
+constexpr int kTLongK = 16;
 constexpr int kUTB = (int)kTileGroups;
-constexpr int kTFwdNA = 4 + 3 * kTK;  // 0 p, 1 mu0, 2 nu0, 3 pK; per step s: 4+3s g, 5+3s mu_s+1, 6+3s nu_s+1
 constexpr int kTBwdNA = 3 + 4 * kTK;  // 0 dP, 1 dmu, 2 dnu; per step s: 3+4s g, 4+4s mu, 5+4s nu, 6+4s dg
 
-struct TFwdArgs {
-  const uint64_t* a[kTFwdNA];
-  AdamCoef c[kTK];
+// Operands 0 p, 1 mu0, 2 nu0, 3 pK; per step s: 4+3s g, 5+3s mu_s+1, 6+3s nu_s+1.
+template <int CAP>
+struct TFwdArgsOf {
+  const uint64_t* a[4 + 3 * CAP];
+  AdamCoef c[CAP];
   int32_t K;
 };
+using TFwdArgs = TFwdArgsOf<kTK>;
 
 // Execution order is reverse step order, as in the flat fused backward.
 struct TBwdArgs {
@@ -397,10 +404,11 @@ __device__ __forceinline__ int stage_window_n(const SegEntry* __restrict__ seg, 
   return W;
 }
 
-template <bool KEEP>
+template <bool KEEP, int CAP>
 __global__ __launch_bounds__(kUTB) void adam_unrolled_fwd_tree_kernel(const SegEntry* __restrict__ seg,
                                                                      const int64_t* __restrict__ tile_first,
-                                                                     int64_t ngroups, int dense_orig, TFwdArgs a) {
+                                                                     int64_t ngroups, int dense_orig,
+                                                                     TFwdArgsOf<CAP> a) {
   __shared__ int64_t s_goff[kWindowMax + 1];
   __shared__ int64_t s_numel[kWindowMax];
   extern __shared__ uint64_t s_ptr[];  // [na][kWindowMax]
@@ -852,6 +860,19 @@ constexpr size_t kBwdTreeLdsPad = kLdsPerCU / kBwdTreeResident - kBwdTreeStaticL
 static_assert(kLdsPerCU / (kBwdTreeStaticLds + kBwdTreeLdsPad) == kBwdTreeResident,
               "the reserved LDS must leave room for exactly kBwdTreeResident workgroups");
 
+template <int CAP>
+void launch_unrolled_fwd_tree(const diffopt_segtable* t, const TFwdArgsOf<CAP>& a, hipStream_t st) {
+  const size_t lds = sizeof(uint64_t) * kWindowMax * (4 + 3 * a.K);
+  int64_t values = 4 + a.K;  // moved per element
+  for (int s = 0; s < a.K; ++s) values += a.a[5 + 3 * s] ? 2 : 0;
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)t->ntiles), dim3(kUTB), lds, st, t->d_seg, t->d_tile_first, t->ngroups,
+                       t->dense_orig, a);
+  };
+  if (keep_run_in_cache(4 * values * t->elems)) go(adam_unrolled_fwd_tree_kernel<true, CAP>);
+  else go(adam_unrolled_fwd_tree_kernel<false, CAP>);
+}
+
 int launch_bwd_tree(const diffopt_segtable* t, const LeafArrays<9>& arr, const AdamCoef& c, hipStream_t st) {
   if (t->ntiles == 0) return DIFFOPT_OK;
   const auto go = [&](auto kernel) {
@@ -962,11 +983,11 @@ extern "C" int diffopt_adam_unrolled_fwd_tree(const diffopt_segtable* table, int
   rc = check_trajectory(who, K, mu_traj, nu_traj, true, false);
   if (rc) return rc;
   hipStream_t st = as_stream(stream);
-  for (int64_t k0 = 0; k0 < K; k0 += kTK) {  // one fused launch per kTK steps
-    TFwdArgs a{};
-    a.K = (int32_t)(K - k0 < kTK ? K - k0 : kTK);
-    // between launches the running moments pass through the state stored at
-    // the boundary, or through the final-state trees when it is not stored
+  // Steps k0+1..k0+steps in one launch.  Between launches the running moments
+  // pass through the state stored at the boundary, or through the final-state
+  // trees when it is not stored.
+  const auto fill = [&](auto& a, int64_t k0, int64_t steps) {
+    a.K = (int32_t)steps;
     a.a[0] = (k0 == 0) ? p0 : pK;
     a.a[1] = mu_traj[k0] ? mu_traj[k0] : mu_traj[K];
     a.a[2] = nu_traj[k0] ? nu_traj[k0] : nu_traj[K];
@@ -981,18 +1002,22 @@ extern "C" int diffopt_adam_unrolled_fwd_tree(const diffopt_segtable* table, int
       a.a[5 + 3 * (a.K - 1)] = mu_traj[K];
       a.a[6 + 3 * (a.K - 1)] = nu_traj[K];
     }
+  };
+  const int64_t chunk = table->tiny ? kTK : kTLongK;
+  for (int64_t k0 = 0; k0 < K; k0 += chunk) {
+    const int64_t steps = K - k0 < chunk ? K - k0 : chunk;
     if (table->tiny) {
+      TFwdArgs a{};
+      fill(a, k0, steps);
       launch_tiny_fwd_k(table, a, st);
+    } else if (steps <= kTK) {
+      TFwdArgs a{};
+      fill(a, k0, steps);
+      launch_unrolled_fwd_tree(table, a, st);
     } else {
-      const size_t lds = sizeof(uint64_t) * kWindowMax * (4 + 3 * a.K);
-      int64_t values = 4 + a.K;  // moved per element
-      for (int s = 0; s < a.K; ++s) values += a.a[5 + 3 * s] ? 2 : 0;
-      const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)table->ntiles), dim3(kUTB), lds, st, table->d_seg,
-                           table->d_tile_first, table->ngroups, table->dense_orig, a);
-      };
-      if (keep_run_in_cache(4 * values * table->elems)) go(adam_unrolled_fwd_tree_kernel<true>);
-      else go(adam_unrolled_fwd_tree_kernel<false>);
+      TFwdArgsOf<kTLongK> a{};
+      fill(a, k0, steps);
+      launch_unrolled_fwd_tree(table, a, st);
     }
     rc = launch_status(who);
     if (rc) return rc;

@@ -182,3 +182,25 @@ def test_fused_tree_recomputed_many_small_full_size():
                        ("dmu0", got[4], ref[4]), ("dnu0", got[5], ref[5])] + \
             [("dg_%d" % (k + 1), got[3][k], ref[3][k]) for k in range(K)]:
         _same(a, b, what)
+
+
+@pytest.mark.parametrize("K,keep", [
+    (10, (5,)), (9, (4,)), (16, (8,)), (15, (7,)),  # two recomputed runs in one launch, equal and unequal
+    (18, (6, 12)), (24, (8, 16)),                   # three: two and one; a forward launch boundary on a stored state
+    (20, (1, 2, 9, 17)), (32, (7, 14, 21, 28)),     # runs around stored steps, the boundary at step 16 unstored
+])
+@pytest.mark.parametrize("mode", ["separate", "packed-views"])
+def test_long_fused_tree_equals_stepwise_bitwise(K, keep, mode):
+    import paper_2211_06934_amd as P
+    numel = _numel(K + 2)
+    table = P.segtable_create(numel)
+    got = _run(P, table, numel, K, 1, 1e-8, mode, False, True, 5, keep=set(keep))
+    ref = _run(P, table, numel, K, 1, 1e-8, mode, False, False, 5)
+    _same(got["pK"], ref["pK"], "p_K")
+    for k in range(K):
+        if got["mu"][k] is not None:
+            _same(got["mu"][k], ref["mu"][k], "mu_%d" % (k + 1))
+            _same(got["nu"][k], ref["nu"][k], "nu_%d" % (k + 1))
+        _same(got["dg"][k], ref["dg"][k], "dg_%d" % (k + 1))
+    _same(got["dm0"], ref["dm0"], "dmu0")
+    _same(got["dv0"], ref["dv0"], "dnu0")
