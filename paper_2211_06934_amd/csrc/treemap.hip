@@ -102,18 +102,20 @@ __device__ __forceinline__ int64_t line_phase(uint64_t leaf) { return (int64_t)(
 // How a group's elements [e0, e0 + 4) within [0, nel) are moved.  A group whose
 // four elements exist takes 128-bit accesses.  For the groups at the ends of a
 // leaf there are two ways:
-// - calls served by the Infinity Cache (KEEP) move a window of four
-//   consecutive elements of the leaf there too: at the ends it lies inside the
-//   leaf, so it holds elements of the neighbouring group as well (whose lane
-//   may be overwriting them, where an output leaf is its input leaf); they are
-//   computed and not stored.  A wave then makes one pass whatever its lanes
-//   hold (2,000 leaves of up to 2,000 elements, Adam forward and VJP: 14.9 us
-//   against 15.4 with a pass element by element; 20,000 leaves of up to 50, 19.7
-//   against 21.9).  Leaves of fewer than four elements move theirs together
-//   too, one by one (Few).
-// - calls that stream from memory go element by element: there a wave whose
-//   lanes are not 16 bytes apart costs more than the extra pass (20,000 leaves
-//   of up to 65,536: forward 586 us with windows, 555 without).
+// - windows: four consecutive elements of the leaf there too, at the ends
+//   inside the leaf, so that they hold elements of the neighbouring group as
+//   well (whose lane may be overwriting them, where an output leaf is its
+//   input leaf); those are computed and not stored.  A wave then makes one
+//   pass whatever its lanes hold.  Leaves of fewer than four elements move
+//   theirs together too, one by one (Few).
+// - element by element, a pass each.
+// The K-step kernels, whose passes are long, and the single steps served by
+// the Infinity Cache (KEEP) take windows (K = 8, 5,000 leaves of up to 20,000
+// elements: 292 us against 308 element by element; K = 10 on 576 packed leaves
+// 144 against 165; one Adam step, 20,000 leaves of up to 50: 19.7 against 21.9).
+// Single steps that stream from memory go element by element: there a wave
+// whose lanes are not 16 bytes apart costs more than the extra pass (20,000
+// leaves of up to 65,536: forward 586 us with windows, 555 without).
 struct Whole {
   int64_t e0;
   __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
@@ -140,16 +142,17 @@ struct One {
   }
 };
 
-struct Window {
+template <bool KEEP>
+struct WindowOf {
   int64_t w;  // first element of the window
   int own;    // bit e: element w + e belongs to this group
-  __device__ __forceinline__ Window(int64_t e0, int64_t nel) {
+  __device__ __forceinline__ WindowOf(int64_t e0, int64_t nel) {
     w = e0 < 0 ? 0 : (e0 + 4 <= nel ? e0 : nel - 4);
     const int d = (int)(e0 - w);  // -3..3
     own = d < 0 ? 15 >> -d : (15 << d) & 15;
   }
   __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
-    return ld<true>((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, w));
+    return ld<KEEP>((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, w));
   }
   template <int N>
   __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
@@ -165,6 +168,8 @@ struct Window {
     }
   }
 };
+
+using Window = WindowOf<true>;
 
 // The elements of a leaf of one to three; a slot without an element takes the
 // group's last one, and computes and stores its value once more.
@@ -209,11 +214,11 @@ __device__ __forceinline__ void other_elements(int64_t e0, int64_t nel, const Bo
 }
 
 // Run a kernel's per-group code on the group's elements, if it has any.
-template <bool KEEP, class Body>
+template <bool KEEP, bool WINDOWS = KEEP, class Body>
 __device__ __forceinline__ void on_group(int64_t e0, int64_t nel, const Body& body) {
   if (e0 + 4 <= 0 || e0 >= nel) return;
-  if constexpr (KEEP) {
-    if (nel >= 4) body(Window(e0, nel));
+  if constexpr (WINDOWS) {
+    if (nel >= 4) body(WindowOf<KEEP>(e0, nel));
     else other_elements<true>(e0, nel, body);
   } else {
     if (e0 >= 0 && e0 + 4 <= nel) body(Whole{e0});
@@ -420,7 +425,7 @@ __global__ __launch_bounds__(kUTB) void adam_unrolled_fwd_tree_kernel(const SegE
   const int t = find_leaf(s_goff, W, gidx);
   const uint64_t* P = s_ptr + t;  // P[q * kWindowMax]: leaf address in operand q
 #define OP(q) P[(q) * kWindowMax]
-  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(3)), s_numel[t], [&](const auto& x) {
+  on_group<KEEP, true>(4 * (gidx - s_goff[t]) - line_phase(OP(3)), s_numel[t], [&](const auto& x) {
     f32x4 p = x.load(OP(0)), m = x.load(OP(1)), v = x.load(OP(2));
     f32x4 g = x.load(OP(4));
     for (int s = 0; s < a.K; ++s) {
@@ -452,7 +457,7 @@ __global__ __launch_bounds__(kUTB) void adam_unrolled_bwd_tree_kernel(const SegE
   const int t = find_leaf(s_goff, W, gidx);
   const uint64_t* P = s_ptr + t;
 #define OP(q) P[(q) * kWindowMax]
-  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
+  on_group<KEEP, true>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
     const f32x4 dP = x.load(OP(0));
     f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 g = x.load(OP(3)), m = x.load(OP(4)), v = x.load(OP(5));
@@ -522,7 +527,7 @@ __global__ __launch_bounds__(kTRB) void adam_unrolled_bwd_tree_remat_kernel(cons
   const int t = find_leaf(s_goff, W, gidx);
   const uint64_t* P = s_ptr + t;
 #define OP(q) P[(q) * kWindowMax]
-  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
+  on_group<KEEP, true>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
     const f32x4 dP = x.load(OP(0));
     f32x4 M[C], V[C], G[C];  // M[s], V[s]: the moments step s consumed
     M[0] = x.load(OP(3));
@@ -552,6 +557,135 @@ __global__ __launch_bounds__(kTRB) void adam_unrolled_bwd_tree_remat_kernel(cons
   });
 #undef OP
 }
+
+// Two such runs in one launch, the later steps first: the running dM, dV stay
+// in registers between them, which saves their round trip and a second read
+// of dP (20 bytes per element; 62 leaves, 1.2e7 elements, K = 10 in two runs of
+// five: 128 -> 108 bytes, its
+// VJP 263 -> 231 us).  C is the longer run's length; run r has
+// len[r] <= C steps, and its operands start at 3 + r (2 + 2C): 0 mu_j, 1 nu_j;
+// per step s: 2+2s g, 3+2s dg.
+template <int C>
+struct TRBwd2Args {
+  const uint64_t* a[3 + 2 * (2 + 2 * C)];  // 0 dP, 1 dmu, 2 dnu
+  AdamCoef c[2][C];
+  int32_t len[2];
+  int32_t init_mv;
+};
+
+template <int C>
+__global__ __launch_bounds__(kTRB) void adam_unrolled_bwd_tree_remat2_kernel(const SegEntry* __restrict__ seg,
+                                                                            const int64_t* __restrict__ tile_first,
+                                                                            int64_t ngroups, int dense_orig,
+                                                                            TRBwd2Args<C> a) {
+  __shared__ int64_t s_goff[kWindowMax + 1];
+  __shared__ int64_t s_numel[kWindowMax];
+  extern __shared__ uint64_t s_ptr[];  // [na][kWindowMax]
+  constexpr int na = 3 + 2 * (2 + 2 * C);
+  const int64_t b = blockIdx.x / kTRSplit;  // table tile
+  const int W = stage_window_n<kTRB>(seg, tile_first, a.a, na, dense_orig, b, s_goff, s_numel, s_ptr);
+  const int64_t gidx = b * kTileGroups + (int64_t)(blockIdx.x % kTRSplit) * kTRB + threadIdx.x;
+  if (gidx >= ngroups) return;
+  const int t = find_leaf(s_goff, W, gidx);
+  const uint64_t* P = s_ptr + t;
+#define OP(q) P[(q) * kWindowMax]
+  on_group<false, true>(4 * (gidx - s_goff[t]) - line_phase(OP(1)), s_numel[t], [&](const auto& x) {
+    const f32x4 dP = x.load(OP(0));
+    f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.init_mv) {
+      dM = x.load(OP(1));
+      dV = x.load(OP(2));
+    }
+#pragma unroll 1
+    for (int r = 0; r < 2; ++r) {
+      const int len = a.len[r], o = 3 + r * (2 + 2 * C);
+      f32x4 M[C], V[C], G[C];  // M[s], V[s]: the moments step s consumed
+      M[0] = x.load(OP(o));
+      V[0] = x.load(OP(o + 1));
+#pragma unroll
+      for (int s = 0; s < C; ++s)
+        if (s < len) G[s] = x.load(OP(o + 2 + 2 * s));
+#pragma unroll
+      for (int s = 0; s + 1 < C; ++s) {
+        if (s + 1 < len) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            M[s + 1][e] = moment1(G[s][e], M[s][e], a.c[r][s]);
+            V[s + 1][e] = moment2(G[s][e], V[s][e], a.c[r][s]);
+          }
+        }
+      }
+#pragma unroll
+      for (int s = C - 1; s >= 0; --s) {
+        if (s < len) {
+          const bool last = r == 0 && s == len - 1 && !a.init_mv;  // the last unrolled step
+          const f32x4 rg = last ? bwd_group<false>(dP, dM, dV, G[s], M[s], V[s], a.c[r][s])
+                                : bwd_group<true>(dP, dM, dV, G[s], M[s], V[s], a.c[r][s]);
+          x.template store<1>({OP(o + 3 + 2 * s)}, {rg});
+        }
+      }
+    }
+    x.template store<2>({OP(1), OP(2)}, {dM, dV});
+  });
+#undef OP
+}
+
+// Fills and launches the two-run VJP: run r covers unrolled steps
+// start[r] + 1 .. start[r] + len[r], start[0] = start[1] + len[1].
+struct TwoRuns {
+  const char* who;
+  const diffopt_segtable* t;
+  hipStream_t st;
+  const uint64_t *dpK, *dmu0, *dnu0;
+  const uint64_t* const* grads;
+  const uint64_t* const* mu_traj;
+  const uint64_t* const* nu_traj;
+  const uint64_t* const* dgrads;
+  int64_t count0;
+  double lr, b1, b2, eps, eps_root;
+  int64_t start[2];
+  int len[2];
+  int32_t init_mv;
+
+  template <int C>
+  void launch() const {
+    TRBwd2Args<C> a{};
+    a.a[0] = dpK;
+    a.a[1] = dmu0;
+    a.a[2] = dnu0;
+    a.init_mv = init_mv;
+    for (int r = 0; r < 2; ++r) {
+      const uint64_t** op = a.a + 3 + r * (2 + 2 * C);
+      a.len[r] = len[r];
+      op[0] = mu_traj[start[r]];
+      op[1] = nu_traj[start[r]];
+      for (int s = 0; s < len[r]; ++s) {
+        op[2 + 2 * s] = grads[start[r] + s];
+        op[3 + 2 * s] = dgrads[start[r] + s];
+        make_coef(who, count0 + start[r] + s, lr, b1, b2, eps, eps_root, &a.c[r][s]);
+      }
+    }
+    const size_t lds = sizeof(uint64_t) * kWindowMax * (3 + 2 * (2 + 2 * C));
+    hipLaunchKernelGGL(adam_unrolled_bwd_tree_remat2_kernel<C>, dim3((unsigned)(t->ntiles * kTRSplit)), dim3(kTRB),
+                       lds, st, t->d_seg, t->d_tile_first, t->ngroups, t->dense_orig, a);
+  }
+
+  void run() const {  // a recomputed run has at least 2 steps
+    switch (len[0] > len[1] ? len[0] : len[1]) {
+      case 2: launch<2>(); break;
+      case 3: launch<3>(); break;
+      case 4: launch<4>(); break;
+      case 5: launch<5>(); break;
+      default: launch<6>(); break;
+    }
+  }
+};
+// Longer runs keep a launch of their own: with 7 or 8 steps the compiler puts
+// the two-run kernel's arguments into scratch memory.  So do runs whose launches
+// fit the Infinity Cache, where the round trip costs little and the second
+// run's loads wait for the first (20,000 leaves of up to 50, K = 10: 83.8 us
+// with two launches, 87.7 with one).
+constexpr int64_t kTwoRunSteps = 6;
 
 template <int C>
 void launch_trbwd(const diffopt_segtable* t, const TRBwdArgs& a, hipStream_t st) {
@@ -1121,6 +1255,18 @@ extern "C" int diffopt_adam_unrolled_bwd_tree(const diffopt_segtable* table, int
         rc = launch_tiny_bwd_c(who, C, table, a, st);
         if (rc) return rc;
         khi = j;
+        rc = launch_status(who);
+        if (rc) return rc;
+        continue;
+      }
+      int64_t i = j;  // start of the run before it, if that is recomputed too: both in one launch
+      if (j >= 1 && !mu_traj[j - 1])
+        while (i == j || !mu_traj[i]) --i;
+      if (i < j && C <= kTwoRunSteps && j - i <= kTwoRunSteps &&
+          !keep_run_in_cache((20 + 8 * C + (init_mv ? 8 : 0)) * table->elems)) {
+        TwoRuns{who, table, st, dpK, dmu0, dnu0, grads, mu_traj, nu_traj, dgrads, count0, lr, b1, b2, eps, eps_root,
+                {j, i}, {C, (int)(j - i)}, init_mv}.run();
+        khi = i;
         rc = launch_status(who);
         if (rc) return rc;
         continue;
