@@ -167,7 +167,7 @@ __global__ __launch_bounds__(B) void adam_fwd_vec(const float* p, const float* g
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(n, head, e)) {
+    if (edge_element<B>(n, head, e)) {
       const FwdOut o = fwd_elem(p[e], g[e], m[e], v[e], c);
       po[e] = o.p;
       mo[e] = o.m;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(B) void adam_bwd_vec(const float* dP, const float* 
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(n, head, e)) {
+    if (edge_element<B>(n, head, e)) {
       const BwdOut o = bwd_elem<HAS_MV>(dP[e], HAS_MV ? dM[e] : 0.0f, HAS_MV ? dV[e] : 0.0f, g[e], m[e], v[e], c);
       dgo[e] = o.g;
       dmo[e] = o.m;
@@ -234,7 +234,6 @@ constexpr int kUFB = DIFFOPT_UFWD_BLOCK;
 constexpr int kUBB = DIFFOPT_UBWD_BLOCK;
 constexpr int kSmallB = DIFFOPT_SMALL_BLOCK;
 constexpr int64_t kSmallVecs = DIFFOPT_SMALL_VECS;
-static_assert(kSmallB >= 64 && kSmallB % 64 == 0, "whole wavefronts; the tail needs 4 lanes");
 
 // Step s of a launch is the launch's s-th step in execution order.
 struct UFwdArgs {
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(B) void adam_unrolled_fwd_vec(UFwdArgs a) {
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(a.n, a.head, e)) ufwd_element(e, a);
+    if (edge_element<B>(a.n, a.head, e)) ufwd_element(e, a);
   }
 }
 
@@ -407,7 +406,7 @@ __global__ __launch_bounds__(B) void adam_unrolled_bwd_vec(UBwdArgs a) {
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(a.n, a.head, e)) ubwd_element(e, a);
+    if (edge_element<B>(a.n, a.head, e)) ubwd_element(e, a);
   }
 }
 
@@ -665,7 +664,7 @@ __global__ __launch_bounds__(B) void adam_unrolled_bwd_remat_vec(URBwdArgs a) {
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(a.n, a.head, e)) urbwd_element<C>(e, a);
+    if (edge_element<B>(a.n, a.head, e)) urbwd_element<C>(e, a);
   }
 }
 

@@ -145,15 +145,18 @@ __device__ __forceinline__ void st(__attribute__((address_space(1))) T* p, T v) 
 // 700 us at n = 1.17e8 (aligned: 542 and 697), 62.2 -> 54.9 and 81.2 -> 70.8 us
 // at n = 1.17e7; arrays in different phases 588 -> 571 and 768 -> 737 us.
 constexpr int kHeadLane = 64;  // first lane of the head's elements; tail lanes are below
+constexpr int kMaxHead = 31;   // elements of a head, at most
 
 inline int64_t line_head(const void* out, int64_t n) {
   const int64_t h = (int64_t)((0 - reinterpret_cast<uintptr_t>(out)) & 127u) / 4;
   return h < n ? h : n;
 }
 
-// The element lane t of the last workgroup moves, if any; n counts from the
-// advanced pointers.
+// The element lane t of the last workgroup (of B threads) moves, if any; n
+// counts from the advanced pointers.
+template <int B>
 __device__ __forceinline__ bool edge_element(int64_t n, int64_t head, int64_t& e) {
+  static_assert(B >= kHeadLane + kMaxHead && B % 64 == 0, "whole wavefronts, with a lane for every element of the head");
   const int t = (int)threadIdx.x;
   e = t < kHeadLane ? (n & ~int64_t(3)) + t : (int64_t)(t - kHeadLane) - head;
   return t < kHeadLane ? e < n : e < 0;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(B) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int64_
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
-    if (edge_element(n, head, e)) {
+    if (edge_element<B>(n, head, e)) {
       float xi[Op::NIN], yo[Op::NOUT];
 #pragma unroll
       for (int a = 0; a < Op::NIN; ++a) xi[a] = s.in[a][e];
