@@ -31,8 +31,10 @@ const at::Tensor& tensor_of(PyObject* o) {
   return THPVariable_Unpack(o);
 }
 
-// Address of a contiguous device tensor of this type with n elements (any
-// number if n < 0); None is the null pointer, an int an address.
+constexpr int64_t kAnyCount = -1;  // an operand of any number of elements
+
+// Address of a contiguous device tensor of this type with n elements; None is
+// the null pointer, an int an address.
 void* address(PyObject* o, at::ScalarType type, int64_t n) {
   if (o == Py_None) return nullptr;
   if (PyLong_CheckExact(o)) {
@@ -44,7 +46,7 @@ void* address(PyObject* o, at::ScalarType type, int64_t n) {
     return p;
   }
   const at::Tensor& t = tensor_of(o);
-  if (!t.is_cuda() || t.scalar_type() != type || !t.is_contiguous() || (n >= 0 && t.numel() != n)) throw Other{};
+  if (!t.is_cuda() || t.scalar_type() != type || !t.is_contiguous() || (n != kAnyCount && t.numel() != n)) throw Other{};
   return t.data_ptr();
 }
 
@@ -98,7 +100,7 @@ struct HandleArg {
   static T get(Slot& s) { return static_cast<T>(s.p); }
   static void set(Slot& s, PyObject* o, int64_t) {
     if (o != Py_None && !PyLong_CheckExact(o)) throw Other{};
-    s.p = address(o, at::kLong, -1);
+    s.p = address(o, at::kLong, kAnyCount);
   }
 };
 template <>
@@ -161,8 +163,9 @@ PyObject* call(int (*fn)(A...), PyObject* const* args, Py_ssize_t nargs) {
   }
   try {
     Slot count;
-    Arg<int64_t>::set(count, args[0], 0);
-    const int64_t n = count.i;
+    if (args[0] != Py_None) Arg<int64_t>::set(count, args[0], 0);
+    if (count.i < 0) throw Other{};  // no tensor has that many elements
+    const int64_t n = args[0] == Py_None ? kAnyCount : count.i;
     Slot slots[sizeof...(A)];
     return PyLong_FromLong(invoke(fn, slots, args + 1, n, std::index_sequence_for<A...>{}));
   } catch (...) {  // an argument of another kind, or a tensor without storage
@@ -172,7 +175,7 @@ PyObject* call(int (*fn)(A...), PyObject* const* args, Py_ssize_t nargs) {
 }
 
 // (n, then the C arguments) -> return code, or None: n is the element count
-// that every tensor operand must have (-1: any).
+// that every tensor operand must have (None: any).
 template <auto FN>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   return call(FN, args, nargs);

@@ -85,7 +85,7 @@ def _load_library():
 _lib = _load_library()
 LIBRARY_PATH = _LIB_PATH
 
-# The native half of this module (csrc/binding.cpp): _native.<entry>(n, C
+# The native half of this module (csrc/binding.cpp): _native.<entry>(n or None, C
 # arguments...) checks the operands, takes their addresses and calls
 # diffopt_<entry>, or returns None for operands it does not take (raw
 # subclasses, wrong sizes, ...), which the code after it here then accepts or
@@ -574,7 +574,7 @@ def es_perturb(params, noise, sigma, antithetic, out, stream=None) -> None:
     if noise.numel() != N * n or out.numel() != (2 if antithetic else 1) * N * n:
         raise ValueError("noise must be [N, n] and out [N or 2N, n]")
     if _done(_native.es_perturb(
-            -1, params, noise, N, n, sigma, int(bool(antithetic)), out, _stream(stream))):
+            None, params, noise, N, n, sigma, int(bool(antithetic)), out, _stream(stream))):
         return
     _check(_lib.diffopt_es_perturb(_addr(params, "params"), _addr(noise, "noise"), int(N), int(n), float(sigma),
                                    int(bool(antithetic)), _addr(out, "out"), _stream(stream)))
@@ -587,7 +587,7 @@ def es_estimate(noise, weights, scale, grad, stream=None) -> None:
     if noise.numel() != N * n:
         raise ValueError("noise must be [N, n] with N = weights.numel(), n = grad.numel()")
     if _done(_native.es_estimate(
-            -1, noise, weights, N, n, scale, grad, _stream(stream))):
+            None, noise, weights, N, n, scale, grad, _stream(stream))):
         return
     _check(_lib.diffopt_es_estimate(_addr(noise, "noise"), _addr(weights, "weights"), int(N), int(n), float(scale),
                                     _addr(grad, "grad"), _stream(stream)))
@@ -612,7 +612,7 @@ def es_perturb_gaussian(params, num_samples: int, seed: int, sigma, antithetic, 
     if out.numel() != (2 if antithetic else 1) * num_samples * n:
         raise ValueError("out must be [N or 2N, n]")
     if _done(_native.es_perturb_gaussian(
-            -1, params, n, num_samples, int(seed) & ((1 << 64) - 1), sigma, int(bool(antithetic)), out,
+            None, params, n, num_samples, int(seed) & ((1 << 64) - 1), sigma, int(bool(antithetic)), out,
             _stream(stream))):
         return
     _check(_lib.diffopt_es_perturb_gaussian(_addr(params, "params"), int(n), int(num_samples),
@@ -629,7 +629,7 @@ def es_estimate_gaussian(fvals, method: str, num_samples: int, seed: int, sigma,
     if m == 1 and f0 is None:
         raise ValueError("the baseline method needs f0 = f(theta)")
     if (m != 1 or _one(f0)) and _done(_native.es_estimate_gaussian(
-            -1, fvals, f0 if m == 1 else None, num_samples, m, grad.numel(),
+            None, fvals, f0 if m == 1 else None, num_samples, m, grad.numel(),
             int(seed) & ((1 << 64) - 1), sigma, grad, _stream(stream))):
         return
     _check(_lib.diffopt_es_estimate_gaussian(_addr(fvals, "fvals"), _addr(f0, "f0", n=1) if m == 1 else None,
@@ -645,7 +645,7 @@ def es_weights(fvals, method: str, num_samples: int, sigma, weights, f0=None, st
     if m == 1 and f0 is None:
         raise ValueError("the baseline method needs f0 = f(theta)")
     if (m != 1 or _one(f0)) and _done(_native.es_weights(
-            -1, fvals, f0 if m == 1 else None, num_samples, m, sigma, weights, _stream(stream))):
+            None, fvals, f0 if m == 1 else None, num_samples, m, sigma, weights, _stream(stream))):
         return
     _check(_lib.diffopt_es_weights(_addr(fvals, "fvals"), _addr(f0, "f0", n=1) if m == 1 else None,
                                    int(num_samples), m, float(sigma), _addr(weights, "weights"), _stream(stream)))

@@ -75,3 +75,21 @@ def test_leaf_pointers_and_flatten_of_any_leaves():
         assert spec.shapes == ((), (2, 3), (2, 3))
     with pytest.raises(ValueError, match="share dtype and device"):
         P.tree.flatten({"a": a, "b": a.double()})
+
+
+@pytest.mark.parametrize("n", [-1, -5])
+def test_negative_counts_are_refused_as_sizes(n):
+    # a tensor never has a negative number of elements; raw addresses reach
+    # the library, which refuses the count itself
+    import paper_2211_06934_amd as P
+    x, out = _operands()
+    h = (0.01, 0.99, 1e-8, 0.0, 0.9)
+    for call in (lambda a, o: P.adam_fwd(*a, *H, *o, n=n), lambda a, o: P.adam_bwd(*a[:3], *a[:3], *H, None, *o, n=n),
+                 lambda a, o: P.sgd_fwd(*a[:3], 0.1, 0.9, True, *o[:2], n=n),
+                 lambda a, o: P.sgd_bwd(*a[:2], 0.1, 0.9, True, *o[:2], n=n),
+                 lambda a, o: P.rmsprop_fwd(*a, *h, *o, n=n),
+                 lambda a, o: P.rmsprop_bwd(*a[:3], *a[:2], *h, *o, n=n)):
+        with pytest.raises(ValueError, match="expected %d elements" % n):
+            call(x, out)
+        with pytest.raises(P.DiffoptError, match="n must be >= 0"):
+            call([t.data_ptr() for t in x], [t.data_ptr() for t in out])
