@@ -14,9 +14,11 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/torch.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 #include <utility>
+#include <vector>
 
 #include "diffopt.h"
 
@@ -181,10 +183,17 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   return call(FN, args, nargs);
 }
 
+// The interpreter lock given up for a scope.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // leaf_pointers(groups, device index) -> list with, per group of leaves, a
 // device int64 tensor of their addresses (None for None): slices of one device
 // tensor, filled by one asynchronous copy from pinned host memory on the
-// current stream.
+// current stream.  The addresses are listed under the interpreter lock, the
+// allocations and the copy, which can wait for the runtime, run without it.
 PyObject* leaf_pointers(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (nargs != 2 || (!PyList_CheckExact(args[0]) && !PyTuple_CheckExact(args[0]))) Py_RETURN_NONE;
   PyObject* out = nullptr;
@@ -196,35 +205,37 @@ PyObject* leaf_pointers(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     }
     const Py_ssize_t k = PySequence_Fast_GET_SIZE(args[0]);
     PyObject** groups = PySequence_Fast_ITEMS(args[0]);
-    int64_t total = 0;
+    std::vector<int64_t> addresses, lengths(static_cast<size_t>(k), -1);  // -1: None
     for (Py_ssize_t g = 0; g < k; ++g) {
       if (groups[g] == Py_None) continue;
       if (!PyList_CheckExact(groups[g]) && !PyTuple_CheckExact(groups[g])) throw Other{};
-      total += PySequence_Fast_GET_SIZE(groups[g]);
-    }
-    const auto opts = at::TensorOptions().dtype(at::kLong);
-    at::Tensor host = at::empty({total}, opts.pinned_memory(true));
-    int64_t* to = host.data_ptr<int64_t>();
-    for (Py_ssize_t g = 0; g < k; ++g) {
-      if (groups[g] == Py_None) continue;
+      const Py_ssize_t len = PySequence_Fast_GET_SIZE(groups[g]);
       PyObject** leaves = PySequence_Fast_ITEMS(groups[g]);
-      for (Py_ssize_t j = 0; j < PySequence_Fast_GET_SIZE(groups[g]); ++j) {
+      for (Py_ssize_t j = 0; j < len; ++j) {
         const at::Tensor& t = tensor_of(leaves[j]);
         if (!t.is_contiguous()) throw Other{};
-        *to++ = reinterpret_cast<int64_t>(t.data_ptr());
+        addresses.push_back(reinterpret_cast<int64_t>(t.data_ptr()));
       }
+      lengths[static_cast<size_t>(g)] = len;
     }
-    const at::Tensor dev = host.to(opts.device(at::kCUDA, static_cast<at::DeviceIndex>(device)), /*non_blocking=*/true);
+    at::Tensor dev;
+    {
+      const Unlocked unlocked;
+      const auto opts = at::TensorOptions().dtype(at::kLong);
+      const at::Tensor host = at::empty({static_cast<int64_t>(addresses.size())}, opts.pinned_memory(true));
+      std::copy(addresses.begin(), addresses.end(), host.data_ptr<int64_t>());
+      dev = host.to(opts.device(at::kCUDA, static_cast<at::DeviceIndex>(device)), /*non_blocking=*/true);
+    }
     out = PyList_New(k);
     if (!out) return nullptr;
     int64_t at = 0;
     for (Py_ssize_t g = 0; g < k; ++g) {
-      if (groups[g] == Py_None) {
+      const int64_t len = lengths[static_cast<size_t>(g)];
+      if (len < 0) {
         Py_INCREF(Py_None);
         PyList_SET_ITEM(out, g, Py_None);
         continue;
       }
-      const int64_t len = PySequence_Fast_GET_SIZE(groups[g]);
       PyObject* t = THPVariable_Wrap(dev.narrow(0, at, len));
       if (!t) {
         Py_DECREF(out);

@@ -93,3 +93,42 @@ def test_negative_counts_are_refused_as_sizes(n):
             call(x, out)
         with pytest.raises(P.DiffoptError, match="n must be >= 0"):
             call([t.data_ptr() for t in x], [t.data_ptr() for t in out])
+
+
+def test_leaf_pointers_let_other_threads_run():
+    # the pinned allocation and the copy wait for the runtime, not for
+    # Python: a thread that wants the interpreter gets it meanwhile.  With the
+    # switch interval out of reach it can only be handed over where a call
+    # gives it up.
+    import sys
+    import threading
+    import time
+
+    import paper_2211_06934_amd as P
+    leaves = [torch.ones(4, device="cuda") for _ in range(64)]
+    groups, dev = (leaves * 64,) * 4, torch.cuda.current_device()
+    native = P.diffopt._native.leaf_pointers
+    native(groups, dev)
+    ticks, stop = [0], threading.Event()
+
+    def run():
+        while not stop.is_set():
+            ticks[0] += 1
+            time.sleep(0)
+
+    old = sys.getswitchinterval()
+    sys.setswitchinterval(1000.0)
+    thread = threading.Thread(target=run)
+    try:
+        thread.start()
+        seen = 0
+        for _ in range(300):
+            before = ticks[0]
+            native(groups, dev)
+            seen += ticks[0] - before
+    finally:
+        stop.set()
+        sys.setswitchinterval(old)
+        time.sleep(0.01)
+        thread.join()
+    assert seen > 0
