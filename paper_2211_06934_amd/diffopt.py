@@ -4,13 +4,16 @@ Argument marshalling only: every function here is the C entry point
 ``diffopt_<name>`` with the same arguments, taking torch tensors (device
 memory) or raw device addresses, and enqueuing on the current torch stream
 unless a stream is given.  Ordinary operands are checked and passed on by the
-native module _binding, everything else by the ctypes code below it.  All arithmetic and data movement happens in the
-HIP library; importing this module fails loudly if the library is missing.
+native module _binding, everything else by the ctypes code below it, which
+also serves alone (with a warning) where that module cannot be loaded.  All
+arithmetic and data movement happens in the HIP library; importing this module
+fails loudly if the library is missing.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import torch
@@ -90,10 +93,19 @@ LIBRARY_PATH = _LIB_PATH
 # diffopt_<entry>, or returns None for operands it does not take (raw
 # subclasses, wrong sizes, ...), which the code after it here then accepts or
 # refuses.
+class _NoNative:
+    """Stands in for a binding that cannot be loaded: hands every call back."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 try:
     from . import _binding as _native
 except ImportError as e:
-    raise ImportError("the native binding is not built (%s); run `python paper_2211_06934_amd/build.py`" % e) from e
+    warnings.warn("the native binding is not built for this torch (%s): calls take the slower ctypes path; run "
+                  "`python paper_2211_06934_amd/build.py`" % e, RuntimeWarning, stacklevel=2)
+    _native = _NoNative()
 
 
 def last_error() -> str:
