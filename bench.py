@@ -68,8 +68,12 @@ B_BWD_ZERO_MV = 28  # dP, g, m, v -> dg, dm, dv (zero moment cotangents)
 B_BWD_FIRST = 28    # dM = dV = 0: dP, g, m, v -> dg, dm, dv
 B_COPY = 8          # pack / unpack: read once, write once
 UNROLL_CHUNK = 16   # steps per launch of the fused K-step driver
-TREE_FWD_CHUNK = 16  # the same for its leaf-direct form, forward
+TREE_FWD_CHUNK = 16  # the same for its leaf-direct form, forward,
+TREE_SMALL_CHUNK = 8  # the forward of a small tree (at most SMALL_LEAVES nonempty leaves and SMALL_ELEMS elements),
 TREE_BWD_CHUNK = 8   # and VJP
+SMALL_LEAVES, SMALL_ELEMS = 32, 1 << 16
+TWO_RUN_STEPS = 6    # longest recomputed run that shares a leaf-direct VJP launch with the run before it,
+TWO_RUN_BYTES = 224 << 20  # if its own launch would move more than this
 
 
 REMAT_SPAN = 8      # longest run of steps whose moments the backward recomputes
@@ -101,13 +105,15 @@ def fwd_plan(K, stored, chunk):
     return launches, b
 
 
-def bwd_plan(K, stored, chunk):
+def bwd_plan(K, stored, chunk, two_run_elems=0):
     """(launches, interface bytes per element) of the fused K-step VJP, as the
     driver plans it, last steps first: a run of steps whose input states are
     stored (at most `chunk`) reads g, mu, nu per step; a run j+1..khi whose
     states j+1..khi-1 are not stored reads mu_j, nu_j once and recomputes the
     rest.  Every launch reads dP, writes dg per step and dmu, dnu, and reads
-    the running dmu, dnu unless it holds step K."""
+    the running dmu, dnu unless it holds step K.  two_run_elems: elements of a
+    tree whose leaf-direct driver runs two recomputed runs in one launch when
+    the later one alone would not fit the Infinity Cache (0: never)."""
     have = set(stored) | {0}
     launches, b, khi = 0, 0, K
     while khi >= 1:
@@ -122,6 +128,12 @@ def bwd_plan(K, stored, chunk):
         else:
             j = max(x for x in have if x < khi)
             b += 8 + 8 * (khi - j)
+            alone = 20 + 8 * (khi - j) + (8 if khi != K else 0)
+            if j >= 1 and j - 1 not in have and alone * two_run_elems > TWO_RUN_BYTES:
+                i = max(x for x in have if x < j)
+                if khi - j <= TWO_RUN_STEPS and j - i <= TWO_RUN_STEPS:
+                    b += 8 + 8 * (j - i)
+                    j = i
             khi = j
     return launches, b
 
@@ -410,8 +422,9 @@ def step_treemap(P, S, ev=None):
 
 def phases_treemap(S):
     K, n = S["K"], S["n"]
-    fl, fb = fwd_plan(K, S["stored"], TREE_FWD_CHUNK)
-    bl, bb = bwd_plan(K, S["stored"], TREE_BWD_CHUNK)
+    small = n <= SMALL_ELEMS and sum(1 for k in S["table"].numel if k) <= SMALL_LEAVES
+    fl, fb = fwd_plan(K, S["stored"], TREE_SMALL_CHUNK if small else TREE_FWD_CHUNK)
+    bl, bb = bwd_plan(K, S["stored"], TREE_BWD_CHUNK, two_run_elems=n)
     return [("adam_fwd_tree", "adam_unrolled_fwd_tree", fl, fb * n),
             ("adam_bwd_tree", "adam_unrolled_bwd_tree", bl, bb * n)]
 

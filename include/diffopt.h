@@ -297,12 +297,17 @@ int diffopt_adam_bwd_tree(const diffopt_segtable* table, const uint64_t* dupdate
  * diffopt_adam_unrolled_fwd / _bwd with every flat buffer replaced by a tree
  * (a device array of leaf addresses).  grads, mu_traj, nu_traj and dgrads are
  * HOST arrays ([K], [K+1], [K+1], [K]) of such device arrays.  The steps run
- * fused, one kernel per 16 steps forward and 8 backward, each lane keeping its elements' running
- * params (forward) or dM, dV (backward) in registers: 16 + 12K and 12 + 16K
- * bytes per element, and results equal to K calls of the single-step
- * leaf-direct entry points bit for bit.  pK may be p0; dmu0 / dnu0 also carry
- * the running cotangents between launches when K > 8.  Output leaves must
- * not overlap input leaves or one another.                                  */
+ * fused, each lane keeping its elements' running params (forward) or dM, dV
+ * (backward) in registers.  Forward: one kernel per 16 steps (8 for a small
+ * tree of at most 32 nonempty leaves and 65,536 elements); 16 + 12K bytes per
+ * element with every state stored.  Backward: a run of stored states takes
+ * one kernel per 8 steps (12 + 16K bytes per element); a run of C steps
+ * recomputed from one stored state takes one kernel (20 + 8C), and two such
+ * neighbouring runs of at most 6 steps share one (28 + 8 (C + C')) when the
+ * later run's kernel would move more than 224 MiB.  Results equal K calls of
+ * the single-step leaf-direct entry points bit for bit.  pK may be p0;
+ * dmu0 / dnu0 also carry the running cotangents between kernels.  Output
+ * leaves must not overlap input leaves or one another.                      */
 int diffopt_adam_unrolled_fwd_tree(const diffopt_segtable* table, int64_t K,
                                    const uint64_t* p0,
                                    const uint64_t* const* grads,

@@ -3,6 +3,7 @@ that the K-step driver must move under each store policy, derived here by
 hand from what each launch reads and writes (fp32, 4 bytes per array)."""
 import importlib.util
 import os
+import types
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -54,8 +55,41 @@ def test_launch_boundaries():
     st = b.stored_states(17, "stored")
     assert b.fwd_plan(17, st, 16) == (2, (16 + 16 * 4 + 16 * 8) + (16 + 4 + 8))
     assert b.bwd_plan(17, st, 16) == (2, (4 + 8 + 16 * 16) + (4 + 8 + 8 + 16))
-    # the leaf-direct driver launches every 8 steps
+    # the leaf-direct driver of a small tree launches every 8 steps
     assert b.fwd_plan(9, b.stored_states(9, "stored"), 8)[0] == 2
+
+
+def test_leaf_direct_launches():
+    b = _bench()
+
+    def plans(K, stored, numel):
+        S = {"K": K, "n": sum(numel), "stored": stored, "table": types.SimpleNamespace(numel=numel)}
+        fwd, bwd = b.phases_treemap(S)
+        return (fwd[2], fwd[3] // S["n"]), (bwd[2], bwd[3] // S["n"])
+
+    # forward: 16 steps a launch, 8 in a small tree (at most 32 nonempty
+    # leaves and 65,536 elements), whose boundary sends p, mu, nu through memory
+    st = b.stored_states(10, "stored")
+    assert plans(10, st, [3000] * 33)[0] == plans(10, st, [70000, 0])[0] == (1, 16 + 10 * 12)
+    assert plans(10, st, [30000, 35536, 0])[0] == (2, (16 + 8 * 12) + (16 + 2 * 12))
+    # VJP, K = 10 with state 5 stored: two recomputed runs of 5 steps.  A tree
+    # whose launch fits the Infinity Cache (60 bytes per element up to 224 MiB)
+    # takes two launches; a larger one takes both runs in one, dP and the
+    # running dM, dV read once: dP in, per run its state and 5 g in and 5 dg
+    # out, dmu0, dnu0 out.
+    st = b.stored_states(10, "recompute")
+    two, one = (2, (4 + 8 + 8 + 5 * 8) + (4 + 8 + 8 + 8 + 5 * 8)), (1, 4 + 2 * (8 + 5 * 8) + 8)
+    assert one == (1, 108)
+    limit = (224 << 20) // 60
+    assert plans(10, st, [limit])[1] == two
+    assert plans(10, st, [limit + 1])[1] == plans(10, st, [11_689_512])[1] == one
+    # runs of 2 and 6 merge, runs of 7 or 8 steps and single steps do not;
+    # three runs: the later two together, the first alone with the running dM, dV
+    big = [20_000_000]
+    assert plans(8, {6, 8}, big)[1] == (1, 12 + (8 + 16) + (8 + 48))
+    assert plans(13, {7, 13}, big)[1] == (2, (12 + 8 + 48) + (12 + 8 + 8 + 56))
+    assert plans(7, {6, 7}, big)[1] == (2, (12 + 16) + (12 + 8 + 8 + 48))
+    assert plans(18, {6, 12, 18}, big)[1] == (2, (12 + 2 * (8 + 48)) + (12 + 8 + 8 + 48))
 
 
 def test_traffic_record_applies_only_to_its_own_launch_size():
