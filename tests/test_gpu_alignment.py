@@ -3,6 +3,9 @@ one phase of the 128-byte lines or each in its own, give the aligned run's
 results bit for bit and touch nothing around them.  Sizes sit at the edges of
 the head and tail handling (heads of up to 31 elements, n % 4 tails, buffers
 shorter than a line) and on both sides of the cached-call limit of each step."""
+import os
+import re
+
 import pytest
 import torch
 
@@ -133,12 +136,25 @@ def _trees(P, sizes, phases, values):
 # tiled kernels (over 32 leaves): empty, tiny and line-sized leaves around tile
 # edges, each tree's leaves at its own phases
 TREE_SIZES = [0, 1, 2, 3, 4, 5, 31, 32, 33, 64, 100, 127, 2048, 2049, 7, 1, 0, 12345] + [1, 3, 513, 6] * 6
+# above the cached-call limit of every step (the smallest moves 16 bytes per
+# element) and of the K-step driver: the streaming forms
+LARGE_TREE_SIZES = TREE_SIZES[:14] + [10_600_001] + TREE_SIZES[14:]
 
 
-@pytest.mark.parametrize("phases", PHASES)
-def test_leaf_direct_steps_at_any_phase(phases):
+def limit_bytes(name):
+    """A size limit of the dispatch rules, from the source that states it."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    text = open(os.path.join(root, "paper_2211_06934_amd", "csrc", "adam_math.hpp")).read()
+    return int(re.search(r"constexpr int64_t %s = int64_t\((\d+)\) << 20;" % name, text).group(1)) << 20
+
+
+@pytest.mark.parametrize("sizes,phases", [(TREE_SIZES, p) for p in PHASES] +
+                         [(LARGE_TREE_SIZES, p) for p in (PHASES[0], PHASES[3])])
+def test_leaf_direct_steps_at_any_phase(sizes, phases):
     import paper_2211_06934_amd as P
-    n, K = sum(TREE_SIZES), 10
+    n, K = sum(sizes), 10
+    if sizes is LARGE_TREE_SIZES:
+        assert 16 * n > limit_bytes("kKeepBytes") and 60 * n > limit_bytes("kKeepRunBytes")
     x = _values(8 + K, n, 11)
     x[2].abs_()
     x[3].abs_()
@@ -150,7 +166,7 @@ def test_leaf_direct_steps_at_any_phase(phases):
     flat["sgd"] = _sgd(P, x[:7], S, n)
     flat["rmsprop"] = _rmsprop(P, x[:7], S, n)
 
-    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp, dm, dv] + [None] * 9)
+    t, S, f, a = _trees(P, sizes, phases, [p, g, m, v, dp, dm, dv] + [None] * 9)
     P.adam_fwd_tree(t, a[0], a[1], a[2], a[3], *HYPER, a[7], a[8], a[9])
     P.adam_bwd_tree(t, a[4], a[5], a[6], a[1], a[2], a[3], *HYPER, a[10], a[11], a[12])
     P.adam_bwd_tree(t, a[4], None, None, a[1], a[2], a[3], *HYPER, a[13], a[14], a[15])
@@ -159,7 +175,7 @@ def test_leaf_direct_steps_at_any_phase(phases):
         assert torch.equal(f[7 + k], flat["adam"][i]), ("adam", k)
     S.check_guards()
 
-    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp] + [None] * 4)
+    t, S, f, a = _trees(P, sizes, phases, [p, g, m, v, dp] + [None] * 4)
     P.sgd_fwd_tree(t, a[0], a[1], a[2], 0.1, 0.9, True, a[5], a[6])
     P.sgd_bwd_tree(t, a[3], a[4], 0.1, 0.9, True, a[7], a[8])
     torch.cuda.synchronize()
@@ -168,7 +184,7 @@ def test_leaf_direct_steps_at_any_phase(phases):
     S.check_guards()
 
     h = (0.01, 0.99, 1e-8, 1e-9, 0.9)
-    t, S, f, a = _trees(P, TREE_SIZES, phases, [p, g, m, v, dp, dm, dv] + [None] * 6)
+    t, S, f, a = _trees(P, sizes, phases, [p, g, m, v, dp, dm, dv] + [None] * 6)
     P.rmsprop_fwd_tree(t, a[0], a[1], a[2], a[3], *h, a[7], a[8], a[9])
     P.rmsprop_bwd_tree(t, a[4], a[5], a[6], a[1], a[2], *h, a[10], a[11], a[12])
     torch.cuda.synchronize()
@@ -184,7 +200,7 @@ def test_leaf_direct_steps_at_any_phase(phases):
         P.adam_unrolled_fwd(p, x[8:], mu, nu, pK, *HYPER)
         P.adam_unrolled_bwd(dp, x[8:], mu, nu, dg, d0, d1, *HYPER)
         order = sorted(kept)
-        t, S, f, a = _trees(P, TREE_SIZES, phases, [p, m, v, dp, *x[8:]] + [None] * (3 + K + 2 * len(kept)))
+        t, S, f, a = _trees(P, sizes, phases, [p, m, v, dp, *x[8:]] + [None] * (3 + K + 2 * len(kept)))
         at = 4 + K + 3 + K
         tmu = [a[1]] + [a[at + order.index(k)] if k in kept else None for k in range(1, K + 1)]
         tnu = [a[2]] + [a[at + len(kept) + order.index(k)] if k in kept else None for k in range(1, K + 1)]

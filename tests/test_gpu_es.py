@@ -252,6 +252,31 @@ def test_perturb_rows_at_every_phase(n, offset):
             assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + R * n:] == 7.0)
 
 
+@pytest.mark.parametrize("antithetic", [False, True])
+@pytest.mark.parametrize("N", [64, 67])
+def test_perturb_of_many_workgroups_at_odd_phase(N, antithetic):
+    # enough workgroups for four samples each (2,048 of them), the last group
+    # of 67 short; rows of odd length against the same rows in longer,
+    # line-aligned ones
+    import paper_2211_06934_amd as P
+    n, m, seed, sigma = 600_001, 600_032, 21, 0.1
+    assert -(-n // 4096) * -(-N // 4) >= 2048
+    R = (2 if antithetic else 1) * N
+    theta = torch.empty(m, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(2))
+    full = torch.empty(R, m, device="cuda")
+    P.es_perturb_gaussian(theta, N, seed, sigma, antithetic, full)
+    buf = torch.full((3 + R * n + 40,), 7.0, device="cuda")
+    P.es_perturb_gaussian(theta[:n], N, seed, sigma, antithetic, buf[3:3 + R * n])
+    torch.cuda.synchronize()
+    assert torch.equal(buf[3:3 + R * n].view(R, n), full[:, :n])
+    assert torch.all(buf[:3] == 7.0) and torch.all(buf[3 + R * n:] == 7.0)
+    # four samples a workgroup or one (a call of the first three alone)
+    few = torch.empty(3, n, device="cuda")
+    P.es_perturb_gaussian(theta[:n], 3, seed, sigma, False, few)
+    torch.cuda.synchronize()
+    assert torch.equal(few, full[:3, :n])
+
+
 @pytest.mark.parametrize("method", ["plain", "baseline", "antithetic"])
 def test_es_weights_match_oracle(method):
     import paper_2211_06934_amd as P

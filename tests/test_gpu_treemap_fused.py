@@ -15,6 +15,7 @@ import numpy as np
 import pytest
 import torch
 
+from tests.test_gpu_alignment import TREE_SIZES, _trees, _values, limit_bytes
 from tests.test_gpu_treemap import _device_tree, _empty_like_tree, _leaves, _ptrs
 from workloads import HYPER, random_shapes
 
@@ -185,8 +186,8 @@ def test_fused_tree_recomputed_many_small_full_size():
 
 
 @pytest.mark.parametrize("K,keep", [
-    (10, (5,)), (9, (4,)), (16, (8,)), (15, (7,)),  # two recomputed runs in one launch, equal and unequal
-    (18, (6, 12)), (24, (8, 16)),                   # three: two and one; a forward launch boundary on a stored state
+    (10, (5,)), (9, (4,)), (16, (8,)), (15, (7,)),  # two recomputed runs, equal and unequal
+    (18, (6, 12)), (24, (8, 16)),                   # three; a forward launch boundary between stored states
     (20, (1, 2, 9, 17)), (32, (7, 14, 21, 28)),     # runs around stored steps, the boundary at step 16 unstored
 ])
 @pytest.mark.parametrize("mode", ["separate", "packed-views"])
@@ -204,3 +205,47 @@ def test_long_fused_tree_equals_stepwise_bitwise(K, keep, mode):
         _same(got["dg"][k], ref["dg"][k], "dg_%d" % (k + 1))
     _same(got["dm0"], ref["dm0"], "dmu0")
     _same(got["dv0"], ref["dv0"], "dnu0")
+
+
+# Two neighbouring recomputed runs of at most 6 steps share a launch in trees
+# whose launch streams from memory: a leaf of 6.6 million elements among empty,
+# tiny and odd ones.
+TWO_RUN_SIZES = TREE_SIZES[:14] + [6_600_001] + TREE_SIZES[14:]
+
+
+@pytest.mark.parametrize("K,kept", [
+    (4, (2,)), (6, (3,)), (8, (4,)), (10, (5,)), (12, (6,)),            # equal runs of 2 to 6 steps
+    (5, (2,)), (5, (3,)), (8, (2,)), (8, (6,)), (11, (5,)), (11, (6,)),  # unequal ones, the later or the earlier longer
+    (18, (6, 12)), (12, (3, 6, 9)), (9, (2, 5, 8)),  # three runs, four, three after a stored step: running dM, dV in
+    (13, (6,)), (13, (7,)), (15, (5, 10)),           # a run of 7 steps keeps a launch of its own
+])
+@pytest.mark.parametrize("phases", [[0], [31], [1, 2, 3, 0, 5, 6, 7, 30, 9, 10, 31, 12]])
+def test_two_recomputed_runs_in_one_launch(K, kept, phases):
+    # against the flat steps one by one, bit for bit
+    import paper_2211_06934_amd as P
+    n, hyper = sum(TWO_RUN_SIZES), (1, LR, B1, B2, EPS, 1e-8)
+    assert (20 + 8 * 2) * n > limit_bytes("kKeepRunBytes")  # the shortest run's launch
+    x = _values(K + 4, n, K)
+    x[2].abs_()
+    p, m0, v0, cot, g = *x[:4], x[4:]
+    new = lambda: torch.empty(n, device="cuda")  # noqa: E731
+    mu, nu = [m0] + [new() for _ in range(K)], [v0] + [new() for _ in range(K)]
+    pk, dg, dm, dv = p.clone(), [new() for _ in range(K)], new(), new()
+    for k in range(K):
+        P.adam_fwd(pk, g[k], mu[k], nu[k], 1 + k, *hyper[1:], pk, mu[k + 1], nu[k + 1])
+    for k in range(K - 1, -1, -1):
+        last = k == K - 1
+        P.adam_bwd(cot, None if last else dm, None if last else dv, g[k], mu[k], nu[k], 1 + k, *hyper[1:], None, dg[k],
+                   dm, dv)
+    stored = sorted({*kept, K})
+    t, S, f, a = _trees(P, TWO_RUN_SIZES, phases, [*x] + [None] * (3 + K + 2 * len(stored)))
+    out, at = 4 + K, 4 + K + 3 + K
+    tmu = [a[1]] + [a[at + stored.index(k)] if k in stored else None for k in range(1, K + 1)]
+    tnu = [a[2]] + [a[at + len(stored) + stored.index(k)] if k in stored else None for k in range(1, K + 1)]
+    P.adam_unrolled_fwd_tree(t, a[0], a[4:out], tmu, tnu, a[out], *hyper)
+    P.adam_unrolled_bwd_tree(t, a[3], a[4:out], tmu, tnu, a[out + 3:at], a[out + 1], a[out + 2], *hyper)
+    torch.cuda.synchronize()
+    want = [pk, dm, dv, *dg, *(mu[k] for k in stored), *(nu[k] for k in stored)]
+    for k, (b, c) in enumerate(zip(f[out:], want)):
+        assert torch.equal(b, c), k
+    S.check_guards()
