@@ -12,16 +12,34 @@
 
 #include "adam_math.hpp"
 
-#ifndef DIFFOPT_ES_PERTURB_ROWS
-#define DIFFOPT_ES_PERTURB_ROWS 8
-#endif
-
-
 namespace diffopt {
 namespace {
 
 constexpr int kEB = 256;   // threads per workgroup
-constexpr int kRows = DIFFOPT_ES_PERTURB_ROWS;  // noise rows per workgroup in perturb
+constexpr int kRows = 8;   // noise rows per workgroup in perturb
+// Perturb calls that read little take plain loads and kKeepRows rows per
+// workgroup (twice the workgroups): theta is read again by every group of
+// rows, and the noise often comes from the cache that its generator wrote.
+// Measured on MI355X, microseconds with streaming loads and 8 rows / plain and
+// 4, one set of buffers, then three in turn; antithetic, one row a sample below:
+//   n = 300,001, N = 8       8.3 / 6.3, 8.9 / 7.3      6.6 / 5.1, 7.1 / 5.6
+//   n = 112,261, N = 64      18.2 / 15.1, 19.4 / 16.1  12.0 / 9.2, 12.8 / 10.9
+//   n = 600,001, N = 32      48.8 / 39.8, 50.1 / 40.0  31.1 / 27.8, 32.3 / 27.6
+//   n = 8,300,000, N = 2     38.9 / 34.1, 39.8 / 37.7  26.2 / 24.7, 27.3 / 26.9
+// The line lies at kPerturbKeepBytes for rows that stay on 16 bytes (above it
+// one row a sample loses where the sets alternate: n = 8,300,000, N = 3 37.9 /
+// 40.5, N = 5 60.7 / 66.1) and at kPerturbKeepOddBytes for others, whose
+// neighbouring vectors share 32-byte sectors (n = 4,200,001, N = 16 186.7 /
+// 170.3 and 112.7 / 103.1), unless theta alone takes much of the cache (n =
+// 11,689,511, N = 2 58.9 / 60.4 and 38.2 / 40.7).  Such rows also store plainly
+// up to kPerturbStoreBytes, so that the parts of a line meet in the cache (n =
+// 1,200,001, N = 4 12.1 -> 11.0 us where the sets alternate, n = 600,001, N = 8
+// 12.0 -> 11.3; above, N = 24 30.7 -> 37.4).
+constexpr int kKeepRows = 4;
+constexpr int64_t kPerturbKeepBytes = int64_t(96) << 20;
+constexpr int64_t kPerturbKeepOddBytes = int64_t(320) << 20;
+constexpr int64_t kPerturbKeepOddTheta = int64_t(8) << 20;  // parameters
+constexpr int64_t kPerturbStoreBytes = int64_t(48) << 20;
 constexpr int kUnroll = 8; // rows in flight per lane in estimate
 constexpr int kMaxClasses = 8;  // phase classes of the noise rows
 // Measured on MI355X (n = 11,689,512, N = 64): 4 slices per lane 0.50 ms,
@@ -48,13 +66,14 @@ struct PerturbPlan {
 };
 
 // Grid: x over 4-element vectors of theta (shifted per class), y over groups
-// of kRows same-phase samples.  The dispatcher walks x fastest, so the chip
+// of ROWS same-phase samples.  The dispatcher walks x fastest, so the chip
 // works through one group of rows at a time (few DRAM pages open at once);
 // theta is re-read per group, mostly from the Infinity Cache.  A lane issues
 // all of its group's row loads first.  Rows are n elements apart, so with
 // n % 4 != 0 (or pointers off 16 bytes) their vectors are only 4-byte aligned
 // and the plan has one unshifted class; vector nv then holds the n % 4 last
 // elements of each row, moved one by one.
+template <int ROWS, bool KEEP, bool KEEP_OUT>
 __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const float* noise, int64_t N, int64_t n,
                                                        float sigma, int antithetic, float* out, PerturbPlan plan) {
   int r = 0;  // phase class of this group
@@ -63,11 +82,11 @@ __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const 
   const int64_t nv = n >> 2;
   if (v < 0 || 4 * v >= n) return;
   const int64_t P = plan.P;
-  const int64_t i0 = r + P * ((int64_t)kRows * ((int64_t)blockIdx.y - plan.gstart[r]));  // first row; rows step by P
+  const int64_t i0 = r + P * ((int64_t)ROWS * ((int64_t)blockIdx.y - plan.gstart[r]));  // first row; rows step by P
   const float* z = noise + 4 * v;
   float* o = out + 4 * v;
   if (v == nv) {
-    for (int64_t i = i0; i < N && i < i0 + P * kRows; i += P)
+    for (int64_t i = i0; i < N && i < i0 + P * ROWS; i += P)
       for (int e = 0; e < (int)(n & 3); ++e) {
         const float x = z[i * n + e], t = theta[4 * v + e];
         o[i * n + e] = fmaf(sigma, x, t);
@@ -75,15 +94,19 @@ __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const 
       }
     return;
   }
-  const f32x4 t = ld(reinterpret_cast<const f32x4u*>(theta) + v);
+  const f32x4 t = ld<KEEP>(reinterpret_cast<const f32x4u*>(theta) + v);
   const auto in = [&](int64_t i) { return reinterpret_cast<const f32x4u*>(z + i * n); };
   const auto to = [&](int64_t i) { return reinterpret_cast<f32x4u*>(o + i * n); };
-  if (i0 + P * (kRows - 1) < N) {
-    f32x4 rw[kRows];
+  const auto put = [&](f32x4u* p, const f32x4u& x) {
+    if (KEEP_OUT) *p = x;
+    else st(p, x);
+  };
+  if (i0 + P * (ROWS - 1) < N) {
+    f32x4 rw[ROWS];
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) rw[u] = ld(in(i0 + P * u));
+    for (int u = 0; u < ROWS; ++u) rw[u] = ld<KEEP>(in(i0 + P * u));
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int64_t i = i0 + P * u;
       f32x4u a, b;
 #pragma unroll
@@ -91,20 +114,20 @@ __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const 
         a[e] = fmaf(sigma, rw[u][e], t[e]);
         b[e] = fmaf(-sigma, rw[u][e], t[e]);
       }
-      st(to(i), a);
-      if (antithetic) st(to(N + i), b);
+      put(to(i), a);
+      if (antithetic) put(to(N + i), b);
     }
   } else {
     for (int64_t i = i0; i < N; i += P) {
-      const f32x4 rw = ld(in(i));
+      const f32x4 rw = ld<KEEP>(in(i));
       f32x4u a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = fmaf(sigma, rw[e], t[e]);
         b[e] = fmaf(-sigma, rw[e], t[e]);
       }
-      st(to(i), a);
-      if (antithetic) st(to(N + i), b);
+      put(to(i), a);
+      if (antithetic) put(to(N + i), b);
     }
   }
 }
@@ -663,7 +686,8 @@ extern "C" int diffopt_es_perturb(const float* params, const float* noise, int64
   hipStream_t st = as_stream(stream);
   PerturbPlan plan{};
   plan.P = 1;
-  if (n % 4 == 0 && al16(params) && al16(noise) && al16(out)) {  // whole 16-byte vectors: align the lanes to the lines
+  const bool vec = n % 4 == 0 && al16(params) && al16(noise) && al16(out);
+  if (vec) {  // whole 16-byte vectors: align the lanes to the lines
     const int64_t q = (n / 4) % 8;
     int64_t g = 8;  // gcd(q, 8)
     if (q != 0) {
@@ -679,18 +703,32 @@ extern "C" int diffopt_es_perturb(const float* params, const float* noise, int64
     const int64_t base = (int64_t)((reinterpret_cast<uintptr_t>(noise) >> 4) & 7u);
     for (int r = 0; r < plan.P; ++r) plan.shift[r] = (int32_t)((base + (int64_t)r * q) & 7);  // row r's phase, in vectors
   }
-  int64_t gy = 0;
-  for (int r = 0; r < plan.P; ++r) {
-    plan.gstart[r] = gy;
-    const int64_t rows = (num_samples - r + plan.P - 1) / plan.P;
-    gy += (rows + kRows - 1) / kRows;
+  const auto groups = [&](int per) {  // rows split into groups of `per`, class by class
+    int64_t gy = 0;
+    for (int r = 0; r < plan.P; ++r) {
+      plan.gstart[r] = gy;
+      const int64_t rows = (num_samples - r + plan.P - 1) / plan.P;
+      gy += (rows + per - 1) / per;
+    }
+    plan.gstart[plan.P] = gy;
+    return gy;
+  };
+  bool keep = num_samples < (vec || n > kPerturbKeepOddTheta ? kPerturbKeepBytes : kPerturbKeepOddBytes) / 4 / n;
+  int64_t gy = groups(keep ? kKeepRows : kRows);
+  if (keep && gy > 65535) {  // more groups than the grid takes: the larger ones
+    keep = false;
+    gy = groups(kRows);
   }
-  plan.gstart[plan.P] = gy;
   if (gy > 65535) return fail(DIFFOPT_EINVAL, "%s: num_samples too large (max about %d)", who, 65535 * kRows);
   const int64_t bx = ((n + 3) / 4 + 7 + kEB - 1) / kEB;  // lanes shifted by up to 7 vectors
   if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
-  hipLaunchKernelGGL(es_perturb_vec, dim3((unsigned)bx, (unsigned)gy), dim3(kEB), 0, st, params, noise, num_samples,
-                     n, (float)sigma, antithetic ? 1 : 0, out, plan);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)bx, (unsigned)gy), dim3(kEB), 0, st, params, noise, num_samples, n,
+                       (float)sigma, antithetic ? 1 : 0, out, plan);
+  };
+  if (!keep) go(es_perturb_vec<kRows, false, false>);
+  else if (!vec && num_samples <= kPerturbStoreBytes / (antithetic ? 8 : 4) / n) go(es_perturb_vec<kKeepRows, true, true>);
+  else go(es_perturb_vec<kKeepRows, true, false>);
   return launch_status(who);
 }
 

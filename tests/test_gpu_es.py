@@ -252,6 +252,45 @@ def test_perturb_rows_at_every_phase(n, offset):
             assert torch.all(buf[:offset] == 7.0) and torch.all(buf[offset + R * n:] == 7.0)
 
 
+@pytest.mark.parametrize("n,N", [(600_001, 24), (4_200_001, 20), (8_388_613, 9), (8_388_612, 3)])
+@pytest.mark.parametrize("antithetic", [False, True])
+def test_perturb_larger_than_the_cache(n, N, antithetic):
+    # streaming stores, then streaming loads too (rows off 16 bytes above 320
+    # MiB, above 96 MiB for many parameters), with whole and short groups of
+    # rows: column ranges equal small calls on those columns alone
+    import paper_2211_06934_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    theta = torch.empty(n, device="cuda").normal_(generator=gen)
+    Z = torch.empty(N, n, device="cuda").normal_(generator=gen)
+    out = torch.empty((2 if antithetic else 1) * N, n, device="cuda")
+    P.es_perturb(theta, Z, 0.1, antithetic, out)
+    for a, b in ((0, 1001), (n // 2, n // 2 + 4097), (n - 997, n)):
+        part = torch.empty(out.shape[0], b - a, device="cuda")
+        P.es_perturb(theta[a:b].contiguous(), Z[:, a:b].contiguous(), 0.1, antithetic, part)
+        torch.cuda.synchronize()
+        assert torch.equal(part, out[:, a:b])
+
+
+@pytest.mark.parametrize("n", [3, 4])
+def test_perturb_of_many_samples(n):
+    # four rows a workgroup would take more groups than the grid holds from
+    # 65,535 x 4 samples on, eight from 65,535 x 8 (a class of rows in phase
+    # each; n = 4 has one per 16-byte phase), where the call is refused
+    import paper_2211_06934_amd as P
+    most = 65535 * 8
+    theta = _dev(normal(n, 1.0, "ges", "p0", n))
+    Z = torch.randn(most + 64, n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    full = torch.empty(2 * 300_001, n, device="cuda")
+    P.es_perturb(theta, Z[:300_001], 0.1, True, full)
+    for a, b in ((0, 1001), (150_000, 262_144), (299_990, 300_001)):
+        part = torch.empty(2 * (b - a), n, device="cuda")
+        P.es_perturb(theta, Z[a:b], 0.1, True, part)
+        torch.cuda.synchronize()
+        assert torch.equal(part, torch.cat([full[a:b], full[300_001 + a:300_001 + b]]))
+    with pytest.raises(P.DiffoptError, match="num_samples too large"):
+        P.es_perturb(theta, Z, 0.1, False, torch.empty(most + 64, n, device="cuda"))
+
+
 @pytest.mark.parametrize("antithetic", [False, True])
 @pytest.mark.parametrize("N", [64, 67])
 def test_perturb_of_many_workgroups_at_odd_phase(N, antithetic):
