@@ -42,13 +42,6 @@ constexpr int64_t kPerturbKeepOddTheta = int64_t(8) << 20;  // parameters
 constexpr int64_t kPerturbStoreBytes = int64_t(48) << 20;
 constexpr int kUnroll = 8; // rows in flight per lane in estimate
 constexpr int kMaxClasses = 8;  // phase classes of the noise rows
-// Measured on MI355X (n = 11,689,512, N = 64): 4 slices per lane 0.50 ms,
-// 2 slices 0.51, 1 slice 0.54.
-#ifndef DIFFOPT_ES_EST_U
-#define DIFFOPT_ES_EST_U 4
-#endif
-constexpr int kEstU = DIFFOPT_ES_EST_U;  // 16-byte grad slices per lane in estimate
-
 // Rows of the [N][n] noise start at 16-byte phases p_i = (base/16 + i nv) mod 8
 // within the 128-byte lines; a wave's 64 vectors of a row then span 9 lines
 // instead of 8 unless the lanes are shifted by p_i.  Rows i and i + P, with
@@ -132,21 +125,22 @@ __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const 
   }
 }
 
-// Each lane owns kEstU 4-element slices of grad, kEB vectors apart, and
+// Each lane owns U 4-element slices of grad, kEB vectors apart, and
 // accumulates the N rows in sample order, kUnroll rows in flight.  A
-// workgroup thus covers kEB * kEstU contiguous vectors of every row; rows
+// workgroup thus covers kEB * U contiguous vectors of every row; rows
 // start at varying phases of the 128-byte lines, so the lines at the ends of a
 // workgroup's range are also fetched by its neighbours, and a wider range
 // makes that a smaller share.  Vectors need only 4-byte alignment; the lane of
 // vector nv takes the n % 4 last elements one by one.
+template <int U>
 __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const float* __restrict__ w, int64_t N,
                                                         int64_t n, float scale, float* grad) {
-  const int64_t v0 = (int64_t)blockIdx.x * (kEB * kEstU) + threadIdx.x;
+  const int64_t v0 = (int64_t)blockIdx.x * (kEB * U) + threadIdx.x;
   const int64_t nv = n >> 2;
-  f32x4 acc[kEstU];
-  bool on[kEstU];
+  f32x4 acc[U];
+  bool on[U];
 #pragma unroll
-  for (int q = 0; q < kEstU; ++q) {
+  for (int q = 0; q < U; ++q) {
     acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     on[q] = v0 + (int64_t)q * kEB < nv;
     if (v0 + (int64_t)q * kEB == nv) {
@@ -163,17 +157,17 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
   };
   int64_t i = 0;
   for (; i + kUnroll <= N; i += kUnroll) {
-    f32x4 r[kUnroll][kEstU];
+    f32x4 r[kUnroll][U];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
 #pragma unroll
-      for (int q = 0; q < kEstU; ++q)
+      for (int q = 0; q < U; ++q)
         if (on[q]) r[u][q] = ld(row(i + u, q));
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const float wi = w[i + u];
 #pragma unroll
-      for (int q = 0; q < kEstU; ++q)
+      for (int q = 0; q < U; ++q)
         if (on[q])
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(wi, r[u][q][e], acc[q][e]);
@@ -182,7 +176,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
   for (; i < N; ++i) {
     const float wi = w[i];
 #pragma unroll
-    for (int q = 0; q < kEstU; ++q)
+    for (int q = 0; q < U; ++q)
       if (on[q]) {
         const f32x4 r = ld(row(i, q));
 #pragma unroll
@@ -190,7 +184,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
       }
   }
 #pragma unroll
-  for (int q = 0; q < kEstU; ++q)
+  for (int q = 0; q < U; ++q)
     if (on[q]) {
       f32x4u out;
 #pragma unroll
@@ -662,6 +656,25 @@ int gauss_split_slots(int64_t work, int64_t N) {
   return work >= (int64_t(1) << 13) || N < 64 ? 64 : 16;
 }
 
+// Slices per lane of the estimate that walks all samples in one lane.  Four
+// keep most of a line's users in one workgroup, which pays once every CU has
+// work and the rows go out eight at a time; fewer samples leave a lane waiting
+// for each row in turn, and fewer workgroups leave CUs idle.  Measured on
+// MI355X, microseconds with 1 / 2 / 4 slices, three sets of buffers in turn:
+//   n = 300,001    N = 5 3.6 / 6.0 / 9.3     N = 16 6.5 / 5.7 / 7.7
+//   n = 600,001    N = 5 5.2 / 6.8 / 10.0    N = 16 9.4 / 10.6 / 8.8    N = 64 35.4 / 38.9 / 28.9
+//   n = 1,200,001  N = 2 3.5 / 4.5 / 6.0     N = 12 12.9 / 15.4 / 19.6
+//   n = 2,400,001  N = 2 6.4 / 6.0 / 7.7     N = 12 23.1 / 22.0 / 25.1
+//   n = 4,200,001  N = 2 11.7 / 10.1 / 13.1  N = 5 21.2 / 18.6 / 26.1   N = 16 51.9 / 46.7 / 47.0
+//   n = 8,300,000  N = 5 33.5 / 34.5 / 41.5  N = 8 48.5 / 48.8 / 48.3
+//   n = 11,689,512, N = 64 540 / 510 / 500
+int estimate_slices(int64_t nvec, int64_t N) {
+  const int64_t wg4 = (nvec + kEB * 4 - 1) / (kEB * 4);  // workgroups with four slices
+  if (N >= 16) return wg4 < 128 ? 1 : 4;
+  if (wg4 < 400) return 1;
+  return N < 8 || wg4 < 1500 ? 2 : 4;
+}
+
 constexpr int kMaxPerturbRows = 65535 * 8;
 // Workgroups of kLRows samples below which each takes one sample instead.
 constexpr int64_t kFewLineGroups = 2048;
@@ -745,7 +758,8 @@ extern "C" int diffopt_es_estimate(const float* noise, const float* weights, int
   hipStream_t st = as_stream(stream);
   const int64_t nvec = (n + 3) / 4;
   const int slots = noise_split_slots(nvec, num_samples);
-  const int64_t per = slots ? slots : kEB * kEstU;  // vectors per workgroup
+  const int slices = estimate_slices(nvec, num_samples);
+  const int64_t per = slots ? slots : kEB * slices;  // vectors per workgroup
   const int64_t bx = (nvec + per - 1) / per;
   if (bx > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
   const dim3 grid((unsigned)bx);
@@ -755,8 +769,12 @@ extern "C" int diffopt_es_estimate(const float* noise, const float* weights, int
   else if (slots == 16)
     hipLaunchKernelGGL(es_estimate_split<16>, grid, dim3(kSB), 0, st, noise, weights, num_samples, n, (float)scale,
                        grad);
-  else
-    hipLaunchKernelGGL(es_estimate_vec, grid, dim3(kEB), 0, st, noise, weights, num_samples, n, (float)scale, grad);
+  else {
+    const auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kEB), 0, st, noise, weights, num_samples, n, (float)scale, grad);
+    };
+    slices == 1 ? go(es_estimate_vec<1>) : slices == 2 ? go(es_estimate_vec<2>) : go(es_estimate_vec<4>);
+  }
   return launch_status(who);
 }
 

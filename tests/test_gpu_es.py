@@ -211,6 +211,27 @@ def test_es_estimate_split_over_samples(n, N):
     assert_mag_close(g.cpu().numpy(), oracle.es_estimate(Z, w, 0.25), oracle.es_estimate_mag(Z, w, 0.25), BWD_RTOL)
 
 
+@pytest.mark.parametrize("n,N", [(300_001, 16), (300_002, 31), (523_263, 16), (523_271, 16), (1_634_303, 7), (1_634_311, 7),
+                                 (1_700_003, 15), (6_140_001, 8), (6_150_003, 8), (6_150_003, 7), (6_150_003, 0)])
+def test_es_estimate_slices_per_lane(n, N):
+    # one, two or four slices a lane, by the parameters and the samples; the
+    # order of a sum is the sample order in all of them
+    import paper_2211_06934_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    Z = torch.empty(N, n, device="cuda").normal_(generator=gen)
+    w = torch.empty(N, device="cuda").normal_(generator=gen)
+    g = torch.full((n + 8,), 7.0, device="cuda")
+    P.es_estimate(Z, w, 0.25, g[:n])
+    torch.cuda.synchronize()
+    assert torch.all(g[n:] == 7.0)
+    want = torch.zeros(n, device="cuda", dtype=torch.float64)
+    mag = torch.zeros(n, device="cuda", dtype=torch.float64)
+    for i in range(N):
+        want += w[i].double() * Z[i].double()
+        mag += (w[i].double() * Z[i].double()).abs()
+    assert torch.all((g[:n].double() - 0.25 * want).abs() <= BWD_RTOL * 0.25 * mag)
+
+
 @pytest.mark.parametrize("n", [1, 5, 511, 515, 8193, 65536 - 512, 65541])
 @pytest.mark.parametrize("N,method", [(15, "plain"), (16, "antithetic"), (63, "baseline"), (64, "plain"), (70, "antithetic")])
 def test_gaussian_estimate_split_over_samples(n, N, method):
