@@ -472,9 +472,8 @@ constexpr int kLW = DIFFOPT_ES_LINE_WAVES;  // waves (segments) per workgroup
 // 1.143, 1.143, 1.138 ms alone, equal when the estimate follows (the chip then
 // runs at its power limit, and one sample per workgroup redoes the
 // sample-independent part of the generator); the sample groups outermost 1.176.
-// One row a sample (not antithetic): 0.839, 0.762, 0.718 ms for 1, 2, 4.  With
-// few workgroups each takes one sample (n = 112,261, N = 64 antithetic: 13.9
-// us against 16.9 for four).
+// One row a sample (not antithetic): 0.839, 0.762, 0.718 ms for 1, 2, 4.
+// Smaller calls take fewer by perturb_samples.
 #ifndef DIFFOPT_ES_LINE_ROWS
 #define DIFFOPT_ES_LINE_ROWS 4
 #endif
@@ -676,8 +675,32 @@ int estimate_slices(int64_t nvec, int64_t N) {
 }
 
 constexpr int kMaxPerturbRows = 65535 * 8;
-// Workgroups of kLRows samples below which each takes one sample instead.
-constexpr int64_t kFewLineGroups = 2048;
+// Samples per workgroup of the generated-noise perturbation over `chunks`
+// parameter chunks.  One while the chip holds all samples' workgroups in about
+// two rounds (four of them fit a CU); beyond that a workgroup that reads theta
+// once for several samples wins, the more so the fewer samples share a chunk's
+// theta in the cache.  Antithetic calls of many samples write enough per sample
+// that one per workgroup stays ahead until the grid is large.  Measured on
+// MI355X, microseconds with 1 / 2 / 4 samples per workgroup; antithetic, one row
+// a sample:
+//   n = 524,000    N = 8 7.5 / 8.2 / 9.2       5.9 / 6.1 / 7.1
+//                  N = 32 23.7 / 26.0 / 27.0   18.3 / 17.1 / 16.6
+//   n = 600,001    N = 16 18.4 / 18.8 / 19.1   11.7 / 11.9 / 14.3
+//   n = 1,000,000  N = 8 15.2 / 13.4 / 13.3    9.7 / 9.3 / 9.5
+//                  N = 32 44.7 / 52.8 / 52.9   34.3 / 32.0 / 30.5
+//   n = 2,000,000  N = 3 12.0 / 11.6 / 10.0    8.5 / 9.1 / 7.6 (three sets of buffers in turn)
+//                  N = 8 28.5 / 26.2 / 26.5    19.3 / 16.9 / 15.9
+//                  N = 12 37.6 / 38.6 / 40.4   26.7 / 24.9 / 23.4
+//   n = 8,300,000  N = 3 43.5 / 40.1 / 37.8    28.9 / 29.2 / 24.5
+//                  N = 8 109.6 / 93.8 / 103.1  74.0 / 66.0 / 61.1
+int perturb_samples(int64_t chunks, int64_t N, bool antithetic) {
+  const int64_t single = chunks * N;  // workgroups of one sample each
+  if (N <= 3) return single < 1400 ? 1 : kLRows;
+  if (single < 1900) return 1;
+  if (!antithetic) return single < 3600 ? 2 : kLRows;
+  if (N < 12) return 2;
+  return chunks * ((N + kLRows - 1) / kLRows) < 2048 ? 1 : kLRows;
+}
 
 bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 bool al4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
@@ -804,7 +827,7 @@ extern "C" int diffopt_es_perturb_gaussian(const float* params, int64_t n, int64
   const int64_t blocks = 64 * ((n + 511) / 512);  // Philox blocks: 64 per 512 parameters
   if ((blocks + kEB - 1) / kEB > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
   const int64_t chunks = (blocks + kLB - 1) / kLB;
-  const int rows = chunks * ((num_samples + kLRows - 1) / kLRows) < kFewLineGroups ? 1 : kLRows;
+  const int rows = perturb_samples(chunks, num_samples, antithetic != 0);
   const int64_t groups = (num_samples + rows - 1) / rows;
   if (chunks * groups > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n x num_samples too large", who);
   hipStream_t st = as_stream(stream);

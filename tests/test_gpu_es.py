@@ -313,14 +313,15 @@ def test_perturb_of_many_samples(n):
 
 
 @pytest.mark.parametrize("antithetic", [False, True])
-@pytest.mark.parametrize("N", [64, 67])
-def test_perturb_of_many_workgroups_at_odd_phase(N, antithetic):
-    # enough workgroups for four samples each (2,048 of them), the last group
-    # of 67 short; rows of odd length against the same rows in longer,
-    # line-aligned ones
+@pytest.mark.parametrize("n,N", [(600_001, 64), (600_001, 67), (600_001, 17), (1_000_003, 8), (1_200_003, 7), (2_000_003, 10),
+                                 (4_000_003, 3), (8_000_003, 2)])
+def test_perturb_of_many_workgroups_at_odd_phase(n, N, antithetic):
+    # enough workgroups for two or four samples each by the rule on parameters
+    # and samples, the last group short or whole; rows of odd length against
+    # the same rows in longer, line-aligned ones
     import paper_2211_06934_amd as P
-    n, m, seed, sigma = 600_001, 600_032, 21, 0.1
-    assert -(-n // 4096) * -(-N // 4) >= 2048
+    m, seed, sigma = (n + 63) // 32 * 32, 21, 0.1
+    assert -(-n // 4096) * N >= 1900  # workgroups of one sample each
     R = (2 if antithetic else 1) * N
     theta = torch.empty(m, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(2))
     full = torch.empty(R, m, device="cuda")
@@ -330,11 +331,11 @@ def test_perturb_of_many_workgroups_at_odd_phase(N, antithetic):
     torch.cuda.synchronize()
     assert torch.equal(buf[3:3 + R * n].view(R, n), full[:, :n])
     assert torch.all(buf[:3] == 7.0) and torch.all(buf[3 + R * n:] == 7.0)
-    # four samples a workgroup or one (a call of the first three alone)
-    few = torch.empty(3, n, device="cuda")
-    P.es_perturb_gaussian(theta[:n], 3, seed, sigma, False, few)
+    # one sample a workgroup in a call on a range of the parameters' prefix
+    few = torch.empty(N, 100_001, device="cuda")
+    P.es_perturb_gaussian(theta[:100_001], N, seed, sigma, False, few)
     torch.cuda.synchronize()
-    assert torch.equal(few, full[:3, :n])
+    assert torch.equal(few, full[:N, :100_001])
 
 
 @pytest.mark.parametrize("method", ["plain", "baseline", "antithetic"])
