@@ -108,14 +108,15 @@ __device__ __forceinline__ int64_t line_phase(uint64_t leaf) { return (int64_t)(
 //   input leaf); those are computed and not stored.  A wave then makes one
 //   pass whatever its lanes hold.  Leaves of fewer than four elements move
 //   theirs together too, one by one (Few).
-// - element by element, a pass each.
+// - on their own, in a pass beside the vectors': element by element, or all
+//   together (Few).
 // The K-step kernels, whose passes are long, and the single steps served by
 // the Infinity Cache (KEEP) take windows (K = 8, 5,000 leaves of up to 20,000
 // elements: 292 us against 308 element by element; K = 10 on 576 packed leaves
 // 144 against 165; one Adam step, 20,000 leaves of up to 50: 19.7 against 21.9).
-// Single steps that stream from memory go element by element: there a wave
-// whose lanes are not 16 bytes apart costs more than the extra pass (20,000
-// leaves of up to 65,536: forward 586 us with windows, 555 without).
+// Single steps that stream from memory give the ends a pass of their own: there
+// a wave whose lanes are not 16 bytes apart costs more than the extra pass
+// (20,000 leaves of up to 65,536: forward 586 us with windows, 555 without).
 struct Whole {
   int64_t e0;
   __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
@@ -171,8 +172,8 @@ struct WindowOf {
 
 using Window = WindowOf<true>;
 
-// The elements of a leaf of one to three; a slot without an element takes the
-// group's last one, and computes and stores its value once more.
+// A group's one to three elements; a slot without an element takes the group's
+// last one, and computes and stores its value once more.
 struct Few {
   int64_t first;
   int last;  // counted from the first
@@ -265,14 +266,33 @@ __global__ __launch_bounds__(kFB) void adam_fwd_tree_kernel(const SegEntry* __re
   const int64_t gidx = b * kTileGroups + threadIdx.x;
   if (gidx >= ngroups) return;
   const int t = find_leaf(s_goff, W, gidx);
-  on_group<KEEP>(4 * (gidx - s_goff[t]) - line_phase(s_ptr[4][t]), s_numel[t], [&](const auto& a) {
-    f32x4 p = a.load(s_ptr[0][t]);
-    const f32x4 g = a.load(s_ptr[1][t]);
-    f32x4 m = a.load(s_ptr[2][t]), v = a.load(s_ptr[3][t]);
+  const int64_t e0 = 4 * (gidx - s_goff[t]) - line_phase(s_ptr[4][t]), nel = s_numel[t];
+  const auto load = [&](const auto& a, f32x4(&x)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = a.load(s_ptr[q][t]);
+  };
+  const auto finish = [&](const auto& a, f32x4(&x)[4]) {
     const uint64_t out[3] = {s_ptr[4][t], s_ptr[5][t], s_ptr[6][t]};
-    fwd_group(p, g, m, v, c);
-    a.store(out, {p, m, v});
-  });
+    fwd_group(x[0], x[1], x[2], x[3], c);
+    a.store(out, {x[0], x[2], x[3]});
+  };
+  const auto step = [&](const auto& a) {
+    f32x4 x[4];
+    load(a, x);
+    finish(a, x);
+  };
+  if constexpr (KEEP) {
+    on_group<KEEP>(e0, nel, step);
+  } else {
+    // The whole groups' loads are in flight while the lanes at the ends of
+    // leaves move theirs, all of a group's at once: 600,000 leaves of up to 100
+    // elements 286 -> 266 us against the ends after the vectors, one by one.
+    const bool whole = e0 >= 0 && e0 + 4 <= nel;
+    f32x4 x[4];
+    if (whole) load(Whole{e0}, x);
+    if (!whole && e0 + 4 > 0 && e0 < nel) step(Few(e0, nel));
+    if (whole) finish(Whole{e0}, x);
+  }
 }
 
 // Operands: 0 dP, 1 dM, 2 dV (null unless HAS_MV), 3 g, 4 m, 5 v (inputs);
@@ -321,16 +341,8 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
       }
     }
   }
-#pragma unroll
-  for (int u = 0; u < kBU; ++u) {
-    const int t = leaf[u];
-    if (kind[u] == 1) {
-      const Vector a = vector_at<Vector>(e0[u], s_numel[t]);
-      const uint64_t out[3] = {s_ptr[6][t], s_ptr[7][t], s_ptr[8][t]};
-      const f32x4 rg = bwd_group<HAS_MV>(P[u], Mb[u], Vb[u], G[u], M[u], V[u], c);
-      a.store(out, {rg, Mb[u], Vb[u]});
-    }
-  }
+  // Ends of leaves first, while the vectors' loads are in flight (600,000 leaves
+  // of up to 100 elements, streaming, 444 -> 395 us).
 #pragma unroll
   for (int u = 0; u < kBU; ++u) {
     const int t = leaf[u];
@@ -347,6 +359,16 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
         const f32x4 rg = bwd_group<HAS_MV>(p, dm, dv, g, m, v, c);
         a.store(out, {rg, dm, dv});
       });
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kBU; ++u) {
+    const int t = leaf[u];
+    if (kind[u] == 1) {
+      const Vector a = vector_at<Vector>(e0[u], s_numel[t]);
+      const uint64_t out[3] = {s_ptr[6][t], s_ptr[7][t], s_ptr[8][t]};
+      const f32x4 rg = bwd_group<HAS_MV>(P[u], Mb[u], Vb[u], G[u], M[u], V[u], c);
+      a.store(out, {rg, Mb[u], Vb[u]});
     }
   }
 }
