@@ -689,13 +689,15 @@ constexpr int kMaxPerturbRows = 65535 * 8;
 //   n = 1,000,000  N = 8 15.2 / 13.4 / 13.3    9.7 / 9.3 / 9.5
 //                  N = 32 44.7 / 52.8 / 52.9   34.3 / 32.0 / 30.5
 //   n = 2,000,000  N = 3 12.0 / 11.6 / 10.0    8.5 / 9.1 / 7.6 (three sets of buffers in turn)
-//                  N = 8 28.5 / 26.2 / 26.5    19.3 / 16.9 / 15.9
+//   n = 2,400,001  N = 3 13.7 / 14.3 / 14.9    9.5 / 11.4 / 11.3 (rows off 16 bytes: each
+//                  sample's storing costs more and hides theta's second read)
+//   n = 2,000,000  N = 8 28.5 / 26.2 / 26.5    19.3 / 16.9 / 15.9
 //                  N = 12 37.6 / 38.6 / 40.4   26.7 / 24.9 / 23.4
 //   n = 8,300,000  N = 3 43.5 / 40.1 / 37.8    28.9 / 29.2 / 24.5
 //                  N = 8 109.6 / 93.8 / 103.1  74.0 / 66.0 / 61.1
-int perturb_samples(int64_t chunks, int64_t N, bool antithetic) {
+int perturb_samples(int64_t chunks, int64_t N, bool antithetic, bool vec) {
   const int64_t single = chunks * N;  // workgroups of one sample each
-  if (N <= 3) return single < 1400 ? 1 : kLRows;
+  if (N <= 3) return single < (vec ? 1400 : 1900) ? 1 : kLRows;
   if (single < 1900) return 1;
   if (!antithetic) return single < 3600 ? 2 : kLRows;
   if (N < 12) return 2;
@@ -827,12 +829,13 @@ extern "C" int diffopt_es_perturb_gaussian(const float* params, int64_t n, int64
   const int64_t blocks = 64 * ((n + 511) / 512);  // Philox blocks: 64 per 512 parameters
   if ((blocks + kEB - 1) / kEB > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n too large", who);
   const int64_t chunks = (blocks + kLB - 1) / kLB;
-  const int rows = perturb_samples(chunks, num_samples, antithetic != 0);
+  const bool vec = n % 4 == 0 && al16(params) && al16(out);
+  const int rows = perturb_samples(chunks, num_samples, antithetic != 0, vec);
   const int64_t groups = (num_samples + rows - 1) / rows;
   if (chunks * groups > 0x7fffffff) return fail(DIFFOPT_EINVAL, "%s: n x num_samples too large", who);
   hipStream_t st = as_stream(stream);
   const dim3 grid((unsigned)(chunks * groups));
-  if (n % 4 == 0 && al16(params) && al16(out))
+  if (vec)
     hipLaunchKernelGGL(es_perturb_gauss_lines<true>, grid, dim3(kLB), 0, st, params, num_samples, n, seed,
                        (float)sigma, antithetic ? 1 : 0, (uint32_t)groups, rows, out);
   else
