@@ -123,9 +123,6 @@ __device__ __forceinline__ int64_t flat_tile(int64_t b, int64_t ntiles) {
 #endif
 }
 
-__device__ __forceinline__ const f32x4u* cv4(const float* q) { return reinterpret_cast<const f32x4u*>(q); }
-__device__ __forceinline__ f32x4u* v4(float* q) { return reinterpret_cast<f32x4u*>(q); }
-
 // One workgroup per tile; the kernels' grid-stride loop covers the (never
 // reached in practice) case of more tiles than a grid dimension holds.
 int64_t grid_for(int64_t tiles) {
@@ -149,9 +146,9 @@ __global__ __launch_bounds__(B) void adam_fwd_vec(const float* p, const float* g
   for (int64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
     const int64_t i = flat_tile(b, ntiles) * B + threadIdx.x;
     if (i >= nv) continue;
-    const f32x4 P = ld<KEEP>(cv4(p) + i), G = ld<KEEP>(cv4(g) + i), M = ld<KEEP>(cv4(m) + i),
-                V = ld<KEEP>(cv4(v) + i);
-    f32x4u rp, rm, rv, ru;
+    const f32x4 P = ld4<KEEP>(p + 4 * i), G = ld4<KEEP>(g + 4 * i), M = ld4<KEEP>(m + 4 * i),
+                V = ld4<KEEP>(v + 4 * i);
+    f32x4 rp, rm, rv, ru;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const FwdOut o = fwd_elem(P[e], G[e], M[e], V[e], c);
@@ -160,10 +157,10 @@ __global__ __launch_bounds__(B) void adam_fwd_vec(const float* p, const float* g
       rv[e] = o.v;
       ru[e] = o.u;
     }
-    st(v4(po) + i, rp);
-    st(v4(mo) + i, rm);
-    st(v4(vo) + i, rv);
-    if (WU) st(v4(uo) + i, ru);
+    st4(po + 4 * i, rp);
+    st4(mo + 4 * i, rm);
+    st4(vo + 4 * i, rv);
+    if (WU) st4(uo + 4 * i, ru);
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
@@ -186,14 +183,14 @@ __global__ __launch_bounds__(B) void adam_bwd_vec(const float* dP, const float* 
   for (int64_t b = blockIdx.x; b < ntiles; b += gridDim.x) {
     const int64_t i = flat_tile(b, ntiles) * B + threadIdx.x;
     if (i >= nv) continue;
-    const f32x4 P = ld<KEEP>(cv4(dP) + i);
+    const f32x4 P = ld4<KEEP>(dP + 4 * i);
     f32x4 Mb = {0.0f, 0.0f, 0.0f, 0.0f}, Vb = {0.0f, 0.0f, 0.0f, 0.0f};
     if (HAS_MV) {
-      Mb = ld<KEEP>(cv4(dM) + i);
-      Vb = ld<KEEP>(cv4(dV) + i);
+      Mb = ld4<KEEP>(dM + 4 * i);
+      Vb = ld4<KEEP>(dV + 4 * i);
     }
-    const f32x4 G = ld<KEEP>(cv4(g) + i), M = ld<KEEP>(cv4(m) + i), V = ld<KEEP>(cv4(v) + i);
-    f32x4u rg, rm, rv;
+    const f32x4 G = ld4<KEEP>(g + 4 * i), M = ld4<KEEP>(m + 4 * i), V = ld4<KEEP>(v + 4 * i);
+    f32x4 rg, rm, rv;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const BwdOut o = bwd_elem<HAS_MV>(P[e], Mb[e], Vb[e], G[e], M[e], V[e], c);
@@ -201,10 +198,10 @@ __global__ __launch_bounds__(B) void adam_bwd_vec(const float* dP, const float* 
       rm[e] = o.m;
       rv[e] = o.v;
     }
-    st(v4(dgo) + i, rg);
-    st(v4(dmo) + i, rm);
-    st(v4(dvo) + i, rv);
-    if (WDP) st(v4(dpo) + i, (f32x4u)P);
+    st4(dgo + 4 * i, rg);
+    st4(dmo + 4 * i, rm);
+    st4(dvo + 4 * i, rv);
+    if (WDP) st4(dpo + 4 * i, P);
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;
@@ -268,11 +265,11 @@ struct UBwdArgs {
 };
 
 __device__ __forceinline__ void ufwd_vector(int64_t i, const UFwdArgs& a) {
-  f32x4 P = ld(cv4(a.p) + i), M = ld(cv4(a.m0) + i), V = ld(cv4(a.v0) + i);
-  f32x4 G = ld(cv4(a.g[0]) + i);
+  f32x4 P = ld4(a.p + 4 * i), M = ld4(a.m0 + 4 * i), V = ld4(a.v0 + 4 * i);
+  f32x4 G = ld4(a.g[0] + 4 * i);
   for (int s = 0; s < a.K; ++s) {  // a runtime loop keeps the code small
     f32x4 Gn = G;
-    if (s + 1 < a.K) Gn = ld(cv4(a.g[s + 1]) + i);
+    if (s + 1 < a.K) Gn = ld4(a.g[s + 1] + 4 * i);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const FwdOut o = fwd_elem(P[e], G[e], M[e], V[e], a.c[s]);
@@ -281,12 +278,12 @@ __device__ __forceinline__ void ufwd_vector(int64_t i, const UFwdArgs& a) {
       V[e] = o.v;
     }
     if (a.m[s]) {  // uniform: the same for every lane
-      st(v4(a.m[s]) + i, (f32x4u)M);
-      st(v4(a.v[s]) + i, (f32x4u)V);
+      st4(a.m[s] + 4 * i, M);
+      st4(a.v[s] + 4 * i, V);
     }
     G = Gn;
   }
-  st(v4(a.pK) + i, (f32x4u)P);
+  st4(a.pK + 4 * i, P);
 }
 
 __device__ __forceinline__ void ufwd_element(int64_t e, const UFwdArgs& a) {
@@ -323,8 +320,8 @@ __global__ __launch_bounds__(B) void adam_unrolled_fwd_vec(UFwdArgs a) {
 
 template <bool HAS_MV>
 __device__ __forceinline__ void ubwd_step(const f32x4& dP, f32x4& dM, f32x4& dV, const f32x4& g, const f32x4& m,
-                                          const f32x4& v, const AdamCoef& c, f32x4u* dgo) {
-  f32x4u rg;
+                                          const f32x4& v, const AdamCoef& c, float* dgo) {
+  f32x4 rg;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const BwdOut o = bwd_elem<HAS_MV>(dP[e], dM[e], dV[e], g[e], m[e], v[e], c);
@@ -332,25 +329,25 @@ __device__ __forceinline__ void ubwd_step(const f32x4& dP, f32x4& dM, f32x4& dV,
     dM[e] = o.m;
     dV[e] = o.v;
   }
-  st(dgo, rg);
+  st4(dgo, rg);
 }
 
 __device__ __forceinline__ void ubwd_vector(int64_t i, const UBwdArgs& a) {
-  const f32x4 dP = ld(cv4(a.dP) + i);
+  const f32x4 dP = ld4(a.dP + 4 * i);
   f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
-  f32x4 G = ld(cv4(a.g[0]) + i), M = ld(cv4(a.m[0]) + i), V = ld(cv4(a.v[0]) + i);
+  f32x4 G = ld4(a.g[0] + 4 * i), M = ld4(a.m[0] + 4 * i), V = ld4(a.v[0] + 4 * i);
   int s = 0;
   if (a.init_mv) {
-    dM = ld(cv4(a.dm) + i);
-    dV = ld(cv4(a.dv) + i);
+    dM = ld4(a.dm + 4 * i);
+    dV = ld4(a.dv + 4 * i);
   } else {  // the last unrolled step: zero cotangents of its mu, nu outputs
     f32x4 Gn = G, Mn = M, Vn = V;
     if (1 < a.K) {
-      Gn = ld(cv4(a.g[1]) + i);
-      Mn = ld(cv4(a.m[1]) + i);
-      Vn = ld(cv4(a.v[1]) + i);
+      Gn = ld4(a.g[1] + 4 * i);
+      Mn = ld4(a.m[1] + 4 * i);
+      Vn = ld4(a.v[1] + 4 * i);
     }
-    ubwd_step<false>(dP, dM, dV, G, M, V, a.c[0], v4(a.dg[0]) + i);
+    ubwd_step<false>(dP, dM, dV, G, M, V, a.c[0], a.dg[0] + 4 * i);
     G = Gn;
     M = Mn;
     V = Vn;
@@ -359,17 +356,17 @@ __device__ __forceinline__ void ubwd_vector(int64_t i, const UBwdArgs& a) {
   for (; s < a.K; ++s) {  // a runtime loop keeps the code small
     f32x4 Gn = G, Mn = M, Vn = V;
     if (s + 1 < a.K) {
-      Gn = ld(cv4(a.g[s + 1]) + i);
-      Mn = ld(cv4(a.m[s + 1]) + i);
-      Vn = ld(cv4(a.v[s + 1]) + i);
+      Gn = ld4(a.g[s + 1] + 4 * i);
+      Mn = ld4(a.m[s + 1] + 4 * i);
+      Vn = ld4(a.v[s + 1] + 4 * i);
     }
-    ubwd_step<true>(dP, dM, dV, G, M, V, a.c[s], v4(a.dg[s]) + i);
+    ubwd_step<true>(dP, dM, dV, G, M, V, a.c[s], a.dg[s] + 4 * i);
     G = Gn;
     M = Mn;
     V = Vn;
   }
-  st(v4(a.dm) + i, (f32x4u)dM);
-  st(v4(a.dv) + i, (f32x4u)dV);
+  st4(a.dm + 4 * i, dM);
+  st4(a.dv + 4 * i, dV);
 }
 
 __device__ __forceinline__ void ubwd_element(int64_t e, const UBwdArgs& a) {
@@ -549,15 +546,15 @@ struct URBwdArgs {
 
 template <int C>
 __device__ __forceinline__ void urbwd_vector(int64_t i, const URBwdArgs& a) {
-  const f32x4 dP = ld(cv4(a.dP) + i);
-  const f32x4 M0 = ld(cv4(a.m0) + i), V0 = ld(cv4(a.v0) + i);
+  const f32x4 dP = ld4(a.dP + 4 * i);
+  const f32x4 M0 = ld4(a.m0 + 4 * i), V0 = ld4(a.v0 + 4 * i);
   f32x4 G[C];
 #pragma unroll
-  for (int s = 0; s < C; ++s) G[s] = ld(cv4(a.g[s]) + i);
+  for (int s = 0; s < C; ++s) G[s] = ld4(a.g[s] + 4 * i);
   f32x4 dM = {0.0f, 0.0f, 0.0f, 0.0f}, dV = {0.0f, 0.0f, 0.0f, 0.0f};
   if (a.init_mv) {
-    dM = ld(cv4(a.dm) + i);
-    dV = ld(cv4(a.dv) + i);
+    dM = ld4(a.dm + 4 * i);
+    dV = ld4(a.dv + 4 * i);
   }
 #if DIFFOPT_REMAT_QUAD_FLAT
   // each VJP step recomputes its input moments from (M0, V0): C(C-1)/2
@@ -566,8 +563,8 @@ __device__ __forceinline__ void urbwd_vector(int64_t i, const URBwdArgs& a) {
   for (int s = C - 1; s >= 0; --s) {
     f32x4 M, V;
     run_moments<C>(s, M0, V0, G, a.c, M, V);
-    if (s == C - 1 && !a.init_mv) ubwd_step<false>(dP, dM, dV, G[s], M, V, a.c[s], v4(a.dg[s]) + i);
-    else ubwd_step<true>(dP, dM, dV, G[s], M, V, a.c[s], v4(a.dg[s]) + i);
+    if (s == C - 1 && !a.init_mv) ubwd_step<false>(dP, dM, dV, G[s], M, V, a.c[s], a.dg[s] + 4 * i);
+    else ubwd_step<true>(dP, dM, dV, G[s], M, V, a.c[s], a.dg[s] + 4 * i);
   }
 #else
   f32x4 M[C], V[C];  // M[s], V[s]: the moments step s consumed
@@ -581,13 +578,13 @@ __device__ __forceinline__ void urbwd_vector(int64_t i, const URBwdArgs& a) {
       V[s + 1][e] = moment2(G[s][e], V[s][e], a.c[s]);
     }
   }
-  if (a.init_mv) ubwd_step<true>(dP, dM, dV, G[C - 1], M[C - 1], V[C - 1], a.c[C - 1], v4(a.dg[C - 1]) + i);
-  else ubwd_step<false>(dP, dM, dV, G[C - 1], M[C - 1], V[C - 1], a.c[C - 1], v4(a.dg[C - 1]) + i);
+  if (a.init_mv) ubwd_step<true>(dP, dM, dV, G[C - 1], M[C - 1], V[C - 1], a.c[C - 1], a.dg[C - 1] + 4 * i);
+  else ubwd_step<false>(dP, dM, dV, G[C - 1], M[C - 1], V[C - 1], a.c[C - 1], a.dg[C - 1] + 4 * i);
 #pragma unroll
-  for (int s = C - 2; s >= 0; --s) ubwd_step<true>(dP, dM, dV, G[s], M[s], V[s], a.c[s], v4(a.dg[s]) + i);
+  for (int s = C - 2; s >= 0; --s) ubwd_step<true>(dP, dM, dV, G[s], M[s], V[s], a.c[s], a.dg[s] + 4 * i);
 #endif
-  st(v4(a.dm) + i, (f32x4u)dM);
-  st(v4(a.dv) + i, (f32x4u)dV);
+  st4(a.dm + 4 * i, dM);
+  st4(a.dv + 4 * i, dV);
 }
 
 template <int C>

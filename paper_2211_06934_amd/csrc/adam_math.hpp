@@ -12,9 +12,9 @@ namespace diffopt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Four consecutive floats at any 4-byte aligned address: loads and stores of
-// it are the same single 128-bit instructions as those of f32x4 (gfx950
-// accepts dword-aligned 128-bit global accesses).
+// Four consecutive floats at any 4-byte aligned address (ld4, st4): loads and
+// stores of it are the same single 128-bit instructions as those of f32x4
+// (gfx950 accepts dword-aligned 128-bit global accesses).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Coefficients derived on the host in fp64 and rounded once to fp32.
@@ -102,11 +102,6 @@ constexpr int64_t kKeepRunBytes = int64_t(224) << 20;
 
 inline bool keep_run_in_cache(int64_t bytes_per_launch) { return bytes_per_launch <= kKeepRunBytes; }
 
-template <bool KEEP = false, typename T>
-__device__ __forceinline__ T ld(const T* p) {
-  return KEEP ? *p : __builtin_nontemporal_load(p);
-}
-
 template <typename T>
 __device__ __forceinline__ void st(T* p, T v) {
 #if DIFFOPT_NT_STORES
@@ -116,19 +111,40 @@ __device__ __forceinline__ void st(T* p, T v) {
 #endif
 }
 
-// The same for pointers into the global address space (addresses that come
-// from LDS-staged leaf tables).
-template <bool KEEP = false, typename T>
-__device__ __forceinline__ T ld(const __attribute__((address_space(1))) T* p) {
-  return KEEP ? *p : __builtin_nontemporal_load(p);
+// Four floats at a 4-byte aligned address.  These take the address as one of
+// floats: a template over the vector type would deduce f32x4 from a pointer to
+// f32x4u and promise the compiler 16 bytes.
+template <bool KEEP = false>
+__device__ __forceinline__ f32x4 ld4(const float* p) {
+  const f32x4u* q = reinterpret_cast<const f32x4u*>(p);
+  return KEEP ? *q : __builtin_nontemporal_load(q);
 }
 
-template <typename T>
-__device__ __forceinline__ void st(__attribute__((address_space(1))) T* p, T v) {
+template <bool KEEP = false>
+__device__ __forceinline__ void st4(float* p, const f32x4& v) {
+  f32x4u* q = reinterpret_cast<f32x4u*>(p);
 #if DIFFOPT_NT_STORES
-  __builtin_nontemporal_store(v, p);
+  if (!KEEP) __builtin_nontemporal_store((f32x4u)v, q);
+  else *q = v;
 #else
-  *p = v;
+  *q = v;
+#endif
+}
+
+// The same for pointers into the global address space (addresses that come
+// from LDS-staged leaf tables).
+template <bool KEEP = false>
+__device__ __forceinline__ f32x4 ld4(const __attribute__((address_space(1))) float* p) {
+  const __attribute__((address_space(1))) f32x4u* q = (const __attribute__((address_space(1))) f32x4u*)p;
+  return KEEP ? *q : __builtin_nontemporal_load(q);
+}
+
+__device__ __forceinline__ void st4(__attribute__((address_space(1))) float* p, const f32x4& v) {
+  __attribute__((address_space(1))) f32x4u* q = (__attribute__((address_space(1))) f32x4u*)p;
+#if DIFFOPT_NT_STORES
+  __builtin_nontemporal_store((f32x4u)v, q);
+#else
+  *q = v;
 #endif
 }
 

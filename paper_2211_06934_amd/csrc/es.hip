@@ -87,40 +87,36 @@ __global__ __launch_bounds__(kEB) void es_perturb_vec(const float* theta, const 
       }
     return;
   }
-  const f32x4 t = ld<KEEP>(reinterpret_cast<const f32x4u*>(theta) + v);
-  const auto in = [&](int64_t i) { return reinterpret_cast<const f32x4u*>(z + i * n); };
-  const auto to = [&](int64_t i) { return reinterpret_cast<f32x4u*>(o + i * n); };
-  const auto put = [&](f32x4u* p, const f32x4u& x) {
-    if (KEEP_OUT) *p = x;
-    else st(p, x);
-  };
+  const f32x4 t = ld4<KEEP>(theta + 4 * v);
+  const auto in = [&](int64_t i) { return z + i * n; };
+  const auto to = [&](int64_t i) { return o + i * n; };
   if (i0 + P * (ROWS - 1) < N) {
     f32x4 rw[ROWS];
 #pragma unroll
-    for (int u = 0; u < ROWS; ++u) rw[u] = ld<KEEP>(in(i0 + P * u));
+    for (int u = 0; u < ROWS; ++u) rw[u] = ld4<KEEP>(in(i0 + P * u));
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
       const int64_t i = i0 + P * u;
-      f32x4u a, b;
+      f32x4 a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = fmaf(sigma, rw[u][e], t[e]);
         b[e] = fmaf(-sigma, rw[u][e], t[e]);
       }
-      put(to(i), a);
-      if (antithetic) put(to(N + i), b);
+      st4<KEEP_OUT>(to(i), a);
+      if (antithetic) st4<KEEP_OUT>(to(N + i), b);
     }
   } else {
     for (int64_t i = i0; i < N; i += P) {
-      const f32x4 rw = ld<KEEP>(in(i));
-      f32x4u a, b;
+      const f32x4 rw = ld4<KEEP>(in(i));
+      f32x4 a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         a[e] = fmaf(sigma, rw[e], t[e]);
         b[e] = fmaf(-sigma, rw[e], t[e]);
       }
-      put(to(i), a);
-      if (antithetic) put(to(N + i), b);
+      st4<KEEP_OUT>(to(i), a);
+      if (antithetic) st4<KEEP_OUT>(to(N + i), b);
     }
   }
 }
@@ -153,7 +149,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
   }
   if (!on[0]) return;
   const auto row = [&](int64_t i, int q) {
-    return reinterpret_cast<const f32x4u*>(noise + i * n) + v0 + (int64_t)q * kEB;
+    return noise + i * n + 4 * (v0 + (int64_t)q * kEB);
   };
   int64_t i = 0;
   for (; i + kUnroll <= N; i += kUnroll) {
@@ -162,7 +158,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
     for (int u = 0; u < kUnroll; ++u)
 #pragma unroll
       for (int q = 0; q < U; ++q)
-        if (on[q]) r[u][q] = ld(row(i + u, q));
+        if (on[q]) r[u][q] = ld4(row(i + u, q));
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const float wi = w[i + u];
@@ -178,7 +174,7 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
 #pragma unroll
     for (int q = 0; q < U; ++q)
       if (on[q]) {
-        const f32x4 r = ld(row(i, q));
+        const f32x4 r = ld4(row(i, q));
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[q][e] = fmaf(wi, r[e], acc[q][e]);
       }
@@ -186,10 +182,10 @@ __global__ __launch_bounds__(kEB) void es_estimate_vec(const float* noise, const
 #pragma unroll
   for (int q = 0; q < U; ++q)
     if (on[q]) {
-      f32x4u out;
+      f32x4 out;
 #pragma unroll
       for (int e = 0; e < 4; ++e) out[e] = scale * acc[q][e];
-      st(reinterpret_cast<f32x4u*>(grad) + v0 + (int64_t)q * kEB, out);
+      st4(grad + 4 * (v0 + (int64_t)q * kEB), out);
     }
 }
 
@@ -263,7 +259,7 @@ __global__ __launch_bounds__(kSB) void es_estimate_split(const float* noise, con
     for (; i + kInFlight <= hi; i += kInFlight) {
       f32x4 r[kInFlight];
 #pragma unroll
-      for (int u = 0; u < kInFlight; ++u) r[u] = ld(reinterpret_cast<const f32x4u*>(z + (i + u) * n));
+      for (int u = 0; u < kInFlight; ++u) r[u] = ld4(z + (i + u) * n);
 #pragma unroll
       for (int u = 0; u < kInFlight; ++u) {
         const float wi = w[i + u];
@@ -273,7 +269,7 @@ __global__ __launch_bounds__(kSB) void es_estimate_split(const float* noise, con
     }
     for (; i < hi; ++i) {
       const float wi = w[i];
-      const f32x4 r = ld(reinterpret_cast<const f32x4u*>(z + i * n));
+      const f32x4 r = ld4(z + i * n);
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] = fmaf(wi, r[e], acc[e]);
     }

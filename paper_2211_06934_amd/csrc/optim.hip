@@ -35,8 +35,8 @@ __global__ __launch_bounds__(B) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int64_
     if (i >= nv) continue;
     f32x4 x[Op::NIN];
 #pragma unroll
-    for (int a = 0; a < Op::NIN; ++a) x[a] = ld<KEEP>(reinterpret_cast<const f32x4u*>(s.in[a]) + i);
-    f32x4u y[Op::NOUT];
+    for (int a = 0; a < Op::NIN; ++a) x[a] = ld4<KEEP>(s.in[a] + 4 * i);
+    f32x4 y[Op::NOUT];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float xi[Op::NIN], yo[Op::NOUT];
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(B) void ew_vec(Streams<Op::NIN, Op::NOUT> s, int64_
       for (int b = 0; b < Op::NOUT; ++b) y[b][e] = yo[b];
     }
 #pragma unroll
-    for (int b = 0; b < Op::NOUT; ++b) st(reinterpret_cast<f32x4u*>(s.out[b]) + i, y[b]);
+    for (int b = 0; b < Op::NOUT; ++b) st4(s.out[b] + 4 * i, y[b]);
   }
   if (blockIdx.x == gridDim.x - 1) {
     int64_t e;

@@ -120,12 +120,12 @@ __device__ __forceinline__ int64_t line_phase(uint64_t leaf) { return (int64_t)(
 struct Whole {
   int64_t e0;
   __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
-    return ld((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, e0));
+    return ld4(at<const float>(leaf, e0));
   }
   template <int N>
   __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
 #pragma unroll
-    for (int q = 0; q < N; ++q) st((gptr<f32x4u>)at<float>(leaf[q], e0), (f32x4u)x[q]);
+    for (int q = 0; q < N; ++q) st4(at<float>(leaf[q], e0), x[q]);
   }
 };
 
@@ -153,13 +153,13 @@ struct WindowOf {
     own = d < 0 ? 15 >> -d : (15 << d) & 15;
   }
   __device__ __forceinline__ f32x4 load(uint64_t leaf) const {
-    return ld<KEEP>((const __attribute__((address_space(1))) f32x4u*)at<const float>(leaf, w));
+    return ld4<KEEP>(at<const float>(leaf, w));
   }
   template <int N>
   __device__ __forceinline__ void store(const uint64_t (&leaf)[N], const f32x4 (&x)[N]) const {
     if (own == 15) {
 #pragma unroll
-      for (int q = 0; q < N; ++q) st((gptr<f32x4u>)at<float>(leaf[q], w), (f32x4u)x[q]);
+      for (int q = 0; q < N; ++q) st4(at<float>(leaf[q], w), x[q]);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)

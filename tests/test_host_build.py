@@ -31,6 +31,17 @@ def test_flat_kernels_refuse_workgroups_without_the_head_lanes():
         assert bad.returncode != 0 and "head" in bad.stderr, macro
 
 
+@needs_hipcc
+@pytest.mark.parametrize("source", ["adam.hip", "es.hip", "optim.hip", "treemap.hip"])
+def test_wide_accesses_promise_no_more_than_four_byte_alignment(source):
+    # buffers and leaves start at any 4-byte aligned address: no 128-bit access
+    # may go through a type that tells the compiler 16 bytes
+    res = subprocess.run([HIPCC, "--offload-arch=gfx950", "--cuda-device-only", "-fsyntax-only", "-std=c++17",
+                          "-Werror=align-mismatch", "-Werror=cast-align", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                          os.path.join(CSRC, source)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-2000:]
+
+
 @pytest.mark.parametrize("binding", [None, b"not a library"])
 def test_package_runs_on_the_library_alone(tmp_path, binding):
     # without a usable native binding (not built, or built against another
