@@ -134,8 +134,8 @@ int64_t grid_for(int64_t tiles) {
 // Vector kernels: tile t covers vectors [t*B, (t+1)*B) for B threads per
 // workgroup, so each load instruction of a wave is one contiguous 1 KiB.
 // Workgroups walk tiles with a grid stride (one tile each when the grid covers
-// them all).  Full tiles skip the bounds check.  The last workgroup also moves
-// the head and the n % 4 tail element by element (see line_head).
+// them all).  The last workgroup also moves the head and the n % 4 tail element
+// by element (see line_head).
 
 template <bool WU, int B, bool KEEP>
 __global__ __launch_bounds__(B) void adam_fwd_vec(const float* p, const float* g, const float* m, const float* v,
@@ -301,9 +301,8 @@ __device__ __forceinline__ void ufwd_element(int64_t e, const UFwdArgs& a) {
   a.pK[e] = P;
 }
 
-// Tile t covers 16-byte vectors [t B, (t+1) B) for B threads per workgroup;
-// only the last tile checks bounds, and the last workgroup also runs the
-// n % 4 tail elements.
+// Tile t covers 4-element vectors [t B, (t+1) B) for B threads per workgroup;
+// the last workgroup also runs the head and the n % 4 tail elements.
 template <int B>
 __global__ __launch_bounds__(B) void adam_unrolled_fwd_vec(UFwdArgs a) {
   const int64_t nv = a.n >> 2;

@@ -7,7 +7,8 @@
 //   estimate:  grad_j = scale * sum_i w_i z_ij   (weights from the caller's f)
 // The estimate is a weighted reduction of N rows: a [1 x N] x [N x n] product
 // with about 0.5 flop per byte, HBM-bound, so it is a stream (each lane owns one
-// 16-byte slice of grad and walks the N rows), not a matrix-core contraction.
+// or several 16-byte slices of grad and walks the N rows), not a matrix-core
+// contraction.
 #include <cmath>
 
 #include "adam_math.hpp"
@@ -327,7 +328,7 @@ __device__ __forceinline__ void mul128(uint64_t c, uint64_t& lo, uint64_t& hi) {
 // registers, becomes the high word of the fourth one's addend: three moves and
 // selects a product instead of five and a half moves and adds (205 instead of
 // 240 VALU instructions per block and sample; the pass at n = 11,689,512, N =
-// 64, perturb then estimate, 1.70 -> 1.62 ms: its generator keeps the chip at
+// 64, perturb then estimate, 1.655 -> 1.598 ms: its generator keeps the chip at
 // its power limit).  The two third
 // multiply-adds and the selects share one asm statement because an SGPR
 // written by a vector instruction may be read by another only two wait states
@@ -630,7 +631,9 @@ __global__ __launch_bounds__(kEB) void es_weights_kernel(const float* __restrict
 // Slots per workgroup of a split estimate over `work` slots and N samples, or 0
 // for the kernel that walks all samples in one lane: split while its lanes
 // cannot fill the chip, and only where every group gets a sample.
-// Measured on MI355X, microseconds plain / 64 slots / 16 slots:
+// Measured on MI355X, microseconds a call back to back, plain (four slices a
+// lane for explicit noise) / 64 slots / 16 slots; the smallest are bound by the
+// calls (n = 1,761, N = 256: 3.5 in the kernel):
 //   explicit noise (slots of 4)  n = 1,761, N = 256: 90 / 8.0 / 4.6;
 //     n = 112,261, N = 64: 19.4 / 5.8 / 9.4; n = 400,001, N = 16: 6.3 / 7.5 / 22,
 //     N = 64: 28.8 / 19.4 / 28, N = 256: 109 / 73 / 88; n = 1,000,003, N = 64:

@@ -5,8 +5,8 @@
 // arithmetic is in optim_ops.hpp.
 // Like Adam they are HBM-bound elementwise streams; they share one generic
 // kernel skeleton with the measured Adam launch shape (1024-thread workgroups,
-// one 4-element vector per lane per array, bounds checks only on the last tile,
-// vectors counted from a line boundary of the first output).
+// 512 for calls that fit the Infinity Cache, one 4-element vector per lane per
+// array, vectors counted from a line boundary of the first output).
 #include <cmath>
 #include <initializer_list>
 

@@ -374,12 +374,13 @@ __global__ __launch_bounds__(kBB) void adam_bwd_tree_kernel(const SegEntry* __re
 }
 
 // ---- fused K-step leaf-direct kernels ----------------------------------------------
-// The K-step driver in one launch per kTK steps, as the flat driver does it:
-// each lane finds its group once, then walks the steps with the running params
+// The K-step driver, several steps a launch (kTK, kTLongK), as the flat driver
+// does it: each lane finds its group once, then walks the steps with the running params
 // (forward) or dM, dV (backward) in registers, loading the next step's inputs
 // before the current step's arithmetic.  The window stages the leaf address
 // of every operand tree of every step in dynamic LDS (NA x kWindowMax x 8
-// bytes: 18.5 KiB for the backward at 8 steps).  One group per lane, one
+// bytes: 18.5 KiB for the backward at 8 steps, 27.5 for the forward at 16).  One
+// group per lane, one
 // table tile (512 groups) per workgroup.
 constexpr int kTK = 8;  // steps per fused launch, VJP and small trees
 // Steps per launch of the tiled forward: a boundary between launches sends
@@ -1005,9 +1006,9 @@ int launch_fwd_tree(const diffopt_segtable* t, const LeafArrays<7>& arr, const A
 }
 
 // Workgroups of the leaf-direct VJP resident per CU.  Its registers allow
-// seven; with six reads and three writes per element that many oversubscribe
-// the memory system, and five ran the 20,000-leaf tree's VJP 4% faster (four:
-// the same; six: 1.5% slower).  The launch reserves otherwise unused dynamic
+// six (eight without incoming moment cotangents); with six reads and three writes per element that many oversubscribe
+// the memory system, and five ran the 20,000-leaf tree's VJP 4% faster than the
+// seven an earlier form allowed (four: the same; six: 1.5% slower).  The launch reserves otherwise unused dynamic
 // LDS so that no more than kBwdTreeResident workgroups fit in a CU's 160 KiB.
 constexpr int kBwdTreeResident = 5;
 constexpr size_t kLdsPerCU = 160 * 1024;
@@ -1208,7 +1209,8 @@ extern "C" int diffopt_adam_unrolled_bwd_tree(const diffopt_segtable* table, int
   hipStream_t st = as_stream(stream);
   // Last steps first: runs of steps whose input states are stored take one
   // launch per kTK steps; a run j+1..khi after one stored state j takes one
-  // launch that recomputes the states it needs.
+  // launch that recomputes the states it needs, two neighbouring ones together
+  // where they stream from memory (TwoRuns).
   for (int64_t khi = K; khi >= 1;) {
     const int32_t init_mv = khi != K;  // the first launch starts from zero cotangents of mu_K, nu_K
     if (mu_traj[khi - 1]) {
