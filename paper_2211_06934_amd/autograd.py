@@ -243,7 +243,8 @@ class SGDTreeFn(torch.autograd.Function):
     apply(table, hyper, has_trace, *leaves) with leaves = p_1..p_S, g_1..g_S
     and, when has_trace, the trace t_1..t_S; returns p'_1..p'_S and, when
     momentum > 0, t'_1..t'_S.  The VJP is linear in the cotangents, so nothing
-    is saved; absent cotangents go to the kernel as NULL (zero)."""
+    is saved.  Torch fills absent cotangents with zeros before the backward
+    sees them; a trace cotangent group that is None goes to the kernel as NULL."""
 
     @staticmethod
     def forward(ctx, table, hyper: SGDHyper, has_trace: bool, *leaves):

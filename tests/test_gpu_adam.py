@@ -1,7 +1,7 @@
 """GPU parity of the fused Adam forward and VJP kernels against the oracle.
 
 Sizes span several workgroup tiles plus ragged tails (n % 4 != 0), the edge
-cases n = 0..5, misaligned pointers (scalar path), in-place aliasing, and the
+cases n = 0..5, misaligned pointers, in-place aliasing, and the
 0/0 point of the VJP.  Tolerances: forward 1e-5, backward 1e-4, per element
 relative to the oracle's term-magnitude scale (see tests/support.py).
 """

@@ -47,7 +47,7 @@ def test_es_estimate_zero_samples_and_misaligned():
     Z = normal(N * n, 1.0, "ges", "misc", 3).reshape(N, n)
     w = normal(N, 1.0, "ges", "cot_p", 3)
     buf = torch.zeros(N * n + 1, device="cuda")
-    zv = buf[1:]  # 4-byte but not 16-byte aligned: element path
+    zv = buf[1:]  # 4-byte but not 16-byte aligned
     zv.copy_(_dev(Z).reshape(-1))
     g = torch.empty(n, device="cuda")
     P.es_estimate(zv, _dev(w), 0.5, g)
@@ -171,7 +171,7 @@ def test_gaussian_paths_misaligned_and_empty():
     import paper_2211_06934_amd as P
     n, N, seed = 4096, 6, 99
     buf = torch.zeros(n + 1, device="cuda")
-    theta = buf[1:]  # 4-byte but not 16-byte aligned: the element path
+    theta = buf[1:]  # 4-byte but not 16-byte aligned
     theta.copy_(_dev(normal(n, 0.05, "ges", "p0", 3)))
     out = torch.empty(N * n + 1, device="cuda")[1:].view(N, n)
     P.es_perturb_gaussian(theta, N, seed, 0.1, False, out)
@@ -183,7 +183,7 @@ def test_gaussian_paths_misaligned_and_empty():
     P.es_estimate_gaussian(f, "plain", N, seed, 0.1, g1)
     P.es_estimate_gaussian(f, "plain", N, seed, 0.1, g2)
     torch.cuda.synchronize()
-    assert torch.equal(out, ref) and torch.equal(g1, g2)  # vector and element paths agree bit for bit
+    assert torch.equal(out, ref) and torch.equal(g1, g2)  # the alignment does not change a bit
     # no samples: the estimate is zero; no parameters: nothing is touched
     z = torch.full((n,), 7.0, device="cuda")
     P.es_estimate_gaussian(torch.empty(0, device="cuda"), "plain", 0, seed, 0.1, z)

@@ -6,7 +6,7 @@ expected values are the oracle's flat step on the packed leaves (forward 1e-5,
 backward 1e-4 of the term-magnitude scale), and the GPU's tree result must
 also equal the GPU's flat kernels on the flattened tree bit for bit (the same
 per-element arithmetic).  Trees hold empty and tiny leaves, separate
-allocations and views out of 16-byte phase (element path); a small tree
+allocations and views out of 16-byte phase; a small tree
 (9 nonempty leaves) takes the one-element-per-lane small-tree kernel.  The MAML tests
 take the meta-gradient through K inner steps of the conv-net, against the same
 loop built on torch.optim's functional SGD / RMSprop, in fp64 on the CPU and in

@@ -3,7 +3,7 @@
 By definition the tree-map step equals flatten -> flat step -> unflatten, so
 the expected values are the oracle's flat step applied to the oracle's pack of
 the leaves, split back with the oracle's unpack.  Trees cover empty and tiny
-leaves, ragged sizes, leaves out of 16-byte phase (element path), in-place
+leaves, ragged sizes, leaves out of 16-byte phase, in-place
 aliasing, and the 20,000-leaf workload at full size (sampled leaves).
 """
 import numpy as np

@@ -1,14 +1,15 @@
-"""The leaf-direct K-step driver runs its steps fused, up to 8 per launch, with
+"""The leaf-direct K-step driver runs its steps fused, up to 16 per launch in the
+forward and 8 in the VJP, with
 each lane's running state in registers.  Each step's arithmetic is that of the
 single-step leaf-direct kernels, in the same order, so the fused driver must
 reproduce the step-by-step composition of diffopt_adam_fwd_tree /
 diffopt_adam_bwd_tree bit for bit: across launch chunks (K = 8, 9, 17), with
-empty leaves, leaves out of 16-byte phase (element path), nonzero initial
+empty leaves, leaves out of 16-byte phase, nonzero initial
 moments and in-place p_K == p0.
 
 With intermediate trajectory entries left NULL, the VJP recomputes those
 states from the latest stored one; the results must equal the fully stored
-run bit for bit, across the forward's 8-step launch boundaries (where the
+run bit for bit, across the forward's 16-step launch boundaries (where the
 running moments pass through the final-state trees) and at the 20,000-leaf
 benchmark size."""
 import numpy as np
@@ -115,9 +116,10 @@ def test_fused_tree_equals_stepwise_bitwise(K, count0, er, mode, in_place):
     (3, 5, 1e-8, "packed-views", False, ()),
     (8, 0, 0.0, "separate", True, ()),                  # one recomputed run of the maximum length
     (9, 2, 1e-8, "packed-views", True, (8,)),
-    (11, 0, 1e-8, "separate", False, (3, 10)),          # state 8 unstored: carried across the launch boundary
+    (11, 0, 1e-8, "separate", False, (3, 10)),          # runs of 3, 7 and 1 steps
     (17, 0, 0.0, "packed-views", False, (2, 9, 16)),
-    (20, 1, 1e-8, "separate", True, (1, 2, 3, 10, 17)),  # stored runs and recomputed runs mixed
+    (20, 1, 1e-8, "separate", True, (1, 2, 3, 10, 17)),  # stored and recomputed runs mixed; state 16 unstored: carried
+                                                        # across the forward's launch boundary
 ])
 def test_fused_tree_recomputed_trajectory_equals_stored_bitwise(K, count0, er, mode, in_place, keep):
     # unstored intermediate states (NULL trajectory entries) are recomputed by

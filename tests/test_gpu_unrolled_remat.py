@@ -12,7 +12,7 @@ stored driver's bit for bit, whatever the store policy:
   - irregular policies whose unstored runs cross the forward's 16-step launch
     boundaries (the running moments then pass through the final-state
     buffers);
-  - ragged n (tail elements), misaligned buffers (element kernels) and an
+  - ragged n (tail elements), misaligned buffers and an
     in-place p_K == p0.
 
 The fully stored driver is itself checked against the oracle elsewhere; one
